@@ -261,8 +261,8 @@ size_t tsm2x_workspace_size(int op, int64_t m, int64_t k, int64_t n,
                             int dtype);
 
 /* Name of the main kernel a call (op, m, k, n, dtype) launches, as
- * profilers print it (for matching timings with profiler summaries), with
- * A 16-byte aligned and lda a multiple of 16 bytes.  Static storage; NULL
+ * profilers print it (for matching timings with profiler summaries).
+ * Static storage; NULL
  * for ops other than TSM_OP_TSM2R, the 16-bit forms, or empty or
  * unsupported shapes. */
 const char* tsm2x_kernel_name(int op, int64_t m, int64_t k, int64_t n, int dtype);

@@ -77,9 +77,8 @@ bool valid_dtype(int dt) { return dt >= TSM_F64 && dt <= TSM_F16_SPLIT; }
 bool plain_dtype(int dt) { return dt == TSM_F64 || dt == TSM_F32; }
 int esize(int dt) { return dt == TSM_F64 ? 8 : 4; }
 
-bool vec_ok(const void* p, int64_t ld, int es) {
-    return ((uintptr_t)p & 15u) == 0 && ((ld * es) % 16) == 0;
-}
+// 16-byte loads of 16-bit planes
+bool planes_vec(const void* p, int64_t ld) { return ((uintptr_t)p & 15u) == 0 && ld % 8 == 0; }
 
 int pow2_ge(int64_t n) {
     int p = 1;
@@ -99,9 +98,9 @@ NNPin pin_of(int64_t m, int64_t k, int64_t n, int dtype) {
     return it == g_pins.end() ? NNPin{0, -1} : it->second;
 }
 
-int plan_nn(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P) {
+int plan_nn(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P) {
     const NNPin pin = pin_of(m, k, n, dtype);
-    return plan_tsm2r(m, k, n, dtype, cus, vec, P, &pin);
+    return plan_tsm2r(m, k, n, dtype, cus, P, &pin);
 }
 
 struct RTPlan {
@@ -314,7 +313,8 @@ int check_ex(int transA, int transB, int64_t m, int64_t k, int64_t n, const void
 int64_t bt_ld(int64_t k, int ce) { return cdiv(k, 16 / ce) * (16 / ce); }
 
 // Bytes of split partials of a TSM2R-kernel product of at most 32 columns,
-// for the kernel instance the call launches (`vec`: 16-byte loads of A).
+// for the kernel instance the call launches (`vec`: 16-byte loads of the
+// 16-bit planes).
 size_t tsm2r_part(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool vec) {
     const int cus = cu_count();
     if (!plain_dtype(dtype)) {
@@ -324,7 +324,7 @@ size_t tsm2r_part(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool v
     }
     if (transA) return plan_tn(k, m, n, dtype, cus).ws;
     NNPlan P{};
-    return plan_nn(m, k, n, dtype, cus, vec, &P) ? 0 : P.ws;
+    return plan_nn(m, k, n, dtype, cus, &P) ? 0 : P.ws;
 }
 
 // Workspace of a TSM2R-kernel product of at most 32 columns: the split
@@ -337,8 +337,8 @@ size_t tsm2r_ws(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool tra
     return part + (transB ? (size_t)bt_ld(k, ce) * n * ce : 0);
 }
 
-// The most any plan of the call can need (the query does not know A's
-// alignment, which picks the kernel instance).
+// The most any plan of the call can need (the query does not know the
+// planes' alignment, which picks the kernel instance).
 size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool transB) {
     const size_t a = tsm2r_ws(transA, m, k, n, dtype, transB, true);
     const size_t b = tsm2r_ws(transA, m, k, n, dtype, transB, false);
@@ -390,7 +390,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     }
     // TSM2R kernels; workspace = [split partials][B copied column-major, or
     // B's packed 16-bit terms for the precision form]
-    const bool avec = vec_ok(A, lda, plain_dtype(dtype) ? esize(dtype) : 2);
+    const bool avec = plain_dtype(dtype) || planes_vec(A, lda);
     void* w = nullptr;
     int rc = get_ws(tsm2r_ws(transA, m, k, n, dtype, transB, avec), ws, ws_bytes, &w);
     if (rc) return rc;
@@ -436,7 +436,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         return check_launch("tn_kernel");
     }
     NNPlan P{};
-    if (plan_nn(m, k, n, dtype, cus, vec_ok(A, lda, esize(dtype)), &P)) return TSM_ERR_UNSUPPORTED;
+    if (plan_nn(m, k, n, dtype, cus, &P)) return TSM_ERR_UNSUPPORTED;
     LaunchNN L{};
     L.fn = P.fn;
     L.m = m; L.k = k; L.n = n; L.A = A; L.lda = lda; L.B = Bk; L.ldb = ldbk; L.C = C; L.ldc = ldc;
@@ -757,7 +757,7 @@ const char* tsm2x_kernel_name(int op, int64_t m, int64_t k, int64_t n, int dtype
     if (op != TSM_OP_TSM2R || m <= 0 || k <= 0 || n <= 0 || n > 32 || !plain_dtype(dtype))
         return nullptr;
     NNPlan P{};
-    return plan_nn(m, k, n, dtype, cu_count(), true, &P) ? nullptr : P.name;
+    return plan_nn(m, k, n, dtype, cu_count(), &P) ? nullptr : P.name;
 }
 
 int tsm2x_tsm2r_plan(int64_t m, int64_t k, int64_t n, int dtype, int* slices, int* tall,
@@ -768,7 +768,7 @@ int tsm2x_tsm2r_plan(int64_t m, int64_t k, int64_t n, int dtype, int* slices, in
     if (!plain_dtype(dtype)) return -4;
     const int c = cu_count();
     NNPlan P{};
-    if (plan_nn(m, k, n, dtype, c, true, &P)) return TSM_ERR_UNSUPPORTED;
+    if (plan_nn(m, k, n, dtype, c, &P)) return TSM_ERR_UNSUPPORTED;
     if (slices) *slices = P.S;
     if (tall) *tall = P.tall;
     if (tiles) *tiles = P.tiles;

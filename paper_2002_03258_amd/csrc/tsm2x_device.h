@@ -22,19 +22,23 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
+// `mem`: the same vector in global memory, aligned as its elements are.  The
+// 16-byte global loads and stores of gfx950 need no more than 4-byte
+// alignment, so columns of any leading dimension and base address take them.
 template <typename T, int N>
 struct VecOf {
     typedef T type __attribute__((ext_vector_type(N)));
+    typedef T mem __attribute__((ext_vector_type(N), aligned(sizeof(T))));
 };
 
 // RL consecutive elements starting at p: one 16-byte non-temporal load when
-// the caller has checked alignment (VEC) and bounds (FULL); otherwise
-// element-wise loads guarded by `valid` elements remaining.
-template <typename T, int RL, bool VEC>
+// all of them are in range (full); otherwise element-wise loads guarded by
+// `valid` elements remaining.
+template <typename T, int RL>
 __device__ __forceinline__ void load_run(const T* __restrict__ p, int64_t valid,
                                          bool full, T (&out)[RL]) {
-    if (VEC && full) {
-        typedef typename VecOf<T, RL>::type V;
+    if (full) {
+        typedef typename VecOf<T, RL>::mem V;
         V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
 #pragma unroll
         for (int r = 0; r < RL; ++r) out[r] = v[r];
@@ -47,11 +51,11 @@ __device__ __forceinline__ void load_run(const T* __restrict__ p, int64_t valid,
 // The store counterpart; NT = false for ordinary stores (a wavefront whose
 // 16-byte stores leave gaps that a second instruction fills: non-temporal
 // stores of such half-filled lines reach HBM as separate partial writes).
-template <typename T, int RL, bool VEC, bool NT = true>
+template <typename T, int RL, bool NT = true>
 __device__ __forceinline__ void store_run(T* __restrict__ p, int64_t valid,
                                           bool full, const T (&v)[RL]) {
-    if (VEC && full) {
-        typedef typename VecOf<T, RL>::type V;
+    if (full) {
+        typedef typename VecOf<T, RL>::mem V;
         V x;
 #pragma unroll
         for (int r = 0; r < RL; ++r) x[r] = v[r];
@@ -111,14 +115,17 @@ __device__ __forceinline__ T beta_out(double v, double beta, const T* p) {
 // (split_reduce_kernel) adds the slices in order.  `red` is LDS scratch of
 // [NSUM][PG][TR] doubles; put(pg, red) stores this wavefront's values of
 // columns pg .. pg+PG-1 (NSUM = WK: every wavefront all TR rows, summed;
-// NSUM = 1: each wavefront its own rows of the tile).  C := beta*C + sum (C is
-// read only if beta != 0).
+// NSUM = 1: each wavefront its own rows of the tile).  The tile's values start
+// at row `row0` of C: tile * TR, or less for a last tile moved up to be
+// whole, whose rows before tile * TR belong to the tile before and are left
+// to it.  C := beta*C + sum (C is read only if beta != 0).
 template <typename T, int NP, int WK, int TR, int PG, int NSUM = WK, typename Put>
 __device__ __forceinline__ void nn_finish(int64_t m, int n, T* __restrict__ C, int64_t ldc,
-                                          double beta, int64_t tile, int s, int nsl,
-                                          double* __restrict__ part, double* red, Put&& put) {
+                                          double beta, int64_t tile, int64_t row0, int s,
+                                          int nsl, double* __restrict__ part, double* red,
+                                          Put&& put) {
     constexpr int NT = WAVE * WK;
-    const int64_t row0 = tile * TR;
+    const int64_t rowt = tile * TR;
 #pragma unroll
     for (int pg = 0; pg < NP; pg += PG) {
         if (pg < n) {
@@ -132,11 +139,11 @@ __device__ __forceinline__ void nn_finish(int64_t m, int n, T* __restrict__ C, i
                 double v = red[pp * TR + rr];
 #pragma unroll
                 for (int ww = 1; ww < NSUM; ++ww) v += red[(ww * PG + pp) * TR + rr];
-                if (p < n && row < m) {
+                if (p < n && row >= rowt && row < m) {
                     if (nsl == 1)
                         C[row + p * ldc] = beta_out(v, beta, C + row + p * ldc);
                     else
-                        part[((tile * nsl + s) * NP + p) * TR + rr] = v;
+                        part[((tile * nsl + s) * NP + p) * TR + (row - rowt)] = v;
                 }
             }
         }

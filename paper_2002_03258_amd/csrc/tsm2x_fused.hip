@@ -31,7 +31,7 @@ namespace tsm {
 // through LDS, so a lane loads 8 rows of a column (one 16-byte run per plane)
 // and writes them, widened to float (hi + lo is exact in float), into the
 // staged block they belong to.
-template <typename T, int NTK, int NTN, int RG, bool VEC, int AF, bool ASPLIT>
+template <typename T, int NTK, int NTN, int RG, bool NTS, bool PV, int AF, bool ASPLIT>
 __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
     int64_t m, int k, int n, const void* __restrict__ Av, const uint16_t* __restrict__ Alo,
     int64_t lda, const T* __restrict__ B, int64_t ldb, const T* __restrict__ dC, int64_t lddc,
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
 #pragma unroll
         for (int pl = 0; pl < (ASPLIT ? 2 : 1); ++pl) {
             const uint16_t* h = (pl == 0 ? (const uint16_t*)Av : Alo) + off;
-            if (VEC && full) {
+            if (PV && full) {
                 const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(h));
 #pragma unroll
                 for (int e = 0; e < 4; ++e) d[pl][e] = v[e];
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
             for (int st = 0; st < KSN; ++st) {
                 const int p = 4 * st + kk;
                 if (p < n)
-                    load_run<T, RL, VEC>(dC + r + p * lddc, m - r, full, xv[st][g]);
+                    load_run<T, RL>(dC + r + p * lddc, m - r, full, xv[st][g]);
                 else
 #pragma unroll
                     for (int q = 0; q < RL; ++q) xv[st][g][q] = T(0);
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
                 for (int st = 0; st < KSK; ++st) {
                     const int c = 4 * st + kk;
                     if (c < k)
-                        load_run<T, RL, VEC>((const T*)Av + r + (int64_t)c * lda, m - r, full,
+                        load_run<T, RL>((const T*)Av + r + (int64_t)c * lda, m - r, full,
                                              xa[AF < 0 ? st : 0][g]);
                     else
 #pragma unroll
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
                         T v[RL];
 #pragma unroll
                         for (int q = 0; q < RL; ++q) v[q] = acca[g][q][t][rr];
-                        store_run<T, RL, VEC>(dA + r + (int64_t)col * ldda, m - r, full, v);
+                        store_run<T, RL, NTS>(dA + r + (int64_t)col * ldda, m - r, full, v);
                     }
                 }
         }
@@ -275,7 +275,7 @@ template <typename T, int NTK, int NTN, int AF, bool ASPLIT>
 static int bwd_launch(const LaunchBwd& L, int64_t* blocks_out, hipStream_t st, bool plan_only) {
     constexpr int RG = 2;
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
-    static const int occ = fused_occupancy(tsm2l_bwd_kernel<T, NTK, NTN, RG, true, AF, ASPLIT>);
+    static const int occ = fused_occupancy(tsm2l_bwd_kernel<T, NTK, NTN, RG, true, true, AF, ASPLIT>);
     const int64_t ntiles = (L.m + TR - 1) / TR;
     int64_t bx = (int64_t)L.cus * occ;
     const int64_t need = (ntiles + 3) / 4;
@@ -283,22 +283,22 @@ static int bwd_launch(const LaunchBwd& L, int64_t* blocks_out, hipStream_t st, b
     if (bx < 1) bx = 1;
     *blocks_out = bx;
     if (plan_only) return 0;
-    // A: 16-byte runs of T, or of the 16-bit planes
-    const bool avec = AF < 0 ? ((uintptr_t)L.A & 15u) == 0 && (L.lda * (int64_t)sizeof(T)) % 16 == 0
-                             : ((uintptr_t)L.A & 15u) == 0 && L.lda % 8 == 0;
-    const bool vec = avec && ((uintptr_t)L.dC & 15u) == 0 && ((uintptr_t)L.dA & 15u) == 0 &&
-                     (L.lddc * (int64_t)sizeof(T)) % 16 == 0 &&
-                     (L.ldda * (int64_t)sizeof(T)) % 16 == 0;
+    // 16-byte runs of the 16-bit planes (T's runs need no alignment)
+    const bool pv = AF < 0 || (((uintptr_t)L.A & 15u) == 0 && L.lda % 8 == 0);
+    // non-temporal stores of dA where each fills whole lines (as rowtile)
+    const bool nts = ((uintptr_t)L.dA & 15u) == 0 && (L.ldda * (int64_t)sizeof(T)) % 16 == 0;
     const uint16_t* alo = ASPLIT ? (const uint16_t*)L.A + L.lda * L.k : nullptr;
     dim3 g((unsigned)bx), b(256);
-    if (vec)
-        TSM_LAUNCH((tsm2l_bwd_kernel<T, NTK, NTN, RG, true, AF, ASPLIT>), g, b, 0, st,
-                           L.m, (int)L.k, (int)L.n, L.A, alo, L.lda, (const T*)L.B, L.ldb,
-                           (const T*)L.dC, L.lddc, (T*)L.dA, L.ldda, L.part);
-    else
-        TSM_LAUNCH((tsm2l_bwd_kernel<T, NTK, NTN, RG, false, AF, ASPLIT>), g, b, 0, st,
-                           L.m, (int)L.k, (int)L.n, L.A, alo, L.lda, (const T*)L.B, L.ldb,
-                           (const T*)L.dC, L.lddc, (T*)L.dA, L.ldda, L.part);
+#define TSM_B(NTS, PV)                                                                            \
+    TSM_LAUNCH((tsm2l_bwd_kernel<T, NTK, NTN, RG, NTS, PV, AF, ASPLIT>), g, b, 0, st, L.m,        \
+               (int)L.k, (int)L.n, L.A, alo, L.lda, (const T*)L.B, L.ldb, (const T*)L.dC, L.lddc, \
+               (T*)L.dA, L.ldda, L.part)
+    if (AF < 0 || pv) {
+        if (nts) TSM_B(true, true); else TSM_B(false, true);
+    } else {
+        TSM_B(false, AF < 0);
+    }
+#undef TSM_B
     if (hipGetLastError() != hipSuccess) return 1;
     return launch_split_reduce(sizeof(T) == 8 ? DT_F64 : DT_F32, 1, (int)bx, 16 * NTN, 16 * NTK,
                                L.k, (int)L.n, L.part, L.dB, L.lddb, 0.0, st);

@@ -52,11 +52,9 @@ struct NNPin {
 };
 
 // Plan of tsm2r for (m, k, n, dtype) on a device with `cus` compute units;
-// `vec`: A is 16-byte aligned with a 16-byte multiple leading dimension;
 // `pin` (may be null) overrides the planner's choices.
 // Returns nonzero if no kernel instance covers the request.
-int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P,
-               const NNPin* pin);
+int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P, const NNPin* pin);
 
 struct LaunchNN {           // tsm2r_nn: C = A*B, column-major A
     const void* fn;
@@ -103,7 +101,8 @@ struct LaunchTN {           // tn: O = X^T*Y, X R x ncols, Y R x n
     const void* yt;         // bf16 planes, n > 16: Y's packed bf16 terms (workspace, or null)
 };
 
-// Low-precision storage forms of A (bf16 / f16, single or split planes).
+// Low-precision storage forms of A (bf16 / f16, single or split planes);
+// `vec`: the planes are 16-byte aligned with a 16-byte multiple leading dimension.
 int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P);
 // L.B: the packed terms of B written by launch_split_b (L.ldb unused)
 int launch_tsm2r_lp(const LaunchNN& L, int dtype, hipStream_t st);

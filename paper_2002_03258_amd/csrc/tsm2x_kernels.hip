@@ -44,7 +44,7 @@ namespace tsm {
 // O[row(rl, q), col0 + 16 t + mrow(kk, r)] in acc[g][q][t][r] with
 // row(rl, q) = row0 + 16*RL*g + RL*rl + q.
 // --------------------------------------------------------------------------
-template <typename T, int KS, int NT16, int RG, bool VEC, bool NTS>
+template <typename T, int KS, int NT16, int RG, bool NTS>
 __global__ __launch_bounds__(256) void rowtile_kernel(
     int64_t m, int kin, int64_t nout, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Y, int64_t ys_in, int64_t ys_out, T* __restrict__ O,
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
             for (int g = 0; g < RG; ++g) {
                 const int64_t r = row0 + 16 * RL * g + RL * rl;
                 if (ji < kin)
-                    load_run<T, RL, VEC>(X + r + ji * ldx, m - r, full, xv[st][g]);
+                    load_run<T, RL>(X + r + ji * ldx, m - r, full, xv[st][g]);
                 else
 #pragma unroll
                     for (int q = 0; q < RL; ++q) xv[st][g][q] = T(0);
@@ -135,11 +135,11 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
                             for (int q = 0; q < RL; ++q) v[q] = acc[g][q][t][rr];
                             if (beta != T(0)) {     // O is read only then
                                 T o[RL];
-                                load_run<T, RL, VEC>(O + r + col * ldo, m - r, full, o);
+                                load_run<T, RL>(O + r + col * ldo, m - r, full, o);
 #pragma unroll
                                 for (int q = 0; q < RL; ++q) v[q] = __builtin_fma(beta, o[q], v[q]);
                             }
-                            store_run<T, RL, VEC, NTS>(O + r + col * ldo, m - r, full, v);
+                            store_run<T, RL, NTS>(O + r + col * ldo, m - r, full, v);
                         }
                     }
             }
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
 // fixed order (workgroup level here, across workgroups by
 // split_reduce_kernel).
 // --------------------------------------------------------------------------
-template <typename T, int NT16, int G, int CT, bool VEC, bool YC>
+template <typename T, int NT16, int G, int CT, bool YC>
 __global__ __launch_bounds__(256) void tn_kernel(
     int64_t R, int64_t ncols, int n, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Y, int64_t ldy, T* __restrict__ O, int64_t ldo,
@@ -206,7 +206,9 @@ __global__ __launch_bounds__(256) void tn_kernel(
 #pragma unroll
         for (int t = 0; t < NT16; ++t) acc[ct][t] = Acc{0, 0, 0, 0};
 
-    // staged column sc: sc < NX -> X column c0 + sc, else Y column sc - NX
+    // staged column sc: sc < NX -> X column c0 + sc (the last column where it
+    // is beyond it: those output rows are not stored), else Y column sc - NX
+    auto xcol = [&](int sc) { return c0 + sc < ncols ? c0 + sc : ncols - 1; };
     auto load = [&](int64_t rb, T (&v)[G][NC / 4][RL]) {
 #pragma unroll
         for (int gs = 0; gs < G; ++gs) {
@@ -217,20 +219,16 @@ __global__ __launch_bounds__(256) void tn_kernel(
             for (int cg = 0; cg < NC / 4; ++cg) {
                 const int sc = 4 * cg + kk;
                 if (cg < NX / 4) {
-                    if (c0 + sc < ncols)
-                        load_run<T, RL, VEC>(X + r + (c0 + sc) * ldx, valid, full, v[gs][cg]);
-                    else
-#pragma unroll
-                        for (int q = 0; q < RL; ++q) v[gs][cg][q] = T(0);
+                    load_run<T, RL>(X + r + xcol(sc) * ldx, valid, full, v[gs][cg]);
                 } else {
                     const T* src = Y + r + (int64_t)(sc - NX) * ldy;
-                    if (YC && VEC && sc - NX < n && full) {
-                        typedef typename VecOf<T, RL>::type V;
+                    if (YC && sc - NX < n && full) {
+                        typedef typename VecOf<T, RL>::mem V;
                         const V y = *reinterpret_cast<const V*>(src);
 #pragma unroll
                         for (int q = 0; q < RL; ++q) v[gs][cg][q] = y[q];
                     } else if (sc - NX < n) {
-                        load_run<T, RL, VEC>(src, valid, full, v[gs][cg]);
+                        load_run<T, RL>(src, valid, full, v[gs][cg]);
                     } else {
 #pragma unroll
                         for (int q = 0; q < RL; ++q) v[gs][cg][q] = T(0);
@@ -280,7 +278,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
     };
     // whole steps: straight-line 16-byte loads (Y through the cache)
     auto load_full = [&](int64_t rb, T (&v)[G][NC / 4][RL]) {
-        typedef typename VecOf<T, RL>::type V;
+        typedef typename VecOf<T, RL>::mem V;
 #pragma unroll
         for (int gs = 0; gs < G; ++gs) {
             const int64_t r = rb + gs * SR + RL * rl;
@@ -288,7 +286,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
             for (int cg = 0; cg < NC / 4; ++cg) {
                 const int sc = 4 * cg + kk;
                 if (cg < NX / 4) {
-                    load_run<T, RL, true>(X + r + (c0 + sc) * ldx, RL, true, v[gs][cg]);
+                    load_run<T, RL>(X + r + xcol(sc) * ldx, RL, true, v[gs][cg]);
                 } else {
                     const int p = sc - NX < n ? sc - NX : n - 1;
                     const V y = *reinterpret_cast<const V*>(Y + r + (int64_t)p * ldy);
@@ -299,12 +297,12 @@ __global__ __launch_bounds__(256) void tn_kernel(
         }
     };
 
-    // pf and every step whole: the next step held in flight across the waits
+    // pf, whole steps: the next step held in flight across the waits
     // for this one (the scheduling barriers keep its loads ahead of them;
     // the bounds branches of the general loop made those waits drain every
     // load).  Not with four stages per step, whose two steps do not fit the
     // registers.
-    if (G <= 2 && pf && VEC && YC && wb1 > wb0 && c0 + NX <= ncols && (wb1 - wb0) % (G * SR) == 0) {
+    if (G <= 2 && pf && YC && wb1 - wb0 >= G * SR) {
         const int64_t nit = (wb1 - wb0) / (G * SR);
         T va[G][NC / 4][RL], vb[G][NC / 4][RL];
         load_full(wb0, va);
@@ -324,6 +322,10 @@ __global__ __launch_bounds__(256) void tn_kernel(
             stage_mul(vb, true);
         } else {
             stage_mul(va, true);
+        }
+        if (wb0 + nit * G * SR < wb1) {
+            load(wb0 + nit * G * SR, va);
+            stage_mul(va, false);
         }
     } else if (wb1 > wb0) {
         const int64_t nit = (wb1 - wb0 + G * SR - 1) / (G * SR);
@@ -392,56 +394,50 @@ static int occupancy(K kernel, int threads) {
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 template <typename T, int KS, int NT16, int RG, bool NTS>
-static int rowtile_launch_st(const LaunchRT& L, bool vec, hipStream_t st) {
+static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
     // persistent grid: as many workgroups as fit at once (queried occupancy),
     // but no more than there are groups of 4 row tiles
-    static const int occ_v = occupancy(rowtile_kernel<T, KS, NT16, RG, true, NTS>, 256);
-    static const int occ_s = occupancy(rowtile_kernel<T, KS, NT16, RG, false, NTS>, 256);
+    static const int occ = occupancy(rowtile_kernel<T, KS, NT16, RG, NTS>, 256);
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
     const int64_t ntiles = (L.m + TR - 1) / TR;
-    int64_t bx = (int64_t)L.cus * (vec ? occ_v : occ_s) / (L.blocks_y > 0 ? L.blocks_y : 1);
+    int64_t bx = (int64_t)L.cus * occ / (L.blocks_y > 0 ? L.blocks_y : 1);
     const int64_t need = (ntiles + 3) / 4;
     if (bx > need) bx = need;
     if (L.blocks_x > 0 && bx > L.blocks_x) bx = L.blocks_x;
     if (bx < 1) bx = 1;
     dim3 grid((unsigned)bx, (unsigned)L.blocks_y), block(256);
-    if (vec)
-        TSM_LAUNCH((rowtile_kernel<T, KS, NT16, RG, true, NTS>), grid, block, 0, st, L.m,
-                   L.kin, L.nout, (const T*)L.X, L.ldx, (const T*)L.Y, L.ys_in, L.ys_out,
-                   (T*)L.O, L.ldo, (int64_t)L.cols_per_block, (T)L.beta);
-    else
-        TSM_LAUNCH((rowtile_kernel<T, KS, NT16, RG, false, NTS>), grid, block, 0, st, L.m,
-                   L.kin, L.nout, (const T*)L.X, L.ldx, (const T*)L.Y, L.ys_in, L.ys_out,
-                   (T*)L.O, L.ldo, (int64_t)L.cols_per_block, (T)L.beta);
+    TSM_LAUNCH((rowtile_kernel<T, KS, NT16, RG, NTS>), grid, block, 0, st, L.m, L.kin, L.nout,
+               (const T*)L.X, L.ldx, (const T*)L.Y, L.ys_in, L.ys_out, (T*)L.O, L.ldo,
+               (int64_t)L.cols_per_block, (T)L.beta);
     return 0;
 }
 
-// The stores of O are non-temporal (they fill whole cache lines: four columns
-// x 256 bytes per wavefront instruction); TSM2X_RT_NTS=0 selects ordinary
-// stores (measurement).  A next-tile register prefetch was measured and
+// The stores of O are non-temporal where they fill whole cache lines (four
+// columns x 256 bytes per wavefront instruction); columns of O that start
+// inside a 16-byte piece leave partial lines at every run's ends, which only
+// ordinary stores merge in the cache.  TSM2X_RT_NTS=0/1 overrides
+// (measurement).  A next-tile register prefetch was measured and
 // dropped: the extra waves it costs hid the latency better.
 template <typename T, int KS, int NT16, int RG>
-static int rowtile_launch(const LaunchRT& L, bool vec, hipStream_t st) {
+static int rowtile_launch(const LaunchRT& L, hipStream_t st) {
     const char* e = std::getenv("TSM2X_RT_NTS");
-    const bool nts = !(e && *e == '0');
-    return nts ? rowtile_launch_st<T, KS, NT16, RG, true>(L, vec, st)
-               : rowtile_launch_st<T, KS, NT16, RG, false>(L, vec, st);
+    const bool whole = aligned16(L.O) && (L.ldo * (int64_t)sizeof(T)) % 16 == 0;
+    const bool nts = e && *e ? *e != '0' : whole;
+    return nts ? rowtile_launch_st<T, KS, NT16, RG, true>(L, st)
+               : rowtile_launch_st<T, KS, NT16, RG, false>(L, st);
 }
 
 template <typename T>
 static int rowtile_dispatch(const LaunchRT& L, hipStream_t st) {
-    const bool vec = aligned16(L.X) && aligned16(L.O) &&
-                     ((L.ldx * (int64_t)sizeof(T)) % 16 == 0) &&
-                     ((L.ldo * (int64_t)sizeof(T)) % 16 == 0);
     const bool wide = L.nout > 16;   // two 16-column tiles per pass
     switch (L.kp) {
-        case 8: return wide ? rowtile_launch<T, 2, 2, 2>(L, vec, st) : rowtile_launch<T, 2, 1, 2>(L, vec, st);
+        case 8: return wide ? rowtile_launch<T, 2, 2, 2>(L, st) : rowtile_launch<T, 2, 1, 2>(L, st);
         // k = 16 and 32 with n <= 16: one row group per lane (more waves per
         // SIMD) measured up to 16 % faster for float (k = 16) and 2.7 % on
         // average at k = 32, double the same or faster; for k = 8 and for the
         // wide instances with two groups it was slower
-        case 16: return wide ? rowtile_launch<T, 4, 2, 2>(L, vec, st) : rowtile_launch<T, 4, 1, 1>(L, vec, st);
-        case 32: return wide ? rowtile_launch<T, 8, 2, 1>(L, vec, st) : rowtile_launch<T, 8, 1, 1>(L, vec, st);
+        case 16: return wide ? rowtile_launch<T, 4, 2, 2>(L, st) : rowtile_launch<T, 4, 1, 1>(L, st);
+        case 32: return wide ? rowtile_launch<T, 8, 2, 1>(L, st) : rowtile_launch<T, 8, 1, 1>(L, st);
     }
     return 1;
 }
@@ -453,22 +449,18 @@ int launch_rowtile(const LaunchRT& L, int dtype, hipStream_t st) {
 }
 
 template <typename T, int NT16, int G, int CT>
-static int tn_launch(const LaunchTN& L, bool vec, hipStream_t st) {
+static int tn_launch(const LaunchTN& L, hipStream_t st) {
     // L.groups 16-column tiles, a multiple of CT: CT of them per workgroup.
     // Y is read by every column group: cached loads when there are several
     // (YC), non-temporal ones when it is streamed once.
     const int64_t gx = L.groups / CT;
     dim3 grid((unsigned)gx, (unsigned)L.S), block(256);
-    if (vec && gx > 1)
-        TSM_LAUNCH((tn_kernel<T, NT16, G, CT, true, true>), grid, block, 0, st, L.R,
-                           L.ncols, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O,
-                           L.ldo, L.rslice, L.part, L.beta, L.pf);
-    else if (vec)
-        TSM_LAUNCH((tn_kernel<T, NT16, G, CT, true, false>), grid, block, 0, st, L.R,
+    if (gx > 1)
+        TSM_LAUNCH((tn_kernel<T, NT16, G, CT, true>), grid, block, 0, st, L.R,
                            L.ncols, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O,
                            L.ldo, L.rslice, L.part, L.beta, L.pf);
     else
-        TSM_LAUNCH((tn_kernel<T, NT16, G, CT, false, false>), grid, block, 0, st, L.R,
+        TSM_LAUNCH((tn_kernel<T, NT16, G, CT, false>), grid, block, 0, st, L.R,
                            L.ncols, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O,
                            L.ldo, L.rslice, L.part, L.beta, L.pf);
     return 0;
@@ -476,22 +468,19 @@ static int tn_launch(const LaunchTN& L, bool vec, hipStream_t st) {
 
 template <typename T>
 static int tn_dispatch(const LaunchTN& L, hipStream_t st) {
-    const bool vec = aligned16(L.X) && aligned16(L.Y) &&
-                     ((L.ldx * (int64_t)sizeof(T)) % 16 == 0) &&
-                     ((L.ldy * (int64_t)sizeof(T)) % 16 == 0);
     // G stages of 16*RL rows per loop iteration (loads for the next iteration
     // are in flight while the current one is staged and multiplied); CT
     // 16-column output tiles per wavefront share each staged Y tile
     int rc = 1;
     const bool wide = L.n > 16;
     if (L.ct == 2) {
-        rc = wide ? tn_launch<T, 2, 1, 2>(L, vec, st) : tn_launch<T, 1, 1, 2>(L, vec, st);
+        rc = wide ? tn_launch<T, 2, 1, 2>(L, st) : tn_launch<T, 1, 1, 2>(L, st);
     } else if (L.rg == 4) {
-        rc = wide ? tn_launch<T, 2, 4, 1>(L, vec, st) : tn_launch<T, 1, 4, 1>(L, vec, st);
+        rc = wide ? tn_launch<T, 2, 4, 1>(L, st) : tn_launch<T, 1, 4, 1>(L, st);
     } else if (L.rg == 2) {
-        rc = wide ? tn_launch<T, 2, 2, 1>(L, vec, st) : tn_launch<T, 1, 2, 1>(L, vec, st);
+        rc = wide ? tn_launch<T, 2, 2, 1>(L, st) : tn_launch<T, 1, 2, 1>(L, st);
     } else {
-        rc = wide ? tn_launch<T, 2, 1, 1>(L, vec, st) : tn_launch<T, 1, 1, 1>(L, vec, st);
+        rc = wide ? tn_launch<T, 2, 1, 1>(L, st) : tn_launch<T, 1, 1, 1>(L, st);
     }
     if (rc || L.S <= 1) return rc;
     return launch_split_reduce(sizeof(T) == 8 ? DT_F64 : DT_F32, L.groups, L.S,

@@ -118,7 +118,7 @@ __device__ __forceinline__ void scatter_step(T (&v)[2 * H], int (&c)[2 * H], T (
     }
 }
 
-template <typename T, int KS, int NT16, int RG, bool VEC, bool RES, bool ROWX>
+template <typename T, int KS, int NT16, int RG, bool RES, bool ROWX>
 __global__ __launch_bounds__(256) void kmeans_assign_kernel(
     int64_t m, int k, int n, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Mu,
     int64_t ldm, const T* __restrict__ mu2, int32_t* __restrict__ labels,
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                 for (int g = 0; g < RG; ++g) {
                     const int64_t r = row0 + 16 * RL * g + RL * rl;
                     if (j < k)
-                        load_run<T, RL, VEC>(X + r + (int64_t)j * ldx, m - r, full,
+                        load_run<T, RL>(X + r + (int64_t)j * ldx, m - r, full,
                                              raw[st * RG + g]);
                     else
 #pragma unroll
@@ -192,8 +192,8 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                 const int p = pc / PPP, f0 = kc + (pc % PPP) * RL;
                 const int64_t pt = row0 + p;
                 const T* src = X + pt * ldx + f0;
-                if (VEC && pt < m && f0 + RL <= k) {
-                    typedef typename VecOf<T, RL>::type V;
+                if (pt < m && f0 + RL <= k) {
+                    typedef typename VecOf<T, RL>::mem V;
                     const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(src));
 #pragma unroll
                     for (int e = 0; e < RL; ++e) raw[i][e] = v[e];
@@ -306,8 +306,8 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
             const T v = x22[i] + v2[i];
             d[i] = none ? T(__builtin_nan("")) : (v < T(0) ? T(0) : v);
         }
-        store_run<int32_t, NQ, VEC, false>(labels + r, m - r, full, lab);
-        if (dist) store_run<T, NQ, VEC, false>(dist + r, m - r, full, d);
+        store_run<int32_t, NQ, false>(labels + r, m - r, full, lab);
+        if (dist) store_run<T, NQ, false>(dist + r, m - r, full, d);
     };
     auto init = [&](T (&bv)[R], int (&bc)[R], T (&x2)[R]) {
 #pragma unroll
@@ -397,7 +397,7 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
     // that each of the four lanes of a row keeps at least one row
     constexpr int RG = sizeof(T) == 4 ? 1 : 2;
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
-    static const int occ = km_occupancy(kmeans_assign_kernel<T, KS, NT16, RG, true, RES, ROWX>);
+    static const int occ = km_occupancy(kmeans_assign_kernel<T, KS, NT16, RG, RES, ROWX>);
     const int64_t ntiles = (L.m + TR - 1) / TR;
     int64_t bx = (int64_t)L.cus * occ;
     const int64_t need = (ntiles + 3) / 4;
@@ -407,20 +407,10 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
     TSM_LAUNCH(kmeans_norms_kernel<T>, dim3(nb), dim3(256), 0, st, (int)L.k, (int)L.n,
                        (const T*)L.Mu, L.ldm, (T*)L.mu2);
     if (hipGetLastError() != hipSuccess) return 1;
-    // 16-byte runs of X (row-major: the last piece of a point whose k values
-    // end inside it is read element-wise) and of the outputs
-    const int es = (int)sizeof(T);
-    const bool vec = ((uintptr_t)L.X & 15u) == 0 && (L.ldx * es) % 16 == 0 &&
-                     ((uintptr_t)L.labels & 15u) == 0 && ((uintptr_t)L.dist & 15u) == 0;
     dim3 g((unsigned)bx), b(256);
-    if (vec)
-        TSM_LAUNCH((kmeans_assign_kernel<T, KS, NT16, RG, true, RES, ROWX>), g, b, 0, st, L.m,
-                           (int)L.k, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Mu, L.ldm,
-                           (const T*)L.mu2, L.labels, (T*)L.dist);
-    else
-        TSM_LAUNCH((kmeans_assign_kernel<T, KS, NT16, RG, false, RES, ROWX>), g, b, 0, st, L.m,
-                           (int)L.k, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Mu, L.ldm,
-                           (const T*)L.mu2, L.labels, (T*)L.dist);
+    TSM_LAUNCH((kmeans_assign_kernel<T, KS, NT16, RG, RES, ROWX>), g, b, 0, st, L.m, (int)L.k,
+               (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Mu, L.ldm, (const T*)L.mu2, L.labels,
+               (T*)L.dist);
     return hipGetLastError() != hipSuccess;
 }
 

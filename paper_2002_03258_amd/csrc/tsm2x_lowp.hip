@@ -44,6 +44,7 @@
 
 namespace tsm {
 
+typedef VecOf<float, 4>::mem f32x4m;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -98,8 +99,8 @@ __global__ __launch_bounds__(256) void split_kernel(int64_t m, int64_t k,
         const int64_t valid = m - i0;
         float a[8];
         if (VEC && valid >= 8) {
-            const f32x4 v0 = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src));
-            const f32x4 v1 = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src) + 1);
+            const f32x4m v0 = __builtin_nontemporal_load(reinterpret_cast<const f32x4m*>(src));
+            const f32x4m v1 = __builtin_nontemporal_load(reinterpret_cast<const f32x4m*>(src) + 1);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 a[q] = v0[q];
@@ -334,17 +335,9 @@ __global__ __launch_bounds__(WAVE * WK) void tsm2r_lp_kernel(
     // 16384^2.  Without the scheduling barriers the compiler sank the next
     // chunk's loads below the waits and it gained nothing.
     if (wk1 > wk0 && row0 < m) {
-        const int ng = (int)((wk1 - wk0 + 31) / 32);
-        if (!PF || !(VEC && full && (wk1 - wk0) % (32 * U) == 0)) {
-            for (int g = 0; g < ng; ++g) {
-                uint32_t raw[NPL][8][4];
-                u32x4 bt[NT16][NBT];
-                loadA(wk0 + 32 * g, raw);
-                loadBt(wk0 + 32 * g, bt);
-                chunk(raw, bt);
-            }
-        } else {
-            // every chunk whole: the next step in flight while this one is
+        int64_t j1 = wk0;        // columns from here on one chunk at a time
+        if (PF && VEC && full && wk1 - wk0 >= 32 * U) {
+            // whole steps: the next step in flight while this one is
             // multiplied, in straight-line code (no bounds branches, so the
             // waits for this step's operands leave the next step's loads
             // outstanding); its B terms are loaded before its A for the same
@@ -383,12 +376,20 @@ __global__ __launch_bounds__(WAVE * WK) void tsm2r_lp_kernel(
             } else {
                 mul_step(ra, ba);
             }
+            j1 = wk0 + (int64_t)32 * U * ns;
+        }
+        for (; j1 < wk1; j1 += 32) {
+            uint32_t raw[NPL][8][4];
+            u32x4 bt[NT16][NBT];
+            loadA(j1, raw);
+            loadBt(j1, bt);
+            chunk(raw, bt);
         }
     }
 
     // lane holds C[r + q, 16 t + 4 kk + rr] in acc[q][t][rr]
     nn_finish<float, NP, WK, TRW, PG, RS ? 1 : WK>(
-        m, n, C, ldc, beta, tile, s, nsl, part, reinterpret_cast<double*>(smem),
+        m, n, C, ldc, beta, tile, tile * TRW, s, nsl, part, reinterpret_cast<double*>(smem),
         [&](int pg, double* red) {
             const int t = pg / 16;
 #pragma unroll
@@ -511,8 +512,8 @@ __attribute__((amdgpu_waves_per_eu(lp_l_waves<KS, NT16>(), 8))) void tsm2l_lp_ke
                     float* c = C + r + (int64_t)col * ldc;
                     if (beta != 0.f) {
                         float o0[4], o1[4];
-                        load_run<float, 4, VEC>(c, m - r, full, o0);
-                        load_run<float, 4, VEC>(c + 4, m - r - 4, full, o1);
+                        load_run<float, 4>(c, m - r, full, o0);
+                        load_run<float, 4>(c + 4, m - r - 4, full, o1);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             v0[q] = __builtin_fmaf(beta, o0[q], v0[q]);
@@ -520,8 +521,8 @@ __attribute__((amdgpu_waves_per_eu(lp_l_waves<KS, NT16>(), 8))) void tsm2l_lp_ke
                         }
                     }
                     // the two stores fill alternate 16-byte halves of the lines
-                    store_run<float, 4, VEC, false>(c, m - r, full, v0);
-                    store_run<float, 4, VEC, false>(c + 4, m - r - 4, full, v1);
+                    store_run<float, 4, false>(c, m - r, full, v0);
+                    store_run<float, 4, false>(c + 4, m - r - 4, full, v1);
                 }
             }
         if (more) {
@@ -560,8 +561,9 @@ __attribute__((amdgpu_waves_per_eu(lp_l_waves<KS, NT16>(), 8))) void tsm2l_lp_ke
 // three (five) matrix-core instructions where the float path takes eight,
 // and no widening.  Products of 16-bit values are exact in float, so the
 // error against the stored values is that of float accumulation, as on the
-// float path.  Whole wavefronts load straight-line; ragged ones (rows, X
-// columns, unaligned Y) take the same step with bounds-checked loads.
+// float path.  Whole steps load straight-line (X columns beyond ncols read
+// the last one; their output rows are not stored); a last partial step and
+// unaligned planes take the same step with bounds-checked loads.
 // Y columns beyond n read column n - 1; their output columns are never
 // stored.  With four output tiles per workgroup the split form's 16-bit
 // tiles take 136 KB of LDS: one workgroup per CU.  For n > 16 (YT) Y's
@@ -629,18 +631,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
             const int p = YD ? 16 * (yi % NT16) + rl : 4 * (yi % YG) + kk;
             const int64_t valid = wb1 - r;
             const bool full = valid >= 4;
-            if (YC && VEC && p < n && full) {
+            if (YC && p < n && full) {
                 // Y re-read by every column group: through the cache
-                const f32x4 y = *reinterpret_cast<const f32x4*>(Y + r + (int64_t)p * ldy);
+                const f32x4m y = *reinterpret_cast<const f32x4m*>(Y + r + (int64_t)p * ldy);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) yv[yi][q] = y[q];
             } else if (p < n)
-                load_run<float, 4, VEC>(Y + r + (int64_t)p * ldy, valid, full, yv[yi]);
+                load_run<float, 4>(Y + r + (int64_t)p * ldy, valid, full, yv[yi]);
             else
 #pragma unroll
                 for (int q = 0; q < 4; ++q) yv[yi][q] = 0.f;
         }
     };
+    // X column c0 + sc, the last one where it is beyond it: those output rows
+    // are not stored
+    auto xcol = [&](int sc) { return c0 + sc < ncols ? c0 + sc : ncols - 1; };
     // X (and staged Y) of a step are loaded one step ahead; direct Y is loaded
     // at the start of its own step (its registers would cost a wavefront)
     auto loadX = [&](int64_t rb, uint32_t (&xv)[XG][NPL][4]) {
@@ -650,16 +655,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
             const bool full = valid >= 8;
 #pragma unroll
             for (int cg = 0; cg < XG; ++cg) {
-                const int64_t c = c0 + 4 * cg + kk;
+                const int64_t c = xcol(4 * cg + kk);
 #pragma unroll
-                for (int pl = 0; pl < NPL; ++pl) {
-                    const uint16_t* P = pl == 0 ? Xh : Xl;
-                    if (c < ncols)
-                        load8h<VEC>(P + r + c * ldx, valid, full, xv[cg][pl]);
-                    else
-#pragma unroll
-                        for (int d = 0; d < 4; ++d) xv[cg][pl][d] = 0u;
-                }
+                for (int pl = 0; pl < NPL; ++pl)
+                    load8h<VEC>((pl == 0 ? Xh : Xl) + r + c * ldx, valid, full, xv[cg][pl]);
             }
         }
     };
@@ -716,24 +715,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
         }
     };
 
-    // pf and every step whole (rows and columns in range, 16-byte loads, Y
-    // direct): straight-line loads, the next step's X kept in flight across
+    // pf, whole steps (16-byte loads, Y direct): straight-line loads, the next step's X kept in flight across
     // the waits for this step's operands (the scheduling barriers stop the
     // compiler from sinking those loads below the waits).
-    const bool whole = !MX && pf && VEC && YC && YD && c0 + NX <= ncols && (wb1 - wb0) % SR == 0;
-    // MX: the same whole-wavefront test without pf (pf only picks one or two
-    // steps in flight, with the same arithmetic); ragged wavefronts take the
+    const bool whole = !MX && pf && VEC && YC && YD && wb1 - wb0 >= SR;
+    // MX: the same without pf (pf only picks one or two steps in flight, with
+    // the same arithmetic); a last partial step and unaligned planes take the
     // MX step too, with bounds-checked loads
-    const bool mx_whole = MX && VEC && YC && c0 + NX <= ncols && (wb1 - wb0) % SR == 0;
+    const bool mx_whole = MX && VEC && YC && wb1 - wb0 >= SR;
     // two steps in flight need two X steps in registers: not with four split tiles
     constexpr bool MX_TWO = MX && !(SPLIT && CT >= 4);
     auto loadX_full = [&](int64_t rb, uint32_t (&xv)[XG][NPL][4]) {
 #pragma unroll
         for (int pl = 0; pl < NPL; ++pl) {
-            const uint16_t* P = (pl == 0 ? Xh : Xl) + rb + 8 * rl + (c0 + kk) * ldx;
+            const uint16_t* P = (pl == 0 ? Xh : Xl) + rb + 8 * rl;
 #pragma unroll
             for (int cg = 0; cg < XG; ++cg) {
-                const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(P + 4 * cg * ldx));
+                const u32x4 v = __builtin_nontemporal_load(
+                    reinterpret_cast<const u32x4*>(P + xcol(4 * cg + kk) * ldx));
 #pragma unroll
                 for (int d = 0; d < 4; ++d) xv[cg][pl][d] = v[d];
             }
@@ -745,8 +744,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
         for (int yi = 0; yi < YW; ++yi) {
             const int p = 16 * (yi % NT16) + rl;
             const int pc = p < n ? p : n - 1;
-            const f32x4 y = *reinterpret_cast<const f32x4*>(Y + rb + 16 * (yi / NT16) + 4 * kk +
-                                                            (int64_t)pc * ldy);
+            const f32x4m y = *reinterpret_cast<const f32x4m*>(Y + rb + 16 * (yi / NT16) + 4 * kk +
+                                                              (int64_t)pc * ldy);
 #pragma unroll
             for (int q = 0; q < 4; ++q) yv[yi][q] = y[q];
         }
@@ -774,15 +773,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
                 for (int t = 0; t < NT16; ++t) {
                     const int p = 16 * t + rl;
                     const int pc = p < n ? p : n - 1;
-                    const f32x4* src = reinterpret_cast<const f32x4*>(Y + rb + 32 * blk + 8 * kk +
-                                                                      (int64_t)pc * ldy);
+                    const f32x4m* src = reinterpret_cast<const f32x4m*>(Y + rb + 32 * blk + 8 * kk +
+                                                                        (int64_t)pc * ldy);
                     ym[blk][t][0] = src[0];
                     ym[blk][t][1] = src[1];
                 }
         }
     };
     // the same rows with bounds: rows at or beyond wb1 and columns beyond n
-    // are zero (ragged wavefronts, unaligned Y)
+    // are zero (partial steps, unaligned planes)
     auto loadY_mx_gen = [&](int64_t rb, YBuf& ym) {
         if constexpr (YT) {
             // X rows at or beyond wb1 are zero; blocks beyond R are not read
@@ -806,8 +805,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
                     const int64_t valid = wb1 - r;
                     float v0[4], v1[4];
                     if (p < n) {
-                        load_run<float, 4, VEC>(Y + r + (int64_t)p * ldy, valid, valid >= 4, v0);
-                        load_run<float, 4, VEC>(Y + r + 4 + (int64_t)p * ldy, valid - 4, valid >= 8,
+                        load_run<float, 4>(Y + r + (int64_t)p * ldy, valid, valid >= 4, v0);
+                        load_run<float, 4>(Y + r + 4 + (int64_t)p * ldy, valid - 4, valid >= 8,
                                                 v1);
                     } else {
 #pragma unroll
@@ -906,8 +905,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
                 step_mx(xa, ym);
             }
         }
+        if (wb0 + nit * SR < wb1) {
+            loadX(wb0 + nit * SR, xa);
+            loadY_mx_gen(wb0 + nit * SR, ym);
+            step_mx(xa, ym);
+        }
     } else if (MX && wb1 > wb0) {
-        // ragged or unaligned: one step at a time, loads bounds-checked
+        // unaligned planes, or less than a step: loads bounds-checked
         const int64_t nit = (wb1 - wb0 + SR - 1) / SR;
         for (int64_t it = 0; it < nit; ++it) {
             uint32_t xv[XG][NPL][4];
@@ -942,6 +946,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
             loadY_full(wb0 + (it + 1) * SR, yv);
             step(xb, yv);
         } else {
+            step(xa, yv);
+        }
+        if (wb0 + nit * SR < wb1) {
+            loadX(wb0 + nit * SR, xa);
+            loadY(wb0 + nit * SR, yv);
             step(xa, yv);
         }
     } else if (!MX && wb1 > wb0) {
@@ -1169,8 +1178,7 @@ int launch_tsm2l_lp(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
                     int cus, hipStream_t st) {
     const int fmt = (dtype == DT_BF16 || dtype == DT_BF16_SPLIT) ? FMT_BF16 : FMT_F16;
     const bool split = dtype == DT_BF16_SPLIT || dtype == DT_F16_SPLIT;
-    const bool vec = ((uintptr_t)A & 15u) == 0 && (lda % 8) == 0 && ((uintptr_t)C & 15u) == 0 &&
-                     (ldc % 4) == 0;
+    const bool vec = ((uintptr_t)A & 15u) == 0 && (lda % 8) == 0;
     const uint16_t* ah = (const uint16_t*)A;
     const uint16_t* al = split ? ah + lda * k : nullptr;
     const int ki = (int)k, ni = (int)n;
@@ -1191,8 +1199,7 @@ int launch_tsm2l_lp(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
 static int launch_tn_lp_main(const LaunchTN& L, int dtype, hipStream_t st) {
     const int fmt = (dtype == DT_BF16 || dtype == DT_BF16_SPLIT) ? FMT_BF16 : FMT_F16;
     const bool split = dtype == DT_BF16_SPLIT || dtype == DT_F16_SPLIT;
-    const bool vec = ((uintptr_t)L.X & 15u) == 0 && (L.ldx % 8) == 0 &&
-                     ((uintptr_t)L.Y & 15u) == 0 && (L.ldy % 4) == 0;
+    const bool vec = ((uintptr_t)L.X & 15u) == 0 && (L.ldx % 8) == 0;
     const uint16_t* xh = (const uint16_t*)L.X;
     const uint16_t* xl = split ? xh + L.ldx * L.ncols : nullptr;
     // L.groups 16-column tiles, a multiple of L.ct: L.ct of them per workgroup
@@ -1269,8 +1276,9 @@ int launch_tn_lp(const LaunchTN& L, int dtype, hipStream_t st) {
 
 int launch_split(int64_t m, int64_t k, const float* A, int64_t lda, void* hi, void* lo,
                  int64_t ldh, int fmt, hipStream_t st) {
-    const bool vec = ((uintptr_t)A & 15u) == 0 && (lda % 4) == 0 && ((uintptr_t)hi & 15u) == 0 &&
-                     (!lo || ((uintptr_t)lo & 15u) == 0) && (ldh % 8) == 0;
+    // 16-byte stores of the planes (A's 16-byte loads need no alignment)
+    const bool vec = ((uintptr_t)hi & 15u) == 0 && (!lo || ((uintptr_t)lo & 15u) == 0) &&
+                     (ldh % 8) == 0;
     const int64_t total = cdiv_lp(m, 8) * k;
     int64_t blocks = cdiv_lp(total, 256);
     if (blocks > 8192) blocks = 8192;

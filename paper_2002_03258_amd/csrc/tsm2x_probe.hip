@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void probe_stream_kernel(const u32x4p* __restr
 // 4 ((4 t + rr) % KS) + kk of the same rows (of X, or of X + Y with TWO): a
 // fixed column mapping, so that every store depends on a load; only the
 // bytes moved matter.
-template <typename T, int KS, int NT16, int RG, bool VEC, bool TWO>
+template <typename T, int KS, int NT16, int RG, bool TWO>
 __global__ __launch_bounds__(256) void probe_tiles_kernel(int64_t m, int kin, int nout,
                                                           const T* __restrict__ X, int64_t ldx,
                                                           const T* __restrict__ Y, int64_t ldy,
@@ -95,8 +95,8 @@ __global__ __launch_bounds__(256) void probe_tiles_kernel(int64_t m, int kin, in
             for (int g = 0; g < RG; ++g) {
                 const int64_t r = row0 + 16 * RL * g + RL * rl;
                 if (ji < kin) {
-                    load_run<T, RL, VEC>(X + r + ji * ldx, m - r, full, xv[st][g]);
-                    if (TWO) load_run<T, RL, VEC>(Y + r + ji * ldy, m - r, full, yv[TWO ? st : 0][g]);
+                    load_run<T, RL>(X + r + ji * ldx, m - r, full, xv[st][g]);
+                    if (TWO) load_run<T, RL>(Y + r + ji * ldy, m - r, full, yv[TWO ? st : 0][g]);
                 } else {
 #pragma unroll
                     for (int q = 0; q < RL; ++q) xv[st][g][q] = yv[TWO ? st : 0][g][q] = T(0);
@@ -119,8 +119,8 @@ __global__ __launch_bounds__(256) void probe_tiles_kernel(int64_t m, int kin, in
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr) {
                     const int col = 16 * t + M::mrow(kk, rr);
-                    if (col < nout) store_run<T, RL, VEC>(O + r + col * ldo, m - r, full,
-                                                          xv[(4 * t + rr) % KS][g]);
+                    if (col < nout) store_run<T, RL>(O + r + col * ldo, m - r, full,
+                                                     xv[(4 * t + rr) % KS][g]);
                 }
         }
     }
@@ -138,22 +138,15 @@ template <typename T, int KS, int NT16, int RG, bool TWO>
 static void probe_tiles_go(int64_t m, int kin, int nout, const void* X, int64_t ldx,
                            const void* Y, int64_t ldy, void* O, int64_t ldo, int64_t blocks,
                            int cus, hipStream_t st) {
-    const bool vec = ((uintptr_t)X & 15u) == 0 && ((uintptr_t)O & 15u) == 0 &&
-                     (ldx * (int64_t)sizeof(T)) % 16 == 0 && (ldo * (int64_t)sizeof(T)) % 16 == 0 &&
-                     (!TWO || (((uintptr_t)Y & 15u) == 0 && (ldy * (int64_t)sizeof(T)) % 16 == 0));
-    static const int occ = probe_occupancy(probe_tiles_kernel<T, KS, NT16, RG, true, TWO>);
+    static const int occ = probe_occupancy(probe_tiles_kernel<T, KS, NT16, RG, TWO>);
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
     const int64_t need = ((m + TR - 1) / TR + 3) / 4;
     int64_t bx = blocks > 0 ? blocks : (int64_t)cus * occ;
     if (bx > need) bx = need;
     if (bx > 0x7fffffff) bx = 0x7fffffff;
     if (bx < 1) bx = 1;
-    if (vec)
-        TSM_LAUNCH((probe_tiles_kernel<T, KS, NT16, RG, true, TWO>), dim3((unsigned)bx), dim3(256), 0,
-                   st, m, kin, nout, (const T*)X, ldx, (const T*)Y, ldy, (T*)O, ldo);
-    else
-        TSM_LAUNCH((probe_tiles_kernel<T, KS, NT16, RG, false, TWO>), dim3((unsigned)bx), dim3(256),
-                   0, st, m, kin, nout, (const T*)X, ldx, (const T*)Y, ldy, (T*)O, ldo);
+    TSM_LAUNCH((probe_tiles_kernel<T, KS, NT16, RG, TWO>), dim3((unsigned)bx), dim3(256), 0, st, m,
+               kin, nout, (const T*)X, ldx, (const T*)Y, ldy, (T*)O, ldo);
 }
 
 // the row groups per lane of the rowtile instance for (kin, nout); with two

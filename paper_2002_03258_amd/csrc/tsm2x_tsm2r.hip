@@ -25,6 +25,11 @@ namespace tsm {
 // loads outstanding across the waits for the current chunk.  Lane l ends up with
 // C[row0 + 16*RL*g + RL*rl + q, 16t + mrow(kk, r)] in acc[g][q][t][r].
 //
+// A's columns may start at any element: the 16-byte loads need no alignment
+// (element-wise loads there ran at half the rate: FP32 10007 x 9973, n = 5,
+// 136 us, now 74), and a last tile or chunk that would leave the matrix is
+// moved up, or clamped and zeroed, instead of loaded element by element.
+//
 // The k range is split across the WK wavefronts of a workgroup and across
 // workgroups; the partial sums are added in double precision in a fixed
 // order (in LDS within the workgroup, then by split_reduce_kernel).
@@ -38,12 +43,12 @@ namespace tsm {
 template <typename T, int NT16>
 constexpr int nn_waves() { return NT16 == 1 ? 3 : 2; }
 
-template <typename T, int NT16, int RG, int ST, int WK, bool VEC, bool PF = TSM2X_NN_PREFETCH>
+template <typename T, int NT16, int RG, int ST, int WK, bool PF = TSM2X_NN_PREFETCH>
 __global__ __launch_bounds__(WAVE * WK)
 __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kernel(
     int64_t m, int64_t k, int n, const T* __restrict__ A, int64_t lda,
     const T* __restrict__ B, int64_t ldb, T* __restrict__ C, int64_t ldc,
-    int64_t kslice, double* __restrict__ part, int bvec, int pf, double beta) {
+    int64_t kslice, double* __restrict__ part, int pf, double beta, int swz) {
     typedef Mfma<T> M;
     typedef typename M::acc Acc;
     constexpr int RL = 16 / (int)sizeof(T);
@@ -59,9 +64,21 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
     const int lane = threadIdx.x & (WAVE - 1);
     const int rl = lane & 15, kk = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);   // wavefront-uniform
-    const int64_t tile = blockIdx.x;
-    const int s = blockIdx.y, nsl = gridDim.y;
-    const int64_t row0 = tile * TR;
+    const int nsl = gridDim.y;
+    int64_t tile = blockIdx.x;
+    int s = blockIdx.y;
+    if (swz) {
+        // workgroup ids go round the 8 XCDs in turn: give each XCD a run of
+        // neighbouring tiles (launch_tsm2r_nn)
+        const unsigned id = blockIdx.x + blockIdx.y * gridDim.x, all = gridDim.x * gridDim.y;
+        const unsigned x = id & 7, q = all >> 3, r = all & 7;
+        const unsigned lin = x * q + (x < r ? x : r) + (id >> 3);
+        s = lin / gridDim.x;
+        tile = lin - s * gridDim.x;
+    }
+    // a last tile that would leave the matrix starts early enough to be whole
+    // (nn_finish writes only its own rows)
+    const int64_t row0 = tile * TR + TR > m && m >= TR ? m - TR : tile * TR;
     const bool full = (row0 + TR <= m);
     const int64_t kb0 = (int64_t)s * kslice;
     const int64_t kb1 = (kb0 + kslice < k) ? kb0 + kslice : k;
@@ -85,7 +102,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
             for (int g = 0; g < RG; ++g) {
                 const int64_t r = row0 + 16 * RL * g + RL * rl;
                 if (j < wk1)
-                    load_run<T, RL, VEC>(A + r + j * lda, m - r, full, av[st][g]);
+                    load_run<T, RL>(A + r + j * lda, m - r, full, av[st][g]);
                 else
 #pragma unroll
                     for (int q = 0; q < RL; ++q) av[st][g][q] = T(0);
@@ -100,8 +117,8 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
             const int p = 16 * t + rl;
             const int64_t jb = j0 + ST * kk;
             const T* __restrict__ src = B + jb + (int64_t)p * ldb;
-            if (p < n && bvec && jb + ST <= wk1) {
-                typedef typename VecOf<T, BW>::type V;
+            if (p < n && jb + ST <= wk1) {
+                typedef typename VecOf<T, BW>::mem V;
 #pragma unroll
                 for (int h = 0; h < ST / BW; ++h) {
                     const V v = *reinterpret_cast<const V*>(src + h * BW);
@@ -135,10 +152,10 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         for (int st = 0; st < ST; ++st)
 #pragma unroll
             for (int g = 0; g < RG; ++g)
-                load_run<T, RL, true>(base + st * lda + 16 * RL * g, RL, true, av[st][g]);
+                load_run<T, RL>(base + st * lda + 16 * RL * g, RL, true, av[st][g]);
     };
     auto loadB_full = [&](int64_t j0, T (&bv)[NT16][ST]) {
-        typedef typename VecOf<T, BW>::type V;
+        typedef typename VecOf<T, BW>::mem V;
 #pragma unroll
         for (int t = 0; t < NT16; ++t) {
             const int p = 16 * t + rl;
@@ -160,13 +177,30 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         mul(av, bz);
     };
 
-    // Every chunk whole: the next chunk held in flight across the waits for
+    // the last columns of a full tile, fewer than a chunk: loads at clamped
+    // columns, zeroed beyond wk1 (A too: 0 * inf would be NaN)
+    auto loadA_tail = [&](int64_t j0, T (&av)[ST][RG][RL]) {
+        const T* base = A + row0 + RL * rl;
+#pragma unroll
+        for (int st = 0; st < ST; ++st) {
+            const int64_t j = j0 + ST * kk + st;
+#pragma unroll
+            for (int g = 0; g < RG; ++g) {
+                load_run<T, RL>(base + (j < wk1 ? j : wk1 - 1) * lda + 16 * RL * g, RL, true,
+                                av[st][g]);
+#pragma unroll
+                for (int q = 0; q < RL; ++q) av[st][g][q] = j < wk1 ? av[st][g][q] : T(0);
+            }
+        }
+    };
+
+    // Whole chunks: the next chunk held in flight across the waits for
     // this one (the scheduling barriers stop the compiler from sinking its
     // loads below them; with the bounds branches of the general loop, the
     // waits after each join counted nothing as in flight and drained every
     // load).  Not for the tall tiles (RG = 4), whose two chunks do not fit
     // the register budget.
-    if (PF && RG <= 2 && VEC && pf && full && bvec && wk1 > wk0 && (wk1 - wk0) % CW == 0) {
+    if (PF && RG <= 2 && pf && full && wk1 - wk0 >= CW) {
         const int ng = (int)((wk1 - wk0) / CW);
         T aa[ST][RG][RL], ab[ST][RG][RL], ba[NT16][ST], bb[NT16][ST];
         loadB_full(wk0, ba);
@@ -190,6 +224,11 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
             mul_live(ab, bb);
         } else {
             mul_live(aa, ba);
+        }
+        if (wk0 + (int64_t)CW * ng < wk1) {
+            loadB(wk0 + (int64_t)CW * ng, ba);
+            loadA_tail(wk0 + (int64_t)CW * ng, aa);
+            mul(aa, ba);
         }
     } else if (wk1 > wk0) {
         const int ng = (int)((wk1 - wk0 + CW - 1) / CW);
@@ -223,7 +262,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         }
     }
 
-    nn_finish<T, NP, WK, TR, PG>(m, n, C, ldc, beta, tile, s, nsl, part,
+    nn_finish<T, NP, WK, TR, PG>(m, n, C, ldc, beta, tile, row0, s, nsl, part,
                                  reinterpret_cast<double*>(smem), [&](int pg, double* red) {
         const int t = pg / 16;
 #pragma unroll
@@ -250,8 +289,6 @@ static int occupancy(K kernel, int threads) {
     return nb;
 }
 
-static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
 struct NNInstance {
     const void* fn;
     int tile_rows;
@@ -260,35 +297,34 @@ struct NNInstance {
     const char* name; // as profilers print the kernel
 };
 
-template <typename T, int NT16, int RG, int ST, bool VEC>
+template <typename T, int NT16, int RG, int ST>
 static NNInstance nn_instance() {
-    static const int occ = occupancy(tsm2r_nn_kernel<T, NT16, RG, ST, 4, VEC>, 256);
+    static const int occ = occupancy(tsm2r_nn_kernel<T, NT16, RG, ST, 4>, 256);
     static char name[80];
     static const bool named =
-        std::snprintf(name, sizeof name, "tsm2r_nn_kernel<%s, %d, %d, %d, 4, %s, %s>",
-                      sizeof(T) == 8 ? "double" : "float", NT16, RG, ST, VEC ? "true" : "false",
+        std::snprintf(name, sizeof name, "tsm2r_nn_kernel<%s, %d, %d, %d, 4, %s>",
+                      sizeof(T) == 8 ? "double" : "float", NT16, RG, ST,
                       TSM2X_NN_PREFETCH ? "true" : "false") > 0;
     (void)named;
-    return NNInstance{(const void*)tsm2r_nn_kernel<T, NT16, RG, ST, 4, VEC>,
+    return NNInstance{(const void*)tsm2r_nn_kernel<T, NT16, RG, ST, 4>,
                       16 * (16 / (int)sizeof(T)) * RG, 4 * ST, occ, name};
 }
 
 // Two tile heights per type: 16*RL*2 rows with 16-column chunks, and twice
 // the rows with 8-column chunks.  Both keep 8 KB of A in flight per wavefront.
-template <bool VEC>
 static bool nn_pick(int dtype, int np, bool tall, NNInstance* out) {
     if (dtype == DT_F64) {
         if (tall)
-            *out = np <= 16 ? nn_instance<double, 1, 4, 2, VEC>() : nn_instance<double, 2, 4, 2, VEC>();
+            *out = np <= 16 ? nn_instance<double, 1, 4, 2>() : nn_instance<double, 2, 4, 2>();
         else
-            *out = np <= 16 ? nn_instance<double, 1, 2, 4, VEC>() : nn_instance<double, 2, 2, 4, VEC>();
+            *out = np <= 16 ? nn_instance<double, 1, 2, 4>() : nn_instance<double, 2, 2, 4>();
         return true;
     }
     if (dtype == DT_F32) {
         if (tall)
-            *out = np <= 16 ? nn_instance<float, 1, 4, 2, VEC>() : nn_instance<float, 2, 4, 2, VEC>();
+            *out = np <= 16 ? nn_instance<float, 1, 4, 2>() : nn_instance<float, 2, 4, 2>();
         else
-            *out = np <= 16 ? nn_instance<float, 1, 2, 4, VEC>() : nn_instance<float, 2, 2, 4, VEC>();
+            *out = np <= 16 ? nn_instance<float, 1, 2, 4>() : nn_instance<float, 2, 2, 4>();
         return true;
     }
     return false;
@@ -319,8 +355,7 @@ static int nn_pf(int64_t n, int dtype, int tall, int64_t W, int cus) {
     return (W <= cus && 8 * W >= 7 * (int64_t)cus) ? 1 : 0;
 }
 
-int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P,
-               const NNPin* pin) {
+int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P, const NNPin* pin) {
     // partial sums are stored at the kernel's padded width (16 or 32 columns)
     const int np = n <= 16 ? 16 : 32;
     const int es = dtype == DT_F64 ? 8 : 4;
@@ -341,8 +376,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NN
     for (int tall = 0; tall < 2; ++tall) {
         if (tall_force >= 0 && tall != (int)tall_force) continue;
         NNInstance I{};
-        if (!(vec ? nn_pick<true>(dtype, np, tall, &I) : nn_pick<false>(dtype, np, tall, &I)))
-            return 1;
+        if (!nn_pick(dtype, np, tall, &I)) return 1;
         const int64_t tiles = cdiv64(m, I.tile_rows);
         const int64_t slots = (int64_t)cus * I.occ;
         const int64_t tgt = target < slots ? target : slots;
@@ -378,11 +412,11 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NN
     }
     if (!found) return 1;
     // one workgroup per CU with the prefetch, unless the caller or an
-    // override fixed the plan (the prefetch needs 16-byte loads of A)
-    const bool free_plan = vec && s_pin <= 0 && tall_force < 0 && !(ft && *ft);
+    // override fixed the plan
+    const bool free_plan = s_pin <= 0 && tall_force < 0 && !(ft && *ft);
     if (free_plan) {
         NNInstance I{};
-        if (nn_pick<true>(dtype, np, false, &I)) {
+        if (nn_pick(dtype, np, false, &I)) {
             const int64_t tiles = cdiv64(m, I.tile_rows);
             int64_t S = cus / tiles;
             const int64_t s_len = k / (WK * 64);
@@ -408,15 +442,12 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NN
             }
         }
     }
-    P->pf = vec ? nn_pf(n, dtype, P->tall, P->tiles * P->S, cus) : 0;
+    P->pf = nn_pf(n, dtype, P->tall, P->tiles * P->S, cus);
     return 0;
 }
 
 int launch_tsm2r_nn(const LaunchNN& L, int dtype, hipStream_t st) {
     int n32 = (int)L.n;
-    // 16-byte loads of B's column runs need an aligned B with ldb*size % 16 == 0
-    const int es = dtype == DT_F64 ? 8 : 4;
-    int bvec = aligned16(L.B) && ((L.ldb * es) % 16 == 0);
     // the next chunk held in flight (see tsm2r_nn_kernel) where it measured
     // faster (the plan's choice, plan_tsm2r): one workgroup per CU; n > 16,
     // where the matrix cores' share of a chunk is largest, +15-25 % (FP32 at
@@ -426,10 +457,19 @@ int launch_tsm2r_nn(const LaunchNN& L, int dtype, hipStream_t st) {
     const char* pfe = std::getenv("TSM2X_NN_PF");
     int pf = (pfe && *pfe) ? (int)std::strtol(pfe, nullptr, 10) : L.pf;
     double beta = L.beta;
+    // Columns that do not start on a 128-byte line: vertically neighbouring
+    // tiles share a line of every column, which both then fetch unless they
+    // run on one XCD (whose L2 serves the second): neighbouring tiles on one
+    // XCD there.  FP32, n = 5: A 10007 x 9973 82 -> 74 us (aligned, 10048 x
+    // 9984: 64), FP32 20011^2 302 -> 286, FP64 7777 x 6001 75 -> 70.  Line-
+    // aligned columns keep the round-robin order: FP32 16384^2 ran 2.5 %
+    // slower with neighbours on one XCD, the others within 1.5 % either way.
+    const int es = dtype == DT_F64 ? 8 : 4;
+    int swz = ((uintptr_t)L.A % 128) != 0 || (L.lda * es) % 128 != 0;
     void* args[] = {(void*)&L.m,   (void*)&L.k,      (void*)&n32,    (void*)&L.A,
                     (void*)&L.lda, (void*)&L.B,      (void*)&L.ldb,  (void*)&L.C,
-                    (void*)&L.ldc, (void*)&L.kslice, (void*)&L.part, (void*)&bvec,
-                    (void*)&pf,    (void*)&beta};
+                    (void*)&L.ldc, (void*)&L.kslice, (void*)&L.part, (void*)&pf,
+                    (void*)&beta,  (void*)&swz};
     hipError_t e;
     {
         LaunchTimer timer(L.fn, st);

@@ -1,0 +1,100 @@
+"""Edges of the tiles and steps: matrices of odd sizes and odd leading
+dimensions, whose columns start at any element, against the FP64 oracle at
+the tolerances of the plain forms."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2002_03258_amd as tsm
+import seeded_inputs as si
+
+from helpers import TOL, dev_matrix, err, host_matrix, to_np
+
+pytestmark = pytest.mark.gpu
+
+DTYPES = [torch.float64, torch.float32]
+
+
+def _odd_ld(x, shift=1):
+    """x as a column-major view with an odd leading dimension, `shift`
+    elements into its storage, NaN around it."""
+    rows, cols = x.shape
+    store = torch.full((cols, (rows + shift) | 1), float("nan"), dtype=x.dtype, device=x.device)
+    v = store[:, shift:shift + rows].t()
+    v.copy_(x)
+    return v
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(127, 2050, 5), (128, 2049, 20), (129, 4099, 4), (511, 8191, 17),
+                                   (3001, 3001, 20), (65, 70, 32)])
+def test_tsm2r_any_alignment(dev, monkeypatch, dtype, m, k, n):
+    """A whole last tile moved up, a clamped last chunk: with the next chunk in
+    flight and without, equal bit for bit; beta != 0 added once per row."""
+    seed = 3000 + m + k + n
+    A = _odd_ld(dev_matrix(seed, si.STREAM_A, m, k, dtype, dev))
+    B = _odd_ld(dev_matrix(seed, si.STREAM_B, k, n, dtype, dev))
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype),
+                        host_matrix(seed, si.STREAM_B, k, n, dtype))
+    got = []
+    for pf in ("0", "1"):
+        monkeypatch.setenv("TSM2X_NN_PF", pf)
+        got.append(tsm.tsm2r(A, B))
+        C = _odd_ld(torch.ones((n, m), dtype=dtype, device=dev).t())
+        tsm.tsm2r(A, B, out=C, beta=2.0)
+        assert err(to_np(C), ref + 2.0) <= TOL[dtype]
+    assert torch.equal(got[0], got[1])
+    assert err(to_np(got[1]), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_tsm2r_infinite_last_column(dev, monkeypatch, dtype):
+    """The clamped loads of the last chunk leave an infinity in A's last column
+    to its own row."""
+    m, k, n = 300, 1037, 6
+    A = dev_matrix(3, si.STREAM_A, m, k, dtype, dev)
+    B = torch.ones((n, k), dtype=dtype, device=dev).t()
+    A[7, k - 1] = float("inf")
+    for pf in ("0", "1"):
+        monkeypatch.setenv("TSM2X_NN_PF", pf)
+        C = tsm.tsm2r(A, B)
+        assert torch.isinf(C[7]).all()
+        assert torch.isfinite(C).sum().item() == (m - 1) * n
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(2049, 33, 20), (4097, 95, 5), (8193, 31, 24), (70, 130, 32)])
+def test_grad_b_any_alignment(dev, monkeypatch, dtype, m, k, n):
+    seed = 3100 + m + k + n
+    A = _odd_ld(dev_matrix(seed, si.STREAM_A, m, k, dtype, dev))
+    dC = _odd_ld(dev_matrix(seed, si.STREAM_DC, m, n, dtype, dev))
+    got = []
+    for pf in ("0", "1"):
+        monkeypatch.setenv("TSM2X_TN_PF", pf)
+        got.append(tsm.grad_b(A, dC))
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype).T,
+                        host_matrix(seed, si.STREAM_DC, m, n, dtype))
+    assert torch.equal(got[0], got[1])
+    assert err(to_np(got[1]), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("lo", [False, True])
+@pytest.mark.parametrize("m,k,n", [(1029, 2079, 9), (517, 4127, 32), (4099, 90, 8), (2051, 130, 24)])
+def test_planes_with_odd_sizes(dev, lo, m, k, n):
+    """The 16-bit forms on odd sizes: forward, dB and the TSM2L forms with
+    float operands at any alignment, against the oracle on the stored values."""
+    seed = 3200 + m + k + n
+    A = _odd_ld(dev_matrix(seed, si.STREAM_A, m, k, torch.float32, dev))
+    B = dev_matrix(seed, si.STREAM_B, k, n, torch.float32, dev)
+    dC = _odd_ld(dev_matrix(seed, si.STREAM_DC, m, n, torch.float32, dev))
+    S = tsm.split(A, "bf16", lo=lo)
+    hi, low = oracle.split(np.asfortranarray(host_matrix(seed, si.STREAM_A, m, k, torch.float32)
+                                             .astype(np.float32)), oracle.BF16)
+    stored = oracle.decode_plane(hi, oracle.BF16)
+    if lo:
+        stored = stored + oracle.decode_plane(low, oracle.BF16)
+    ref = oracle.matmul(stored, host_matrix(seed, si.STREAM_B, k, n, torch.float32))
+    assert err(to_np(tsm.tsm2r(S, B)), ref) <= 3e-6
+    ref = oracle.matmul(stored.T, host_matrix(seed, si.STREAM_DC, m, n, torch.float32))
+    assert err(to_np(tsm.grad_b(S, dC)), ref) <= 3e-6
