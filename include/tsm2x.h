@@ -129,9 +129,10 @@ int tsm2l(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
  *           tsm2x_workspace_size(op, m, k, n, dtype) bytes (op TSM_OP_TSM2R,
  *           TSM_OP_TSM2R_ROWMAJOR for transA = 1, TSM_OP_TSM2L), any
  *           contents; NULL: the library's own (see "Workspace").
- * tsm2r_ex uses the TSM2R kernels (transA = 1: the reduction along the
- * contiguous dimension, the tn kernel), tsm2l_ex the TSM2L kernels where
- * they apply (transA = 0, k <= 32) and the TSM2R ones otherwise.
+ * tsm2r_ex uses the TSM2R kernels (transA = 1, k > 32: the reduction along
+ * the contiguous dimension, the tn kernel), tsm2l_ex the TSM2L kernels where
+ * they apply (transA = 0, k <= 32) and the TSM2R ones otherwise; a transA = 1
+ * product with k <= 32 runs on the TSM2L kernel's row-major form in either.
  * Arguments: 1 transA, 2 transB, 3 m, 4 k, 5 n, 6 A, 7 lda, 8 B, 9 ldb,
  * 10 beta, 11 C, 12 ldc, 13 dtype, 14 ws, 15 ws_bytes, 16 stream.
  * Errors: -i for argument i; TSM_ERR_UNSUPPORTED for transA = 1 with a

@@ -346,8 +346,13 @@ size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool
 }
 
 // C := beta*C + op(A)*op(B) on validated arguments.  `lform` asks for the TSM2L
-// kernels (all of B on chip); they need a column-major A and k <= 32, other
-// shapes run on the TSM2R kernels, which are correct for any k.  n > 32 is
+// kernels (all of B on chip) for a column-major A with k <= 32; other shapes
+// run on the TSM2R kernels, which are correct for any k.  A row-major A with
+// k <= 32 takes the TSM2L kernel either way: the reduction kernel splits the
+// contiguous dimension over its lanes and wavefronts, and one of at most 32
+// elements leaves most of them idle (FP32 4194304 x 16, n = 16: 1499 us
+// there, 105 here; 17 columns, n = 28: 2.1 ms and 158 us; a column-major A
+// takes 103 and 152).  n > 32 is
 // done in panels of 32 columns of B and C, A being read once per panel.
 int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n, const void* A,
             int64_t lda, const void* B, int64_t ldb, double beta, void* C, int64_t ldc,
@@ -372,7 +377,15 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         return TSM_SUCCESS;
     }
     const int cus = cu_count();
-    if (lform && !transA && k <= 32) {
+    const bool rowx = transA && k <= 32;      // plain types only (above)
+    if (rowx && ws) {
+        // nothing is put there, but a workspace that this product's size
+        // query would not have given is refused all the same
+        void* w = nullptr;
+        const int rc = get_ws(tsm2r_ws(transA, m, k, n, dtype, transB, true), ws, ws_bytes, &w);
+        if (rc) return rc;
+    }
+    if ((lform && !transA && k <= 32) || rowx) {
         // B(j, p) at B[j*bsj + p*bsp]: both orders of B are plain strides here
         const int64_t bsj = transB ? ldb : 1, bsp = transB ? 1 : ldb;
         if (!plain_dtype(dtype)) {
@@ -383,6 +396,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         RTPlan P = plan_rowtile(m, k, n, dtype, cus);
         LaunchRT L{};
         L.m = m; L.kin = (int)k; L.nout = n; L.X = A; L.ldx = lda; L.Y = B; L.ys_in = bsj;
+        L.x_rowmajor = rowx;
         L.ys_out = bsp; L.O = C; L.ldo = ldc; L.kp = P.kp; L.cols_per_block = (int)P.cpb;
         L.blocks_x = P.bx; L.blocks_y = P.by; L.cus = cus; L.beta = beta;
         if (launch_rowtile(L, dtype, st)) return TSM_ERR_UNSUPPORTED;

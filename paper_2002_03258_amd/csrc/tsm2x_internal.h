@@ -75,6 +75,7 @@ struct LaunchNN {           // tsm2r_nn: C = A*B, column-major A
 struct LaunchRT {           // rowtile: O = X*Y, X m x kin (kin <= 32)
     int64_t m; int kin; int64_t nout;
     const void* X; int64_t ldx;
+    int x_rowmajor;         // 0: column-major X; 1: row i at X + i*ldx
     const void* Y; int64_t ys_in, ys_out;
     void* O; int64_t ldo;
     int kp;                 // padded kin: 8, 16 or 32

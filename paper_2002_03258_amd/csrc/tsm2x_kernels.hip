@@ -43,12 +43,19 @@ namespace tsm {
 // col0 + 16 t + rl) and T[kk][rl] = X[row(rl, q), 4 st + kk]; lane l holds
 // O[row(rl, q), col0 + 16 t + mrow(kk, r)] in acc[g][q][t][r] with
 // row(rl, q) = row0 + 16*RL*g + RL*rl + q.
+//
+// Row-major X (ROWX: row i at X + i*ldx, its kin values contiguous): the
+// contraction may visit the columns in any order, so step st takes column
+// jcol(st) = 4 W (st / W) + W kk + st % W (W = the values of a 16-byte piece,
+// or KS if fewer) and a lane's W steps are one contiguous load of its row;
+// the four rows q of a lane lie next to each other, so the loads of a tile
+// cover it whole and each line is fetched once.  Nothing goes through LDS.
 // --------------------------------------------------------------------------
-template <typename T, int KS, int NT16, int RG, bool NTS>
+template <typename T, int KS, int NT16, int RG, bool NTS, int ROWX>
 __global__ __launch_bounds__(256) void rowtile_kernel(
     int64_t m, int kin, int64_t nout, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Y, int64_t ys_in, int64_t ys_out, T* __restrict__ O,
-    int64_t ldo, int64_t cols_per_block, T beta) {
+    int64_t ldo, int64_t cols_per_block, double beta) {
     typedef Mfma<T> M;
     typedef typename M::acc Acc;
     constexpr int RL = 16 / (int)sizeof(T);
@@ -62,13 +69,16 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
     const int64_t cb0 = (int64_t)blockIdx.y * cols_per_block;
     const int64_t cb1 = (cb0 + cols_per_block < nout) ? cb0 + cols_per_block : nout;
 
+    constexpr int W = RL < KS ? RL : KS;     // columns of a lane's piece (ROWX)
+    auto jcol = [&](int st) { return ROWX ? 4 * W * (st / W) + W * kk + st % W : 4 * st + kk; };
+
     T yv[KS][NT16];
     auto loadY = [&](int64_t c0) {
 #pragma unroll
         for (int st = 0; st < KS; ++st)
 #pragma unroll
             for (int t = 0; t < NT16; ++t) {
-                const int ji = 4 * st + kk;
+                const int ji = jcol(st);
                 const int64_t jo = c0 + 16 * t + rl;
                 yv[st][t] = (ji < kin && jo < cb1) ? Y[ji * ys_in + jo * ys_out] : T(0);
             }
@@ -76,7 +86,62 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
     const bool one_pass = (cb1 - cb0) <= CW;
     if (one_pass) loadY(cb0);
 
+    // ROWX: a piece that ends beyond kin loads the row's last W values, which
+    // `place` shifts into order when the tile is used (the selects right
+    // behind each load would wait for it); rows beyond m load row m - 1 (they
+    // are not stored).  A row of fewer than W values is read value by value.
+    auto loadX_row = [&](int64_t tile, T (&xv)[KS][RG][RL]) {
+        typedef typename VecOf<T, W>::mem V;
+        auto row = [&](int g, int q) {
+            const int64_t r = tile * TR + 16 * RL * g + RL * rl + q;
+            return X + (r < m ? r : m - 1) * ldx;
+        };
+        if (ROWX == 1 || kin >= W) {
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int q = 0; q < RL; ++q)
+#pragma unroll
+                    for (int h = 0; h < KS / W; ++h) {
+                        const int j0 = 4 * W * h + W * kk;
+                        const int jc = ROWX == 1 || j0 < kin - W ? j0 : kin - W;
+                        const V v = *reinterpret_cast<const V*>(row(g, q) + jc);
+#pragma unroll
+                        for (int e = 0; e < W; ++e) xv[W * h + e][g][q] = v[e];
+                    }
+        } else {
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int q = 0; q < RL; ++q)
+#pragma unroll
+                    for (int st = 0; st < KS; ++st)
+                        xv[st][g][q] = jcol(st) < kin ? row(g, q)[jcol(st)] : T(0);
+        }
+    };
+    auto place = [&](T (&xv)[KS][RG][RL]) {
+#pragma unroll
+        for (int h = 0; h < KS / W; ++h) {
+            const int j0 = 4 * W * h + W * kk;
+            const int sh = j0 < kin - W ? 0 : j0 - (kin - W);
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int q = 0; q < RL; ++q)
+#pragma unroll
+                    for (int e = 0; e < W; ++e) {
+                        T v = T(0);
+#pragma unroll
+                        for (int s = 0; s + e < W; ++s) v = sh == s ? xv[W * h + e + s][g][q] : v;
+                        xv[W * h + e][g][q] = v;
+                    }
+        }
+    };
     auto loadX = [&](int64_t tile, T (&xv)[KS][RG][RL]) {
+        if constexpr (ROWX) {
+            loadX_row(tile, xv);
+            return;
+        }
         const int64_t row0 = tile * TR;
         const bool full = (row0 + TR <= m);
 #pragma unroll
@@ -103,6 +168,7 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
         const int64_t row0 = tile * TR;
         const bool full = (row0 + TR <= m);
         const bool more = tile + tstride < ntiles;
+        if (ROWX == 2 && kin >= W) place(xv);
         for (int64_t c0 = cb0; c0 < cb1; c0 += CW) {
             if (!one_pass) loadY(c0);
             Acc acc[RG][RL][NT16];
@@ -133,11 +199,13 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
                             T v[RL];
 #pragma unroll
                             for (int q = 0; q < RL; ++q) v[q] = acc[g][q][t][rr];
-                            if (beta != T(0)) {     // O is read only then
+                            if (beta != 0.0) {     // O is read only then
                                 T o[RL];
                                 load_run<T, RL>(O + r + col * ldo, m - r, full, o);
 #pragma unroll
-                                for (int q = 0; q < RL; ++q) v[q] = __builtin_fma(beta, o[q], v[q]);
+                                for (int q = 0; q < RL; ++q)
+                                    v[q] = ROWX ? (T)((double)v[q] + beta * (double)o[q])
+                                                : (T)__builtin_fma((T)beta, o[q], v[q]);
                             }
                             store_run<T, RL, NTS>(O + r + col * ldo, m - r, full, v);
                         }
@@ -393,11 +461,11 @@ static int occupancy(K kernel, int threads) {
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <typename T, int KS, int NT16, int RG, bool NTS>
+template <typename T, int KS, int NT16, int RG, bool NTS, int ROWX>
 static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
     // persistent grid: as many workgroups as fit at once (queried occupancy),
     // but no more than there are groups of 4 row tiles
-    static const int occ = occupancy(rowtile_kernel<T, KS, NT16, RG, NTS>, 256);
+    static const int occ = occupancy(rowtile_kernel<T, KS, NT16, RG, NTS, ROWX>, 256);
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
     const int64_t ntiles = (L.m + TR - 1) / TR;
     int64_t bx = (int64_t)L.cus * occ / (L.blocks_y > 0 ? L.blocks_y : 1);
@@ -406,9 +474,9 @@ static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
     if (L.blocks_x > 0 && bx > L.blocks_x) bx = L.blocks_x;
     if (bx < 1) bx = 1;
     dim3 grid((unsigned)bx, (unsigned)L.blocks_y), block(256);
-    TSM_LAUNCH((rowtile_kernel<T, KS, NT16, RG, NTS>), grid, block, 0, st, L.m, L.kin, L.nout,
+    TSM_LAUNCH((rowtile_kernel<T, KS, NT16, RG, NTS, ROWX>), grid, block, 0, st, L.m, L.kin, L.nout,
                (const T*)L.X, L.ldx, (const T*)L.Y, L.ys_in, L.ys_out, (T*)L.O, L.ldo,
-               (int64_t)L.cols_per_block, (T)L.beta);
+               (int64_t)L.cols_per_block, L.beta);
     return 0;
 }
 
@@ -423,8 +491,15 @@ static int rowtile_launch(const LaunchRT& L, hipStream_t st) {
     const char* e = std::getenv("TSM2X_RT_NTS");
     const bool whole = aligned16(L.O) && (L.ldo * (int64_t)sizeof(T)) % 16 == 0;
     const bool nts = e && *e ? *e != '0' : whole;
-    return nts ? rowtile_launch_st<T, KS, NT16, RG, true>(L, st)
-               : rowtile_launch_st<T, KS, NT16, RG, false>(L, st);
+    const int rowx = !L.x_rowmajor ? 0 : L.kin == 4 * KS ? 1 : 2;
+    if (rowx == 2)
+        return nts ? rowtile_launch_st<T, KS, NT16, RG, true, 2>(L, st)
+                   : rowtile_launch_st<T, KS, NT16, RG, false, 2>(L, st);
+    if (rowx == 1)
+        return nts ? rowtile_launch_st<T, KS, NT16, RG, true, 1>(L, st)
+                   : rowtile_launch_st<T, KS, NT16, RG, false, 1>(L, st);
+    return nts ? rowtile_launch_st<T, KS, NT16, RG, true, 0>(L, st)
+               : rowtile_launch_st<T, KS, NT16, RG, false, 0>(L, st);
 }
 
 template <typename T>

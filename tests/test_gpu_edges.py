@@ -98,3 +98,34 @@ def test_planes_with_odd_sizes(dev, lo, m, k, n):
     assert err(to_np(tsm.tsm2r(S, B)), ref) <= 3e-6
     ref = oracle.matmul(stored.T, host_matrix(seed, si.STREAM_DC, m, n, torch.float32))
     assert err(to_np(tsm.grad_b(S, dC)), ref) <= 3e-6
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(1, 1, 1), (63, 2, 3), (64, 3, 16), (65, 4, 17), (129, 5, 32),
+                                   (1000, 7, 8), (4097, 8, 31), (127, 9, 5), (333, 15, 16),
+                                   (128, 16, 33), (4099, 17, 20), (257, 30, 7), (5000, 31, 32),
+                                   (31, 32, 40)])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_rowmajor_tall_product(dev, dtype, m, k, n, pad):
+    """A row-major A with k <= 32 on the TSM2L kernel, rows `pad` elements
+    apart (NaN between them, an infinity in one row), through every entry; a
+    beta is applied once, in double."""
+    seed = 3300 + m + k + n
+    src = dev_matrix(seed, si.STREAM_A, m, k, dtype, dev)
+    store = torch.full((m, k + pad), float("nan"), dtype=dtype, device=dev)
+    A = store[:, pad // 2:pad // 2 + k]
+    A.copy_(src)
+    B = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev)
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype),
+                        host_matrix(seed, si.STREAM_B, k, n, dtype))
+    for fn in (tsm.tsm2l, tsm.tsm2r, tsm.gemm):
+        assert err(to_np(fn(A, B)), ref) <= TOL[dtype]
+        assert err(to_np(fn(A, B.contiguous())), ref) <= TOL[dtype]
+    C = _odd_ld(torch.ones((n, m), dtype=dtype, device=dev).t())
+    tsm.gemm(A, B, out=C, beta=-0.5)
+    assert err(to_np(C), ref - 0.5) <= TOL[dtype]
+    if m > 2:
+        A[m // 2, k - 1] = float("inf")
+        C = tsm.tsm2l(A, torch.ones((n, k), dtype=dtype, device=dev).t())
+        assert torch.isinf(C[m // 2]).all()
+        assert torch.isfinite(C).sum().item() == (m - 1) * n
