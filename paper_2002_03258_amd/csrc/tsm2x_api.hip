@@ -337,12 +337,25 @@ size_t tsm2r_ws(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool tra
     return part + (transB ? (size_t)bt_ld(k, ce) * n * ce : 0);
 }
 
+// A column-major A of at most 32 rows, wider than the TSM2L kernels take:
+// both operands are long in k and short otherwise (tsmttsm of row-major
+// matrices), which the tt kernel reads as they stand; the TSM2R kernel tiles
+// rows, of which there are few here, and copies a row-major B (FP32 16 x
+// 1048576, n = 16, B row-major: 172 us, tt 29; B column-major: 122 and 33).
+// A plan pinned for the shape keeps the TSM2R kernel.
+bool tt_shape(int transA, int64_t m, int64_t k, int64_t n, int dtype) {
+    if (transA || m > 32 || k <= 32 || !plain_dtype(dtype)) return false;
+    const NNPin pin = pin_of(m, k, n, dtype);
+    return pin.S == 0 && pin.tall < 0;
+}
+
 // The most any plan of the call can need (the query does not know the
 // planes' alignment, which picks the kernel instance).
 size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool transB) {
     const size_t a = tsm2r_ws(transA, m, k, n, dtype, transB, true);
     const size_t b = tsm2r_ws(transA, m, k, n, dtype, transB, false);
-    return a > b ? a : b;
+    const size_t c = tt_shape(transA, m, k, n, dtype) ? tt_ws(k, (int)m, (int)n, cu_count()) : 0;
+    return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 
 // C := beta*C + op(A)*op(B) on validated arguments.  `lform` asks for the TSM2L
@@ -401,6 +414,23 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         L.blocks_x = P.bx; L.blocks_y = P.by; L.cus = cus; L.beta = beta;
         if (launch_rowtile(L, dtype, st)) return TSM_ERR_UNSUPPORTED;
         return check_launch("rowtile_kernel");
+    }
+    if (tt_shape(transA, m, k, n, dtype)) {
+        // a caller's workspace of the size the TSM2R kernels need is accepted,
+        // and they run if it is too small for this kernel's partials
+        const size_t need = tt_ws(k, (int)m, (int)n, cus);
+        const size_t nn = tsm2r_ws(transA, m, k, n, dtype, transB, true);
+        if (!ws || ws_bytes >= (nn > need ? nn : need)) {
+            void* w = nullptr;
+            const int rc = get_ws(ws && nn > need ? nn : need, ws, ws_bytes, &w);
+            if (rc) return rc;
+            LaunchTT L{};
+            L.R = k; L.ma = (int)m; L.n = (int)n; L.X = A; L.ldx = lda; L.Y = B; L.ldy = ldb;
+            L.y_rowmajor = transB; L.O = C; L.ldo = ldc; L.part = (double*)w; L.beta = beta;
+            L.cus = cus;
+            if (launch_tt(L, dtype, st)) return TSM_ERR_UNSUPPORTED;
+            return check_launch("tt_kernel");
+        }
     }
     // TSM2R kernels; workspace = [split partials][B copied column-major, or
     // B's packed 16-bit terms for the precision form]

@@ -102,6 +102,19 @@ struct LaunchTN {           // tn: O = X^T*Y, X R x ncols, Y R x n
     const void* yt;         // bf16 planes, n > 16: Y's packed bf16 terms (workspace, or null)
 };
 
+struct LaunchTT {           // tt: O = X^T*Y, row-major X R x ma and Y R x n, ma, n <= 32
+    int64_t R; int ma, n;
+    const void* X; int64_t ldx;       // row r at X + r*ldx
+    const void* Y; int64_t ldy;
+    int y_rowmajor;         // 1: row r at Y + r*ldy; 0: column-major Y
+    void* O; int64_t ldo;
+    double* part;           // tt_ws bytes (workspace)
+    double beta;            // O := beta*O + X^T*Y (O read only if beta != 0)
+    int cus;
+};
+size_t tt_ws(int64_t R, int ma, int n, int cus);
+int launch_tt(const LaunchTT& L, int dtype, hipStream_t st);
+
 // Low-precision storage forms of A (bf16 / f16, single or split planes);
 // `vec`: the planes are 16-byte aligned with a 16-byte multiple leading dimension.
 int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P);

@@ -129,3 +129,43 @@ def test_rowmajor_tall_product(dev, dtype, m, k, n, pad):
         C = tsm.tsm2l(A, torch.ones((n, k), dtype=dtype, device=dev).t())
         assert torch.isinf(C[m // 2]).all()
         assert torch.isfinite(C).sum().item() == (m - 1) * n
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("R,ma,n", [(33, 1, 1), (255, 3, 5), (256, 16, 16), (257, 17, 16),
+                                    (8191, 16, 33), (8193, 32, 17), (131073, 31, 32),
+                                    (1000003, 5, 2)])
+def test_short_and_long_product(dev, dtype, R, ma, n):
+    """A column-major A of few rows (tt kernel), B by rows and by columns, with
+    padded rows; a beta applied once; an infinity in the last row stays in its
+    own outputs; a caller's workspace, also one that holds no more than the
+    TSM2R plan's partials; the pinned TSM2R kernel gives the same product."""
+    seed = 3400 + R + ma + n
+    X = dev_matrix(seed, si.STREAM_A, R, ma, dtype, dev).contiguous()
+    Y = _odd_ld(dev_matrix(seed, si.STREAM_B, R, n, dtype, dev))
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, R, ma, dtype).T,
+                        host_matrix(seed, si.STREAM_B, R, n, dtype))
+    rows = torch.full((R, n + 3), float("nan"), dtype=dtype, device=dev)
+    Yr = rows[:, 1:n + 1]
+    Yr.copy_(Y)
+    code = tsm.F64 if dtype == torch.float64 else tsm.F32
+    for y in (Y, Yr):
+        got = tsm.tsmttsm(X, y)
+        assert err(to_np(got), ref) <= TOL[dtype]
+        assert torch.equal(got, tsm.tsmttsm(X, y))
+        ws = torch.empty(tsm.workspace_size(tsm.OP_TSM2R, ma, R, n, code) + 256,
+                         dtype=torch.uint8, device=dev)
+        assert torch.equal(got, tsm.tsmttsm(X, y, workspace=ws))
+        C = torch.ones((n, ma), dtype=dtype, device=dev).t()
+        tsm.tsmttsm(X, y, out=C, beta=3.0)
+        assert err(to_np(C), ref + 3.0) <= TOL[dtype]
+    if n <= 32:
+        tsm.pin_tsm2r(ma, R, n, code, 1, 0)
+        try:
+            assert err(to_np(tsm.tsmttsm(X, Yr)), ref) <= TOL[dtype]
+        finally:
+            tsm.unpin_tsm2r(ma, R, n, code)
+    X[R - 1, ma - 1] = float("inf")
+    C = tsm.tsmttsm(X, torch.ones((R, n), dtype=dtype, device=dev))
+    assert torch.isinf(C[ma - 1]).all()
+    assert torch.isfinite(C).sum().item() == (ma - 1) * n
