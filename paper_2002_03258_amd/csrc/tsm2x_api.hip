@@ -77,8 +77,11 @@ bool valid_dtype(int dt) { return dt >= TSM_F64 && dt <= TSM_F16_SPLIT; }
 bool plain_dtype(int dt) { return dt == TSM_F64 || dt == TSM_F32; }
 int esize(int dt) { return dt == TSM_F64 ? 8 : 4; }
 
-// 16-byte loads of 16-bit planes
-bool planes_vec(const void* p, int64_t ld) { return ((uintptr_t)p & 15u) == 0 && ld % 8 == 0; }
+// What picks a kernel's instance: plain types, every column on a 128-byte
+// line; 16-bit planes, every column on 16 bytes.
+bool aligned(const void* p, int64_t ld, int dtype) {
+    return plain_dtype(dtype) ? line_aligned(p, ld * esize(dtype)) : ((uintptr_t)p & 15u) == 0 && ld % 8 == 0;
+}
 
 int pow2_ge(int64_t n) {
     int p = 1;
@@ -98,9 +101,9 @@ NNPin pin_of(int64_t m, int64_t k, int64_t n, int dtype) {
     return it == g_pins.end() ? NNPin{0, -1} : it->second;
 }
 
-int plan_nn(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P) {
+int plan_nn(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P) {
     const NNPin pin = pin_of(m, k, n, dtype);
-    return plan_tsm2r(m, k, n, dtype, cus, P, &pin);
+    return plan_tsm2r(m, k, n, dtype, cus, line, P, &pin);
 }
 
 struct RTPlan {
@@ -155,7 +158,6 @@ struct TNPlan {
     int64_t groups;         // 16-column output tiles (a multiple of ct)
     int S;
     int64_t rslice;
-    int rg;
     int ct;                 // output tiles per workgroup
     int pf;                 // 16-bit forms: the next step's X held in flight
     bool yt;                // bf16 planes, n > 16: Y split once into packed terms
@@ -163,17 +165,41 @@ struct TNPlan {
     size_t ws;
 };
 
-// tn: one workgroup per ct 16-row output tiles (columns of X) and slice of
-// R; the WK = 4 wavefronts split the slice.
+// Time of a grid of W equal workgroups relative to the same work spread evenly
+// over the `cus` compute units.  A CU takes hardly more than its share of the
+// memory bandwidth, however many workgroups it holds, so the grid lasts as
+// long as the CUs with one workgroup more than the others; with at most one
+// workgroup per CU nothing overlaps the ends of its loop (5 %).
+double grid_time(int64_t W, int cus) {
+    return W <= cus ? 1.05 * cus / (double)W : (double)(cdiv(W, cus) * cus) / (double)W;
+}
+
+// Plain types: one workgroup per ct 16-column tiles (of the output rows) and
+// slice of R; its 4 wavefronts split the slice, each with its next step in
+// flight.  n > 16: two tiles, which share each staged Y, and one stage of rows
+// per step; n <= 16: two tiles and one stage, or one tile and two stages,
+// whichever grid takes less time (two tiles read 3-7 % faster; FP32 4096^2,
+// n = 8, 128 or 256 workgroups: 17.5 and 14.2 us).  The split S takes the least time
+// by grid_time, the two steps a wavefront spends on filling its pipeline and
+// on the sums, and the partials; at least two steps per wavefront.  (Before:
+// two tiles, S for two workgroups per CU and at least eight steps, nothing in
+// flight for n <= 16.  FP32 20032^2, n = 8: 358 us, now 247; 4096^2: 24 and
+// 14; 3001^2: 43 and 13; FP64 20011^2, n = 16: 868 and 643.)
+void plan_tn_plain(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan* P);
+
 TNPlan plan_tn(int64_t R, int64_t ncols, int64_t n, int dt, int cus) {
     TNPlan P{};
-    // output tiles per workgroup: two share each Y tile when there are
-    // several column groups (Y is then re-read by every group).  The 16-bit
-    // forms take Y straight from L2 then (staged in LDS too, two tiles needed
-    // one workgroup per CU).  With n > 16 two tiles fit one workgroup per CU
-    // only; with the next step in flight they still beat one tile (A 16384^2
-    // and 32768^2, n = 24, 32: split 3.4-4.2 -> 4.4-4.9 TB/s, single
-    // 2.0-2.6 -> 2.5-3.1; without the prefetch one tile was faster)
+    if (plain_dtype(dt)) {
+        plan_tn_plain(R, ncols, n, dt, cus, &P);
+        return P;
+    }
+    // 16-bit forms.  Output tiles per workgroup: two share each Y tile when
+    // there are several column groups (Y is then re-read by every group); they
+    // take Y straight from L2 (staged in LDS too, two tiles needed one
+    // workgroup per CU).  With n > 16 two tiles fit one workgroup per CU only;
+    // with the next step in flight they still beat one tile (A 16384^2 and
+    // 32768^2, n = 24, 32: split 3.4-4.2 -> 4.4-4.9 TB/s, single 2.0-2.6 ->
+    // 2.5-3.1; without the prefetch one tile was faster)
     // bfloat16 planes with n <= 16 and more than four tiles: four tiles per
     // workgroup and one workgroup per CU on the 16-bit matrix cores
     // (tn_lp_kernel, MX; A 16384^2, n = 8: split 5.8 -> 6.6 TB/s, single
@@ -189,11 +215,7 @@ TNPlan plan_tn(int64_t R, int64_t ncols, int64_t n, int dt, int cus) {
     P.ct = ncols > 16 ? (int)env_int("TSM2X_TN_CT", ct_dflt) : 1;
     if (P.ct == 4 && !bf) P.ct = 2;
     if (P.ct != 1 && P.ct != 2 && P.ct != 4) P.ct = 1;
-    // rows per wavefront loop iteration: G stages of 16*RL rows for the
-    // float kernels (one stage with two output tiles), 128 for the 16-bit form
-    P.rg = P.ct >= 2 ? 1 : (int)env_int("TSM2X_TN_G", 2);
-    if (P.rg != 1 && P.rg != 2 && P.rg != 4) P.rg = 2;
-    const int64_t RB = plain_dtype(dt) ? 16 * (16 / esize(dt)) * P.rg : 128;
+    const int64_t RB = 128;                   // rows per wavefront step
     const int NT16 = n <= 16 ? 1 : 2;
     P.groups = cdiv(cdiv(ncols, 16), P.ct) * P.ct;
     const int64_t target = env_int("TSM2X_TN_TARGET_BLOCKS", (int64_t)cus * (P.ct == 4 ? 1 : 2));
@@ -212,10 +234,8 @@ TNPlan plan_tn(int64_t R, int64_t ncols, int64_t n, int dt, int cus) {
         P.yt_off = (P.ws + 255) / 256 * 256;
         P.ws = P.yt_off + yt_bytes;
     }
-    // The next step held in flight (tn_kernel, tn_lp_kernel), where it
-    // measured faster.  Float forms: for n > 16, +48-66 % (A 16384^2 to
-    // 32768^2: 3.0-3.3 -> 4.5-5.3 TB/s); for n <= 16 from -18 % to +6 %, so
-    // not there.  16-bit single form: always (n = 8 and 16: 3.8-4.2 -> 4.8-5.7
+    // The next step held in flight (tn_lp_kernel), where it measured faster.
+    // 16-bit single form: always (n = 8 and 16: 3.8-4.2 -> 4.8-5.7
     // TB/s) and for n > 16 (above).  16-bit split form with n <= 16, whose
     // steps move twice the bytes: only when the grid holds more than two
     // workgroups per CU (at A 16384^2, n = 8, one round of 512 workgroups:
@@ -228,11 +248,48 @@ TNPlan plan_tn(int64_t R, int64_t ncols, int64_t n, int dt, int cus) {
     // override) one step for n <= 8 (5.5 against 4.9 TB/s).
     const bool split = dt == DT_BF16_SPLIT || dt == DT_F16_SPLIT;
     const bool mx = bf && (!split || n <= 16 || P.yt) && P.groups / P.ct > 1;
-    const bool pf = plain_dtype(dt) ? n > 16
-                    : mx            ? P.ct == 4 || n > 8
-                                    : !split || n > 16 || (P.groups / P.ct) * P.S > 2 * (int64_t)cus;
+    const bool pf = mx ? P.ct == 4 || n > 8
+                       : !split || n > 16 || (P.groups / P.ct) * P.S > 2 * (int64_t)cus;
     P.pf = (int)env_int("TSM2X_TN_PF", pf ? 1 : 0);
     return P;
+}
+
+void plan_tn_plain(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan* P) {
+    const bool wide = n > 16;
+    const int es = esize(dt);
+    P->pf = (int)env_int("TSM2X_TN_PF", 1);
+    double best = 0;
+    for (int ct = ncols > (wide ? 16 : 32) ? 2 : 1; ct >= (wide && ncols > 16 ? 2 : 1); --ct) {
+        const int64_t RB = 16 * (16 / es) * (wide || ct == 2 ? 1 : 2);    // rows per wavefront step
+        const int64_t gx = cdiv(cdiv(ncols, 16), ct);
+        // the time of a split in bytes at the streaming rate: X (with one tile
+        // Y is staged twice as often, 6 %), the second launch, 4 to 5 us with
+        // what it costs the host, and the partials, written and read once
+        const double bytes = (double)R * gx * ct * 16 * es * (wide || ct == 2 ? 1.0 : 1.06);
+        const int64_t most = R / (RB * 4 * 2);
+        int64_t last = 0;
+        // candidates: one to four slices, and those that fill j workgroups per CU
+        for (int64_t j = 0; j < 12; ++j) {
+            int64_t S = j < 4 ? j + 1 : (j - 3) * cus / gx;
+            if (S > most) S = most;
+            if (S < 1) S = 1;
+            if (S == last || (j >= 4 && S <= 4)) continue;
+            last = S;
+            const int64_t rs = cdiv(cdiv(R, S), RB * 4) * (RB * 4);
+            const int64_t s = cdiv(R, rs);
+            const double len = (double)rs / (RB * 4);
+            double t = bytes * grid_time(gx * s, cus) * (len + 2) / len;
+            if (s > 1) t += 30e6 + (double)s * gx * ct * 16 * (wide ? 32 : 16) * 16;
+            if (best == 0 || t < best) {
+                best = t;
+                P->ct = ct;
+                P->groups = gx * ct;
+                P->rslice = rs;
+                P->S = (int)s;
+            }
+        }
+    }
+    P->ws = P->S > 1 ? (size_t)P->groups * P->S * 256 * (wide ? 2 : 1) * 8 : 0;
 }
 
 // Workspace: caller's (checked) or the library's grow-only per-device buffer.
@@ -313,8 +370,7 @@ int check_ex(int transA, int transB, int64_t m, int64_t k, int64_t n, const void
 int64_t bt_ld(int64_t k, int ce) { return cdiv(k, 16 / ce) * (16 / ce); }
 
 // Bytes of split partials of a TSM2R-kernel product of at most 32 columns,
-// for the kernel instance the call launches (`vec`: 16-byte loads of the
-// 16-bit planes).
+// for the kernel instance the call launches (`vec`: A is aligned()).
 size_t tsm2r_part(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool vec) {
     const int cus = cu_count();
     if (!plain_dtype(dtype)) {
@@ -324,7 +380,7 @@ size_t tsm2r_part(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool v
     }
     if (transA) return plan_tn(k, m, n, dtype, cus).ws;
     NNPlan P{};
-    return plan_nn(m, k, n, dtype, cus, &P) ? 0 : P.ws;
+    return plan_nn(m, k, n, dtype, cus, vec, &P) ? 0 : P.ws;
 }
 
 // Workspace of a TSM2R-kernel product of at most 32 columns: the split
@@ -349,8 +405,8 @@ bool tt_shape(int transA, int64_t m, int64_t k, int64_t n, int dtype) {
     return pin.S == 0 && pin.tall < 0;
 }
 
-// The most any plan of the call can need (the query does not know the
-// planes' alignment, which picks the kernel instance).
+// The most any plan of the call can need (the query does not know A's
+// alignment, which picks the kernel instance).
 size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool transB) {
     const size_t a = tsm2r_ws(transA, m, k, n, dtype, transB, true);
     const size_t b = tsm2r_ws(transA, m, k, n, dtype, transB, false);
@@ -434,7 +490,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     }
     // TSM2R kernels; workspace = [split partials][B copied column-major, or
     // B's packed 16-bit terms for the precision form]
-    const bool avec = plain_dtype(dtype) || planes_vec(A, lda);
+    const bool avec = aligned(A, lda, dtype);
     void* w = nullptr;
     int rc = get_ws(tsm2r_ws(transA, m, k, n, dtype, transB, avec), ws, ws_bytes, &w);
     if (rc) return rc;
@@ -472,7 +528,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         LaunchTN L{};
         L.R = k; L.ncols = m; L.n = n;
         L.X = A; L.ldx = lda; L.Y = Bk; L.ldy = ldbk; L.O = C; L.ldo = ldc;
-        L.groups = P.groups; L.S = P.S; L.rslice = P.rslice; L.rg = P.rg; L.ct = P.ct;
+        L.groups = P.groups; L.S = P.S; L.rslice = P.rslice; L.ct = P.ct;
         L.pf = P.pf;
         L.beta = beta;
         if (P.S > 1) L.part = (double*)w;
@@ -480,7 +536,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         return check_launch("tn_kernel");
     }
     NNPlan P{};
-    if (plan_nn(m, k, n, dtype, cus, &P)) return TSM_ERR_UNSUPPORTED;
+    if (plan_nn(m, k, n, dtype, cus, avec, &P)) return TSM_ERR_UNSUPPORTED;
     LaunchNN L{};
     L.fn = P.fn;
     L.m = m; L.k = k; L.n = n; L.A = A; L.lda = lda; L.B = Bk; L.ldb = ldbk; L.C = C; L.ldc = ldc;
@@ -598,7 +654,7 @@ int tsm_grad_b(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, cons
     if (rc) return rc;
     LaunchTN L{};
     L.R = m; L.ncols = k; L.n = n; L.X = A; L.ldx = lda; L.Y = dC; L.ldy = lddc; L.O = dB;
-    L.ldo = lddb; L.groups = P.groups; L.S = P.S; L.rslice = P.rslice; L.rg = P.rg; L.ct = P.ct;
+    L.ldo = lddb; L.groups = P.groups; L.S = P.S; L.rslice = P.rslice; L.ct = P.ct;
     L.pf = P.pf;
     if (P.S > 1) L.part = (double*)w;
     if (P.yt) L.yt = (char*)w + P.yt_off;
@@ -801,7 +857,7 @@ const char* tsm2x_kernel_name(int op, int64_t m, int64_t k, int64_t n, int dtype
     if (op != TSM_OP_TSM2R || m <= 0 || k <= 0 || n <= 0 || n > 32 || !plain_dtype(dtype))
         return nullptr;
     NNPlan P{};
-    return plan_nn(m, k, n, dtype, cu_count(), &P) ? nullptr : P.name;
+    return plan_nn(m, k, n, dtype, cu_count(), true, &P) ? nullptr : P.name;
 }
 
 int tsm2x_tsm2r_plan(int64_t m, int64_t k, int64_t n, int dtype, int* slices, int* tall,
@@ -812,7 +868,7 @@ int tsm2x_tsm2r_plan(int64_t m, int64_t k, int64_t n, int dtype, int* slices, in
     if (!plain_dtype(dtype)) return -4;
     const int c = cu_count();
     NNPlan P{};
-    if (plan_nn(m, k, n, dtype, c, &P)) return TSM_ERR_UNSUPPORTED;
+    if (plan_nn(m, k, n, dtype, c, true, &P)) return TSM_ERR_UNSUPPORTED;
     if (slices) *slices = P.S;
     if (tall) *tall = P.tall;
     if (tiles) *tiles = P.tiles;

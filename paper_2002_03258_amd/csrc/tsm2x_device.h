@@ -22,6 +22,17 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
+// Workgroup ids go round the 8 XCDs in turn.  (x, y) of this workgroup of a
+// gridDim.x by gridDim.y grid such that each XCD takes a run of consecutive x
+// (then y) instead.
+__device__ __forceinline__ void xcd_runs(unsigned& x, unsigned& y) {
+    const unsigned id = blockIdx.x + blockIdx.y * gridDim.x, all = gridDim.x * gridDim.y;
+    const unsigned c = id & 7, q = all >> 3, r = all & 7;
+    const unsigned lin = c * q + (c < r ? c : r) + (id >> 3);
+    y = lin / gridDim.x;
+    x = lin - y * gridDim.x;
+}
+
 // `mem`: the same vector in global memory, aligned as its elements are.  The
 // 16-byte global loads and stores of gfx950 need no more than 4-byte
 // alignment, so columns of any leading dimension and base address take them.
@@ -31,15 +42,16 @@ struct VecOf {
     typedef T mem __attribute__((ext_vector_type(N), aligned(sizeof(T))));
 };
 
-// RL consecutive elements starting at p: one 16-byte non-temporal load when
-// all of them are in range (full); otherwise element-wise loads guarded by
-// `valid` elements remaining.
-template <typename T, int RL>
+// RL consecutive elements starting at p: one 16-byte load when all of them
+// are in range (full), non-temporal for NT; otherwise element-wise loads
+// guarded by `valid` elements remaining.
+template <typename T, int RL, bool NT = true>
 __device__ __forceinline__ void load_run(const T* __restrict__ p, int64_t valid,
                                          bool full, T (&out)[RL]) {
     if (full) {
         typedef typename VecOf<T, RL>::mem V;
-        V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
+        V v = NT ? __builtin_nontemporal_load(reinterpret_cast<const V*>(p))
+                 : *reinterpret_cast<const V*>(p);
 #pragma unroll
         for (int r = 0; r < RL; ++r) out[r] = v[r];
     } else {
@@ -151,11 +163,12 @@ __device__ __forceinline__ void nn_finish(int64_t m, int n, T* __restrict__ C, i
 }
 
 // The same for the column tiles of the tn kernels: acc[t][r] of lane l is
-// O[c0 + mrow(l/16, r), 16 t + l%16]; partials go to
-// part[((ctile * nsl + s) * NP + p) * 16 + c].
+// O[cb + mrow(l/16, r), 16 t + l%16], of which the columns below `own` belong
+// to the workgroup before (a last group moved up to be whole); the partial of
+// output row col goes to part[((col / 16 * nsl + s) * NP + p) * 16 + col % 16].
 template <typename T, int NT16, int WK, typename Acc, typename MRow>
 __device__ __forceinline__ void tn_finish(int64_t ncols, int n, T* __restrict__ O, int64_t ldo,
-                                          double beta, int64_t ctile, int s, int nsl,
+                                          double beta, int64_t cb, int64_t own, int s, int nsl,
                                           double* __restrict__ part, double (*red)[WAVE][4 * NT16],
                                           const Acc (&acc)[NT16], MRow mrow) {
     constexpr int NV = 4 * NT16;
@@ -174,13 +187,13 @@ __device__ __forceinline__ void tn_finish(int64_t ncols, int n, T* __restrict__ 
         for (int ww = 1; ww < WK; ++ww) v += red[ww][ln][vi];
         const int t = vi / 4, r = vi % 4;
         const int c = mrow(ln >> 4, r);
-        const int64_t col = ctile * 16 + c;
+        const int64_t col = cb + c;
         const int p = 16 * t + (ln & 15);
-        if (nsl == 1) {
-            if (col < ncols && p < n) O[col + p * ldo] = beta_out(v, beta, O + col + p * ldo);
-        } else {
-            part[((ctile * nsl + s) * NP + p) * 16 + c] = v;
-        }
+        if (col < own || col >= ncols || p >= n) continue;
+        if (nsl == 1)
+            O[col + p * ldo] = beta_out(v, beta, O + col + p * ldo);
+        else
+            part[(((col >> 4) * nsl + s) * NP + p) * 16 + (col & 15)] = v;
     }
 }
 

@@ -31,7 +31,7 @@ namespace tsm {
 // through LDS, so a lane loads 8 rows of a column (one 16-byte run per plane)
 // and writes them, widened to float (hi + lo is exact in float), into the
 // staged block they belong to.
-template <typename T, int NTK, int NTN, int RG, bool NTS, bool PV, int AF, bool ASPLIT>
+template <typename T, int NTK, int NTN, int RG, bool LINE, bool PV, int AF, bool ASPLIT>
 __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
     int64_t m, int k, int n, const void* __restrict__ Av, const uint16_t* __restrict__ Alo,
     int64_t lda, const T* __restrict__ B, int64_t ldb, const T* __restrict__ dC, int64_t lddc,
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
             for (int st = 0; st < KSN; ++st) {
                 const int p = 4 * st + kk;
                 if (p < n)
-                    load_run<T, RL>(dC + r + p * lddc, m - r, full, xv[st][g]);
+                    load_run<T, RL, LINE>(dC + r + p * lddc, m - r, full, xv[st][g]);
                 else
 #pragma unroll
                     for (int q = 0; q < RL; ++q) xv[st][g][q] = T(0);
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
                 for (int st = 0; st < KSK; ++st) {
                     const int c = 4 * st + kk;
                     if (c < k)
-                        load_run<T, RL>((const T*)Av + r + (int64_t)c * lda, m - r, full,
+                        load_run<T, RL, LINE>((const T*)Av + r + (int64_t)c * lda, m - r, full,
                                              xa[AF < 0 ? st : 0][g]);
                     else
 #pragma unroll
@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
                         T v[RL];
 #pragma unroll
                         for (int q = 0; q < RL; ++q) v[q] = acca[g][q][t][rr];
-                        store_run<T, RL, NTS>(dA + r + (int64_t)col * ldda, m - r, full, v);
+                        store_run<T, RL, LINE>(dA + r + (int64_t)col * ldda, m - r, full, v);
                     }
                 }
         }
@@ -285,16 +285,18 @@ static int bwd_launch(const LaunchBwd& L, int64_t* blocks_out, hipStream_t st, b
     if (plan_only) return 0;
     // 16-byte runs of the 16-bit planes (T's runs need no alignment)
     const bool pv = AF < 0 || (((uintptr_t)L.A & 15u) == 0 && L.lda % 8 == 0);
-    // non-temporal stores of dA where each fills whole lines (as rowtile)
-    const bool nts = ((uintptr_t)L.dA & 15u) == 0 && (L.ldda * (int64_t)sizeof(T)) % 16 == 0;
+    // non-temporal where every column starts on a 128-byte line (as rowtile)
+    const int64_t es = sizeof(T);
+    const bool line = (AF >= 0 || line_aligned(L.A, L.lda * es)) && line_aligned(L.dC, L.lddc * es) &&
+                      line_aligned(L.dA, L.ldda * es);
     const uint16_t* alo = ASPLIT ? (const uint16_t*)L.A + L.lda * L.k : nullptr;
     dim3 g((unsigned)bx), b(256);
-#define TSM_B(NTS, PV)                                                                            \
-    TSM_LAUNCH((tsm2l_bwd_kernel<T, NTK, NTN, RG, NTS, PV, AF, ASPLIT>), g, b, 0, st, L.m,        \
+#define TSM_B(LINE, PV)                                                                            \
+    TSM_LAUNCH((tsm2l_bwd_kernel<T, NTK, NTN, RG, LINE, PV, AF, ASPLIT>), g, b, 0, st, L.m,        \
                (int)L.k, (int)L.n, L.A, alo, L.lda, (const T*)L.B, L.ldb, (const T*)L.dC, L.lddc, \
                (T*)L.dA, L.ldda, L.part)
     if (AF < 0 || pv) {
-        if (nts) TSM_B(true, true); else TSM_B(false, true);
+        if (line) TSM_B(true, true); else TSM_B(false, true);
     } else {
         TSM_B(false, AF < 0);
     }

@@ -26,6 +26,11 @@ struct LaunchTimer {
 
 namespace tsm {
 
+// Columns ld_bytes apart from p on all start on a 128-byte line.
+static inline bool line_aligned(const void* p, int64_t ld_bytes) {
+    return (uintptr_t)p % 128 == 0 && ld_bytes % 128 == 0;
+}
+
 enum { DT_F64 = 0, DT_F32 = 1, DT_BF16 = 2, DT_F16 = 3, DT_BF16_SPLIT = 4, DT_F16_SPLIT = 5 };
 
 // Output rows per wavefront of the tn kernel for NP padded output columns:
@@ -52,9 +57,11 @@ struct NNPin {
 };
 
 // Plan of tsm2r for (m, k, n, dtype) on a device with `cus` compute units;
+// `line`: every column of A starts on a 128-byte line;
 // `pin` (may be null) overrides the planner's choices.
 // Returns nonzero if no kernel instance covers the request.
-int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P, const NNPin* pin);
+int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P,
+               const NNPin* pin);
 
 struct LaunchNN {           // tsm2r_nn: C = A*B, column-major A
     const void* fn;
@@ -94,9 +101,8 @@ struct LaunchTN {           // tn: O = X^T*Y, X R x ncols, Y R x n
     int64_t groups;         // 16-column tiles of the output (gridDim.x)
     int S;                  // reduction slices (gridDim.y)
     int64_t rslice;
-    int rg;                 // stages per wavefront loop iteration (1, 2 or 4)
     int ct;                 // 16-column output tiles per workgroup (1 or 2)
-    int pf;                 // 16-bit forms: the next step's X held in flight (0/1)
+    int pf;                 // the next step held in flight (0/1)
     double* part;           // S > 1: partial sums (workspace)
     double beta;            // O := beta*O + X^T*Y (O read only if beta != 0)
     const void* yt;         // bf16 planes, n > 16: Y's packed bf16 terms (workspace, or null)

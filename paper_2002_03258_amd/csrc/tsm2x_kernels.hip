@@ -51,7 +51,7 @@ namespace tsm {
 // the four rows q of a lane lie next to each other, so the loads of a tile
 // cover it whole and each line is fetched once.  Nothing goes through LDS.
 // --------------------------------------------------------------------------
-template <typename T, int KS, int NT16, int RG, bool NTS, int ROWX>
+template <typename T, int KS, int NT16, int RG, bool LINE, int ROWX>
 __global__ __launch_bounds__(256) void rowtile_kernel(
     int64_t m, int kin, int64_t nout, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Y, int64_t ys_in, int64_t ys_out, T* __restrict__ O,
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
             for (int g = 0; g < RG; ++g) {
                 const int64_t r = row0 + 16 * RL * g + RL * rl;
                 if (ji < kin)
-                    load_run<T, RL>(X + r + ji * ldx, m - r, full, xv[st][g]);
+                    load_run<T, RL, LINE>(X + r + ji * ldx, m - r, full, xv[st][g]);
                 else
 #pragma unroll
                     for (int q = 0; q < RL; ++q) xv[st][g][q] = T(0);
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
                                     v[q] = ROWX ? (T)((double)v[q] + beta * (double)o[q])
                                                 : (T)__builtin_fma((T)beta, o[q], v[q]);
                             }
-                            store_run<T, RL, NTS>(O + r + col * ldo, m - r, full, v);
+                            store_run<T, RL, LINE>(O + r + col * ldo, m - r, full, v);
                         }
                     }
             }
@@ -234,12 +234,18 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
 // MFMA layout (16-byte LDS reads, four blocks of 4*RL rows per stage).  LDS operations of one
 // wavefront execute in order, so no barrier is needed between the stage and
 // the read-back.  Lane l holds O[c0 + mrow(kk, r), 16 t + rl] in acc[t][r].
+// The column groups of a slice run next to each other on one XCD, whose L2
+// then fetches the slice's Y once for them (FP32 1000000 x 128, n = 8: 113 ->
+// 93 us; FP64 x 48, n = 5: 77 -> 69); the steps of a wavefront start at a
+// place that depends on its group and slice, so that groups whose columns lie
+// a large power of two apart do not all read the same HBM channels at a time
+// (FP32 16384^2, n = 8: 200 -> 170 us, 8192^2: 71 -> 44).
 // The WK wavefronts of a workgroup split the workgroup's slice of R, and
 // workgroups split R again; partials are added in double precision in a
 // fixed order (workgroup level here, across workgroups by
 // split_reduce_kernel).
 // --------------------------------------------------------------------------
-template <typename T, int NT16, int G, int CT, bool YC>
+template <typename T, int NT16, int G, int CT, bool LINE, bool YC>
 __global__ __launch_bounds__(256) void tn_kernel(
     int64_t R, int64_t ncols, int n, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Y, int64_t ldy, T* __restrict__ O, int64_t ldo,
@@ -253,14 +259,25 @@ __global__ __launch_bounds__(256) void tn_kernel(
     constexpr int NX = 16 * CT;                // staged X columns (CT output tiles)
     constexpr int NC = NX + 16 * NT16;         // then the Y columns
     constexpr int NV = 4 * NT16;
-    __shared__ __align__(16) T lds[WK][NC][SROW];
-    __shared__ double red[WK][WAVE][NV];
+    // the staged tiles, and the wavefronts' sums: over the tiles (the loop is
+    // done by then), except for n > 16, whose workgroups stream 3-5 % faster
+    // with one to a CU than with the two that would fit
+    constexpr size_t LB = sizeof(T) * WK * NC * SROW, SB = sizeof(double) * WK * WAVE * NV;
+    constexpr bool OVER = NT16 == 1;
+    __shared__ __align__(16) unsigned char smem[OVER ? (LB > SB ? LB : SB) : LB + SB];
+    T (*lds)[NC][SROW] = reinterpret_cast<T (*)[NC][SROW]>(smem);
+    double (*red)[WAVE][NV] = reinterpret_cast<double (*)[WAVE][NV]>(smem + (OVER ? 0 : LB));
 
     const int lane = threadIdx.x & (WAVE - 1);
     const int rl = lane & 15, kk = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);   // wavefront-uniform
-    const int64_t c0 = (int64_t)blockIdx.x * NX;
-    const int s = blockIdx.y, nsl = gridDim.y;
+    // a last group of columns that would leave the matrix starts early enough
+    // to be whole (tn_finish writes only its own)
+    const int nsl = gridDim.y;
+    unsigned bx, s;
+    xcd_runs(bx, s);
+    const int64_t cg0 = (int64_t)bx * NX;
+    const int64_t c0 = cg0 + NX > ncols && ncols >= NX ? ncols - NX : cg0;
     const int64_t sb0 = (int64_t)s * rslice;
     const int64_t sb1 = (sb0 + rslice < R) ? sb0 + rslice : R;
     const int64_t lw = rslice / WK;            // multiple of G * SR
@@ -274,9 +291,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
 #pragma unroll
         for (int t = 0; t < NT16; ++t) acc[ct][t] = Acc{0, 0, 0, 0};
 
-    // staged column sc: sc < NX -> X column c0 + sc (the last column where it
-    // is beyond it: those output rows are not stored), else Y column sc - NX
-    auto xcol = [&](int sc) { return c0 + sc < ncols ? c0 + sc : ncols - 1; };
+    // staged column sc: sc < NX -> X column c0 + sc, else Y column sc - NX
     auto load = [&](int64_t rb, T (&v)[G][NC / 4][RL]) {
 #pragma unroll
         for (int gs = 0; gs < G; ++gs) {
@@ -287,7 +302,11 @@ __global__ __launch_bounds__(256) void tn_kernel(
             for (int cg = 0; cg < NC / 4; ++cg) {
                 const int sc = 4 * cg + kk;
                 if (cg < NX / 4) {
-                    load_run<T, RL>(X + r + xcol(sc) * ldx, valid, full, v[gs][cg]);
+                    if (c0 + sc < ncols)
+                        load_run<T, RL, LINE>(X + r + (c0 + sc) * ldx, valid, full, v[gs][cg]);
+                    else
+#pragma unroll
+                        for (int q = 0; q < RL; ++q) v[gs][cg][q] = T(0);
                 } else {
                     const T* src = Y + r + (int64_t)(sc - NX) * ldy;
                     if (YC && sc - NX < n && full) {
@@ -296,7 +315,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
 #pragma unroll
                         for (int q = 0; q < RL; ++q) v[gs][cg][q] = y[q];
                     } else if (sc - NX < n) {
-                        load_run<T, RL>(src, valid, full, v[gs][cg]);
+                        load_run<T, RL, LINE>(src, valid, full, v[gs][cg]);
                     } else {
 #pragma unroll
                         for (int q = 0; q < RL; ++q) v[gs][cg][q] = T(0);
@@ -354,10 +373,11 @@ __global__ __launch_bounds__(256) void tn_kernel(
             for (int cg = 0; cg < NC / 4; ++cg) {
                 const int sc = 4 * cg + kk;
                 if (cg < NX / 4) {
-                    load_run<T, RL>(X + r + xcol(sc) * ldx, RL, true, v[gs][cg]);
+                    load_run<T, RL, LINE>(X + r + (c0 + sc) * ldx, RL, true, v[gs][cg]);
                 } else {
                     const int p = sc - NX < n ? sc - NX : n - 1;
-                    const V y = *reinterpret_cast<const V*>(Y + r + (int64_t)p * ldy);
+                    const V* src = reinterpret_cast<const V*>(Y + r + (int64_t)p * ldy);
+                    const V y = !YC && LINE ? __builtin_nontemporal_load(src) : *src;
 #pragma unroll
                     for (int q = 0; q < RL; ++q) v[gs][cg][q] = y[q];
                 }
@@ -370,38 +390,48 @@ __global__ __launch_bounds__(256) void tn_kernel(
     // the bounds branches of the general loop made those waits drain every
     // load).  Not with four stages per step, whose two steps do not fit the
     // registers.
-    if (G <= 2 && pf && YC && wb1 - wb0 >= G * SR) {
-        const int64_t nit = (wb1 - wb0) / (G * SR);
+    // whole steps, each column group and slice starting at another one; for
+    // n > 16 only slices do, where there is one group: the groups otherwise
+    // gain more from reading the same rows of a large Y at a time (FP64
+    // 16384^2, n = 32: 450 us with rotated groups, 431 without)
+    const int64_t nit = wb1 > wb0 ? (wb1 - wb0) / (G * SR) : 0;
+    const unsigned from = NT16 == 1 ? 3u * bx + WK * s : gridDim.x == 1 ? WK * s : 0u;
+    const int64_t rot = nit > 0 ? from % (unsigned)nit : 0;
+    auto at = [&](int64_t it) {
+        const int64_t i = it + rot;
+        return it < nit ? wb0 + (i < nit ? i : i - nit) * (G * SR) : wb0 + nit * (G * SR);
+    };
+    if (pf && nit > 0 && ncols >= NX) {
         T va[G][NC / 4][RL], vb[G][NC / 4][RL];
-        load_full(wb0, va);
+        load_full(at(0), va);
         int64_t it = 0;
         for (; it + 2 < nit; it += 2) {
-            load_full(wb0 + (it + 1) * G * SR, vb);
+            load_full(at(it + 1), vb);
             __builtin_amdgcn_sched_barrier(0);
             stage_mul(va, true);
-            load_full(wb0 + (it + 2) * G * SR, va);
+            load_full(at(it + 2), va);
             __builtin_amdgcn_sched_barrier(0);
             stage_mul(vb, true);
         }
         if (it + 1 < nit) {
-            load_full(wb0 + (it + 1) * G * SR, vb);
+            load_full(at(it + 1), vb);
             __builtin_amdgcn_sched_barrier(0);
             stage_mul(va, true);
             stage_mul(vb, true);
         } else {
             stage_mul(va, true);
         }
-        if (wb0 + nit * G * SR < wb1) {
-            load(wb0 + nit * G * SR, va);
+        if (at(nit) < wb1) {
+            load(at(nit), va);
             stage_mul(va, false);
         }
     } else if (wb1 > wb0) {
-        const int64_t nit = (wb1 - wb0 + G * SR - 1) / (G * SR);
+        const int64_t all = nit + (at(nit) < wb1 ? 1 : 0);
         T v[G][NC / 4][RL];
-        load(wb0, v);
-        for (int64_t it = 0; it < nit; ++it) {
+        load(at(0), v);
+        for (int64_t it = 0; it < all; ++it) {
             T vn[G][NC / 4][RL];
-            if (it + 1 < nit) load(wb0 + (it + 1) * G * SR, vn);
+            if (it + 1 < all) load(at(it + 1), vn);
             stage_mul(v, false);
 #pragma unroll
             for (int gs = 0; gs < G; ++gs)
@@ -412,12 +442,12 @@ __global__ __launch_bounds__(256) void tn_kernel(
         }
     }
 
-    // one 16-column output tile at a time (global tile index blockIdx.x*CT + ct)
+    // one 16-column output tile at a time
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-        if (ct > 0) __syncthreads();           // red is reused
-        tn_finish<T, NT16, WK>(ncols, n, O, ldo, beta, (int64_t)blockIdx.x * CT + ct, s, nsl, part,
-                               red, acc[ct], [](int kq, int r) { return Mfma<T>::mrow(kq, r); });
+        __syncthreads();                       // red lies over the tiles, and is reused
+        tn_finish<T, NT16, WK>(ncols, n, O, ldo, beta, c0 + 16 * ct, cg0, s, nsl, part, red,
+                               acc[ct], [](int kq, int r) { return Mfma<T>::mrow(kq, r); });
     }
 }
 
@@ -461,11 +491,11 @@ static int occupancy(K kernel, int threads) {
 
 static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
-template <typename T, int KS, int NT16, int RG, bool NTS, int ROWX>
+template <typename T, int KS, int NT16, int RG, bool LINE, int ROWX>
 static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
     // persistent grid: as many workgroups as fit at once (queried occupancy),
     // but no more than there are groups of 4 row tiles
-    static const int occ = occupancy(rowtile_kernel<T, KS, NT16, RG, NTS, ROWX>, 256);
+    static const int occ = occupancy(rowtile_kernel<T, KS, NT16, RG, LINE, ROWX>, 256);
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
     const int64_t ntiles = (L.m + TR - 1) / TR;
     int64_t bx = (int64_t)L.cus * occ / (L.blocks_y > 0 ? L.blocks_y : 1);
@@ -474,31 +504,31 @@ static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
     if (L.blocks_x > 0 && bx > L.blocks_x) bx = L.blocks_x;
     if (bx < 1) bx = 1;
     dim3 grid((unsigned)bx, (unsigned)L.blocks_y), block(256);
-    TSM_LAUNCH((rowtile_kernel<T, KS, NT16, RG, NTS, ROWX>), grid, block, 0, st, L.m, L.kin, L.nout,
+    TSM_LAUNCH((rowtile_kernel<T, KS, NT16, RG, LINE, ROWX>), grid, block, 0, st, L.m, L.kin, L.nout,
                (const T*)L.X, L.ldx, (const T*)L.Y, L.ys_in, L.ys_out, (T*)L.O, L.ldo,
                (int64_t)L.cols_per_block, L.beta);
     return 0;
 }
 
-// The stores of O are non-temporal where they fill whole cache lines (four
-// columns x 256 bytes per wavefront instruction); columns of O that start
-// inside a 16-byte piece leave partial lines at every run's ends, which only
-// ordinary stores merge in the cache.  TSM2X_RT_NTS=0/1 overrides
-// (measurement).  A next-tile register prefetch was measured and
+// LINE: X's and O's columns start on 128-byte lines; loads and stores are then
+// non-temporal (they fill whole lines: four columns x 256 bytes per
+// wavefront instruction).  Otherwise the ends of every run share a line with
+// the next tile's: ordinary loads find it in the cache and ordinary stores
+// merge there (FP64 10302943 x 23, n = 23: 1249 us with
+// non-temporal accesses, 1002 without).  A next-tile register prefetch was measured and
 // dropped: the extra waves it costs hid the latency better.
 template <typename T, int KS, int NT16, int RG>
 static int rowtile_launch(const LaunchRT& L, hipStream_t st) {
-    const char* e = std::getenv("TSM2X_RT_NTS");
-    const bool whole = aligned16(L.O) && (L.ldo * (int64_t)sizeof(T)) % 16 == 0;
-    const bool nts = e && *e ? *e != '0' : whole;
+    const int64_t es = sizeof(T);
+    const bool line = (L.x_rowmajor || line_aligned(L.X, L.ldx * es)) && line_aligned(L.O, L.ldo * es);
     const int rowx = !L.x_rowmajor ? 0 : L.kin == 4 * KS ? 1 : 2;
     if (rowx == 2)
-        return nts ? rowtile_launch_st<T, KS, NT16, RG, true, 2>(L, st)
+        return line ? rowtile_launch_st<T, KS, NT16, RG, true, 2>(L, st)
                    : rowtile_launch_st<T, KS, NT16, RG, false, 2>(L, st);
     if (rowx == 1)
-        return nts ? rowtile_launch_st<T, KS, NT16, RG, true, 1>(L, st)
+        return line ? rowtile_launch_st<T, KS, NT16, RG, true, 1>(L, st)
                    : rowtile_launch_st<T, KS, NT16, RG, false, 1>(L, st);
-    return nts ? rowtile_launch_st<T, KS, NT16, RG, true, 0>(L, st)
+    return line ? rowtile_launch_st<T, KS, NT16, RG, true, 0>(L, st)
                : rowtile_launch_st<T, KS, NT16, RG, false, 0>(L, st);
 }
 
@@ -530,33 +560,28 @@ static int tn_launch(const LaunchTN& L, hipStream_t st) {
     // (YC), non-temporal ones when it is streamed once.
     const int64_t gx = L.groups / CT;
     dim3 grid((unsigned)gx, (unsigned)L.S), block(256);
-    if (gx > 1)
-        TSM_LAUNCH((tn_kernel<T, NT16, G, CT, true>), grid, block, 0, st, L.R,
-                           L.ncols, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O,
-                           L.ldo, L.rslice, L.part, L.beta, L.pf);
-    else
-        TSM_LAUNCH((tn_kernel<T, NT16, G, CT, false>), grid, block, 0, st, L.R,
-                           L.ncols, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O,
-                           L.ldo, L.rslice, L.part, L.beta, L.pf);
+    const int64_t es = sizeof(T);
+    const bool line = line_aligned(L.X, L.ldx * es) && line_aligned(L.Y, L.ldy * es);
+#define TSM_TN(LINE, YC)                                                                          \
+    TSM_LAUNCH((tn_kernel<T, NT16, G, CT, LINE, YC>), grid, block, 0, st, L.R, L.ncols, (int)L.n, \
+               (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O, L.ldo, L.rslice, L.part,      \
+               L.beta, L.pf)
+    if (gx > 1) {
+        if (line) TSM_TN(true, true); else TSM_TN(false, true);
+    } else {
+        if (line) TSM_TN(true, false); else TSM_TN(false, false);
+    }
+#undef TSM_TN
     return 0;
 }
 
 template <typename T>
 static int tn_dispatch(const LaunchTN& L, hipStream_t st) {
-    // G stages of 16*RL rows per loop iteration (loads for the next iteration
-    // are in flight while the current one is staged and multiplied); CT
-    // 16-column output tiles per wavefront share each staged Y tile
-    int rc = 1;
-    const bool wide = L.n > 16;
-    if (L.ct == 2) {
-        rc = wide ? tn_launch<T, 2, 1, 2>(L, st) : tn_launch<T, 1, 1, 2>(L, st);
-    } else if (L.rg == 4) {
-        rc = wide ? tn_launch<T, 2, 4, 1>(L, st) : tn_launch<T, 1, 4, 1>(L, st);
-    } else if (L.rg == 2) {
-        rc = wide ? tn_launch<T, 2, 2, 1>(L, st) : tn_launch<T, 1, 2, 1>(L, st);
-    } else {
-        rc = wide ? tn_launch<T, 2, 1, 1>(L, st) : tn_launch<T, 1, 1, 1>(L, st);
-    }
+    int rc;
+    if (L.n <= 16)
+        rc = L.ct == 2 ? tn_launch<T, 1, 1, 2>(L, st) : tn_launch<T, 1, 2, 1>(L, st);
+    else
+        rc = L.ct == 2 ? tn_launch<T, 2, 1, 2>(L, st) : tn_launch<T, 2, 1, 1>(L, st);
     if (rc || L.S <= 1) return rc;
     return launch_split_reduce(sizeof(T) == 8 ? DT_F64 : DT_F32, L.groups, L.S,
                                L.n <= 16 ? 16 : 32, 16, L.ncols, (int)L.n, L.part, L.O, L.ldo,

@@ -118,7 +118,7 @@ __device__ __forceinline__ void scatter_step(T (&v)[2 * H], int (&c)[2 * H], T (
     }
 }
 
-template <typename T, int KS, int NT16, int RG, bool RES, bool ROWX>
+template <typename T, int KS, int NT16, int RG, bool LINE, bool RES, bool ROWX>
 __global__ __launch_bounds__(256) void kmeans_assign_kernel(
     int64_t m, int k, int n, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Mu,
     int64_t ldm, const T* __restrict__ mu2, int32_t* __restrict__ labels,
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                 for (int g = 0; g < RG; ++g) {
                     const int64_t r = row0 + 16 * RL * g + RL * rl;
                     if (j < k)
-                        load_run<T, RL>(X + r + (int64_t)j * ldx, m - r, full,
+                        load_run<T, RL, LINE>(X + r + (int64_t)j * ldx, m - r, full,
                                              raw[st * RG + g]);
                     else
 #pragma unroll
@@ -194,7 +194,8 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                 const T* src = X + pt * ldx + f0;
                 if (pt < m && f0 + RL <= k) {
                     typedef typename VecOf<T, RL>::mem V;
-                    const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(src));
+                    const V v = LINE ? __builtin_nontemporal_load(reinterpret_cast<const V*>(src))
+                                     : *reinterpret_cast<const V*>(src);
 #pragma unroll
                     for (int e = 0; e < RL; ++e) raw[i][e] = v[e];
                 } else {
@@ -397,7 +398,7 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
     // that each of the four lanes of a row keeps at least one row
     constexpr int RG = sizeof(T) == 4 ? 1 : 2;
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
-    static const int occ = km_occupancy(kmeans_assign_kernel<T, KS, NT16, RG, RES, ROWX>);
+    static const int occ = km_occupancy(kmeans_assign_kernel<T, KS, NT16, RG, true, RES, ROWX>);
     const int64_t ntiles = (L.m + TR - 1) / TR;
     int64_t bx = (int64_t)L.cus * occ;
     const int64_t need = (ntiles + 3) / 4;
@@ -408,9 +409,15 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
                        (const T*)L.Mu, L.ldm, (T*)L.mu2);
     if (hipGetLastError() != hipSuccess) return 1;
     dim3 g((unsigned)bx), b(256);
-    TSM_LAUNCH((kmeans_assign_kernel<T, KS, NT16, RG, RES, ROWX>), g, b, 0, st, L.m, (int)L.k,
-               (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Mu, L.ldm, (const T*)L.mu2, L.labels,
-               (T*)L.dist);
+#define TSM_K(LINE)                                                                            \
+    TSM_LAUNCH((kmeans_assign_kernel<T, KS, NT16, RG, LINE, RES, ROWX>), g, b, 0, st, L.m,      \
+               (int)L.k, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Mu, L.ldm, (const T*)L.mu2, \
+               L.labels, (T*)L.dist)
+    // points whose columns (row-major: whose rows) do not fill 128-byte lines
+    // share lines between loads: not non-temporal then
+    if (line_aligned(L.X, ROWX ? 128 : L.ldx * (int64_t)sizeof(T))) TSM_K(true);
+    else TSM_K(false);
+#undef TSM_K
     return hipGetLastError() != hipSuccess;
 }
 

@@ -561,8 +561,7 @@ __attribute__((amdgpu_waves_per_eu(lp_l_waves<KS, NT16>(), 8))) void tsm2l_lp_ke
 // three (five) matrix-core instructions where the float path takes eight,
 // and no widening.  Products of 16-bit values are exact in float, so the
 // error against the stored values is that of float accumulation, as on the
-// float path.  Whole steps load straight-line (X columns beyond ncols read
-// the last one; their output rows are not stored); a last partial step and
+// float path.  Whole steps load straight-line; a last partial step and
 // unaligned planes take the same step with bounds-checked loads.
 // Y columns beyond n read column n - 1; their output columns are never
 // stored.  With four output tiles per workgroup the split form's 16-bit
@@ -602,7 +601,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
     const int lane = threadIdx.x & (WAVE - 1);
     const int rl = lane & 15, kk = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);   // wavefront-uniform
-    const int64_t c0 = (int64_t)blockIdx.x * NX;
+    // a last group of columns that would leave the matrix starts early enough
+    // to be whole (tn_finish writes only its own)
+    const int64_t cg0 = (int64_t)blockIdx.x * NX;
+    const int64_t c0 = cg0 + NX > ncols && ncols >= NX ? ncols - NX : cg0;
     const int s = blockIdx.y, nsl = gridDim.y;
     const int64_t sb0 = (int64_t)s * rslice;
     const int64_t sb1 = (sb0 + rslice < R) ? sb0 + rslice : R;
@@ -643,9 +645,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
                 for (int q = 0; q < 4; ++q) yv[yi][q] = 0.f;
         }
     };
-    // X column c0 + sc, the last one where it is beyond it: those output rows
-    // are not stored
-    auto xcol = [&](int sc) { return c0 + sc < ncols ? c0 + sc : ncols - 1; };
     // X (and staged Y) of a step are loaded one step ahead; direct Y is loaded
     // at the start of its own step (its registers would cost a wavefront)
     auto loadX = [&](int64_t rb, uint32_t (&xv)[XG][NPL][4]) {
@@ -655,10 +654,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
             const bool full = valid >= 8;
 #pragma unroll
             for (int cg = 0; cg < XG; ++cg) {
-                const int64_t c = xcol(4 * cg + kk);
+                const int64_t c = c0 + 4 * cg + kk;
 #pragma unroll
-                for (int pl = 0; pl < NPL; ++pl)
-                    load8h<VEC>((pl == 0 ? Xh : Xl) + r + c * ldx, valid, full, xv[cg][pl]);
+                for (int pl = 0; pl < NPL; ++pl) {
+                    const uint16_t* P = pl == 0 ? Xh : Xl;
+                    if (c < ncols)
+                        load8h<VEC>(P + r + c * ldx, valid, full, xv[cg][pl]);
+                    else
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) xv[cg][pl][d] = 0u;
+                }
             }
         }
     };
@@ -718,21 +723,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
     // pf, whole steps (16-byte loads, Y direct): straight-line loads, the next step's X kept in flight across
     // the waits for this step's operands (the scheduling barriers stop the
     // compiler from sinking those loads below the waits).
-    const bool whole = !MX && pf && VEC && YC && YD && wb1 - wb0 >= SR;
+    const bool whole = !MX && pf && VEC && YC && YD && ncols >= NX && wb1 - wb0 >= SR;
     // MX: the same without pf (pf only picks one or two steps in flight, with
     // the same arithmetic); a last partial step and unaligned planes take the
     // MX step too, with bounds-checked loads
-    const bool mx_whole = MX && VEC && YC && wb1 - wb0 >= SR;
+    const bool mx_whole = MX && VEC && YC && ncols >= NX && wb1 - wb0 >= SR;
     // two steps in flight need two X steps in registers: not with four split tiles
     constexpr bool MX_TWO = MX && !(SPLIT && CT >= 4);
     auto loadX_full = [&](int64_t rb, uint32_t (&xv)[XG][NPL][4]) {
 #pragma unroll
         for (int pl = 0; pl < NPL; ++pl) {
-            const uint16_t* P = (pl == 0 ? Xh : Xl) + rb + 8 * rl;
+            const uint16_t* P = (pl == 0 ? Xh : Xl) + rb + 8 * rl + (c0 + kk) * ldx;
 #pragma unroll
             for (int cg = 0; cg < XG; ++cg) {
-                const u32x4 v = __builtin_nontemporal_load(
-                    reinterpret_cast<const u32x4*>(P + xcol(4 * cg + kk) * ldx));
+                const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(P + 4 * cg * ldx));
 #pragma unroll
                 for (int d = 0; d < 4; ++d) xv[cg][pl][d] = v[d];
             }
@@ -987,8 +991,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(YT ? 1 : 2,
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
         if (ct > 0) __syncthreads();           // red is reused
-        tn_finish<float, NT16, WK>(ncols, n, O, ldo, 0.0, (int64_t)blockIdx.x * CT + ct, s, nsl,
-                                   part, red, acc[ct],
+        tn_finish<float, NT16, WK>(ncols, n, O, ldo, 0.0, c0 + 16 * ct, cg0, s, nsl, part,
+                                   red, acc[ct],
                                    [](int kq, int r) { return Mfma<float>::mrow(kq, r); });
     }
 }

@@ -43,12 +43,12 @@ namespace tsm {
 template <typename T, int NT16>
 constexpr int nn_waves() { return NT16 == 1 ? 3 : 2; }
 
-template <typename T, int NT16, int RG, int ST, int WK, bool PF = TSM2X_NN_PREFETCH>
+template <typename T, int NT16, int RG, int ST, int WK, bool LINE, bool PF = TSM2X_NN_PREFETCH>
 __global__ __launch_bounds__(WAVE * WK)
 __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kernel(
     int64_t m, int64_t k, int n, const T* __restrict__ A, int64_t lda,
     const T* __restrict__ B, int64_t ldb, T* __restrict__ C, int64_t ldc,
-    int64_t kslice, double* __restrict__ part, int pf, double beta, int swz) {
+    int64_t kslice, double* __restrict__ part, int pf, double beta) {
     typedef Mfma<T> M;
     typedef typename M::acc Acc;
     constexpr int RL = 16 / (int)sizeof(T);
@@ -65,17 +65,9 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
     const int rl = lane & 15, kk = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);   // wavefront-uniform
     const int nsl = gridDim.y;
-    int64_t tile = blockIdx.x;
-    int s = blockIdx.y;
-    if (swz) {
-        // workgroup ids go round the 8 XCDs in turn: give each XCD a run of
-        // neighbouring tiles (launch_tsm2r_nn)
-        const unsigned id = blockIdx.x + blockIdx.y * gridDim.x, all = gridDim.x * gridDim.y;
-        const unsigned x = id & 7, q = all >> 3, r = all & 7;
-        const unsigned lin = x * q + (x < r ? x : r) + (id >> 3);
-        s = lin / gridDim.x;
-        tile = lin - s * gridDim.x;
-    }
+    unsigned bx = blockIdx.x, s = blockIdx.y;
+    if (!LINE) xcd_runs(bx, s);          // (nn_instance)
+    const int64_t tile = bx;
     // a last tile that would leave the matrix starts early enough to be whole
     // (nn_finish writes only its own rows)
     const int64_t row0 = tile * TR + TR > m && m >= TR ? m - TR : tile * TR;
@@ -102,7 +94,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
             for (int g = 0; g < RG; ++g) {
                 const int64_t r = row0 + 16 * RL * g + RL * rl;
                 if (j < wk1)
-                    load_run<T, RL>(A + r + j * lda, m - r, full, av[st][g]);
+                    load_run<T, RL, LINE>(A + r + j * lda, m - r, full, av[st][g]);
                 else
 #pragma unroll
                     for (int q = 0; q < RL; ++q) av[st][g][q] = T(0);
@@ -152,7 +144,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         for (int st = 0; st < ST; ++st)
 #pragma unroll
             for (int g = 0; g < RG; ++g)
-                load_run<T, RL>(base + st * lda + 16 * RL * g, RL, true, av[st][g]);
+                load_run<T, RL, LINE>(base + st * lda + 16 * RL * g, RL, true, av[st][g]);
     };
     auto loadB_full = [&](int64_t j0, T (&bv)[NT16][ST]) {
         typedef typename VecOf<T, BW>::mem V;
@@ -186,7 +178,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
             const int64_t j = j0 + ST * kk + st;
 #pragma unroll
             for (int g = 0; g < RG; ++g) {
-                load_run<T, RL>(base + (j < wk1 ? j : wk1 - 1) * lda + 16 * RL * g, RL, true,
+                load_run<T, RL, LINE>(base + (j < wk1 ? j : wk1 - 1) * lda + 16 * RL * g, RL, true,
                                 av[st][g]);
 #pragma unroll
                 for (int q = 0; q < RL; ++q) av[st][g][q] = j < wk1 ? av[st][g][q] : T(0);
@@ -297,34 +289,42 @@ struct NNInstance {
     const char* name; // as profilers print the kernel
 };
 
-template <typename T, int NT16, int RG, int ST>
+// LINE: every column of A starts on a 128-byte line.  Otherwise vertically
+// neighbouring tiles share a line of every column, which both fetch unless
+// the second finds it in a cache: neighbouring tiles run on one XCD then, and
+// A's loads are not non-temporal.  FP32, n = 5, A 10007 x 9973: 82 us, 73 so;
+// FP32 20011^2, n = 8: 302 and 283; FP64 7777 x 6001, n = 12: 75 and 68.
+// Line-aligned columns keep the workgroups' round-robin order (FP32 16384^2
+// ran 2.5 % slower with neighbours on one XCD, others within 1.5 % either way).
+template <typename T, int NT16, int RG, int ST, bool LINE>
 static NNInstance nn_instance() {
-    static const int occ = occupancy(tsm2r_nn_kernel<T, NT16, RG, ST, 4>, 256);
+    static const int occ = occupancy(tsm2r_nn_kernel<T, NT16, RG, ST, 4, LINE>, 256);
     static char name[80];
     static const bool named =
-        std::snprintf(name, sizeof name, "tsm2r_nn_kernel<%s, %d, %d, %d, 4, %s>",
-                      sizeof(T) == 8 ? "double" : "float", NT16, RG, ST,
+        std::snprintf(name, sizeof name, "tsm2r_nn_kernel<%s, %d, %d, %d, 4, %s, %s>",
+                      sizeof(T) == 8 ? "double" : "float", NT16, RG, ST, LINE ? "true" : "false",
                       TSM2X_NN_PREFETCH ? "true" : "false") > 0;
     (void)named;
-    return NNInstance{(const void*)tsm2r_nn_kernel<T, NT16, RG, ST, 4>,
+    return NNInstance{(const void*)tsm2r_nn_kernel<T, NT16, RG, ST, 4, LINE>,
                       16 * (16 / (int)sizeof(T)) * RG, 4 * ST, occ, name};
 }
 
 // Two tile heights per type: 16*RL*2 rows with 16-column chunks, and twice
 // the rows with 8-column chunks.  Both keep 8 KB of A in flight per wavefront.
+template <bool LINE>
 static bool nn_pick(int dtype, int np, bool tall, NNInstance* out) {
     if (dtype == DT_F64) {
         if (tall)
-            *out = np <= 16 ? nn_instance<double, 1, 4, 2>() : nn_instance<double, 2, 4, 2>();
+            *out = np <= 16 ? nn_instance<double, 1, 4, 2, LINE>() : nn_instance<double, 2, 4, 2, LINE>();
         else
-            *out = np <= 16 ? nn_instance<double, 1, 2, 4>() : nn_instance<double, 2, 2, 4>();
+            *out = np <= 16 ? nn_instance<double, 1, 2, 4, LINE>() : nn_instance<double, 2, 2, 4, LINE>();
         return true;
     }
     if (dtype == DT_F32) {
         if (tall)
-            *out = np <= 16 ? nn_instance<float, 1, 4, 2>() : nn_instance<float, 2, 4, 2>();
+            *out = np <= 16 ? nn_instance<float, 1, 4, 2, LINE>() : nn_instance<float, 2, 4, 2, LINE>();
         else
-            *out = np <= 16 ? nn_instance<float, 1, 2, 4>() : nn_instance<float, 2, 2, 4>();
+            *out = np <= 16 ? nn_instance<float, 1, 2, 4, LINE>() : nn_instance<float, 2, 2, 4, LINE>();
         return true;
     }
     return false;
@@ -355,7 +355,8 @@ static int nn_pf(int64_t n, int dtype, int tall, int64_t W, int cus) {
     return (W <= cus && 8 * W >= 7 * (int64_t)cus) ? 1 : 0;
 }
 
-int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P, const NNPin* pin) {
+int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P,
+               const NNPin* pin) {
     // partial sums are stored at the kernel's padded width (16 or 32 columns)
     const int np = n <= 16 ? 16 : 32;
     const int es = dtype == DT_F64 ? 8 : 4;
@@ -376,7 +377,8 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P, c
     for (int tall = 0; tall < 2; ++tall) {
         if (tall_force >= 0 && tall != (int)tall_force) continue;
         NNInstance I{};
-        if (!nn_pick(dtype, np, tall, &I)) return 1;
+        if (!(line ? nn_pick<true>(dtype, np, tall, &I) : nn_pick<false>(dtype, np, tall, &I)))
+            return 1;
         const int64_t tiles = cdiv64(m, I.tile_rows);
         const int64_t slots = (int64_t)cus * I.occ;
         const int64_t tgt = target < slots ? target : slots;
@@ -416,7 +418,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, NNPlan* P, c
     const bool free_plan = s_pin <= 0 && tall_force < 0 && !(ft && *ft);
     if (free_plan) {
         NNInstance I{};
-        if (nn_pick(dtype, np, false, &I)) {
+        if (line ? nn_pick<true>(dtype, np, false, &I) : nn_pick<false>(dtype, np, false, &I)) {
             const int64_t tiles = cdiv64(m, I.tile_rows);
             int64_t S = cus / tiles;
             const int64_t s_len = k / (WK * 64);
@@ -457,19 +459,10 @@ int launch_tsm2r_nn(const LaunchNN& L, int dtype, hipStream_t st) {
     const char* pfe = std::getenv("TSM2X_NN_PF");
     int pf = (pfe && *pfe) ? (int)std::strtol(pfe, nullptr, 10) : L.pf;
     double beta = L.beta;
-    // Columns that do not start on a 128-byte line: vertically neighbouring
-    // tiles share a line of every column, which both then fetch unless they
-    // run on one XCD (whose L2 serves the second): neighbouring tiles on one
-    // XCD there.  FP32, n = 5: A 10007 x 9973 82 -> 74 us (aligned, 10048 x
-    // 9984: 64), FP32 20011^2 302 -> 286, FP64 7777 x 6001 75 -> 70.  Line-
-    // aligned columns keep the round-robin order: FP32 16384^2 ran 2.5 %
-    // slower with neighbours on one XCD, the others within 1.5 % either way.
-    const int es = dtype == DT_F64 ? 8 : 4;
-    int swz = ((uintptr_t)L.A % 128) != 0 || (L.lda * es) % 128 != 0;
     void* args[] = {(void*)&L.m,   (void*)&L.k,      (void*)&n32,    (void*)&L.A,
                     (void*)&L.lda, (void*)&L.B,      (void*)&L.ldb,  (void*)&L.C,
                     (void*)&L.ldc, (void*)&L.kslice, (void*)&L.part, (void*)&pf,
-                    (void*)&beta,  (void*)&swz};
+                    (void*)&beta};
     hipError_t e;
     {
         LaunchTimer timer(L.fn, st);

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(WAVE * TT_WK) void tt_kernel(
 #pragma unroll
     for (int a = 0; a < NTA; ++a) {
         if (a > 0) __syncthreads();            // red is reused
-        tn_finish<T, NTB, TT_WK>(ma, n, O, ldo, beta, a, blockIdx.x, gridDim.x, part, red, acc[a],
+        tn_finish<T, NTB, TT_WK>(ma, n, O, ldo, beta, 16 * a, 0, blockIdx.x, gridDim.x, part, red, acc[a],
                                  [](int kq, int r) { return Mfma<T>::mrow(kq, r); });
     }
 }
