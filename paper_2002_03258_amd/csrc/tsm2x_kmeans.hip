@@ -118,7 +118,7 @@ __device__ __forceinline__ void scatter_step(T (&v)[2 * H], int (&c)[2 * H], T (
     }
 }
 
-template <typename T, int KS, int NT16, int RG, bool LINE, bool RES, bool ROWX>
+template <typename T, int KS, int NT16, int RG, bool LINE, bool RES, int ROWX>
 __global__ __launch_bounds__(256) void kmeans_assign_kernel(
     int64_t m, int k, int n, const T* __restrict__ X, int64_t ldx, const T* __restrict__ Mu,
     int64_t ldm, const T* __restrict__ mu2, int32_t* __restrict__ labels,
@@ -185,30 +185,65 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                         for (int q = 0; q < RL; ++q) raw[st * RG + g][q] = T(0);
                 }
             }
-        } else {
+        } else if (ROWX == 1) {
+            // whole 16-byte pieces of points and of nothing
+            typedef typename VecOf<T, RL>::type V;
+            if (!RES && full && kc + KC <= k) {
+#pragma unroll
+                for (int i = 0; i < NP; ++i) {
+                    const int pc = lane + WAVE * i;
+                    const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(
+                        X + (row0 + pc / PPP) * ldx + kc + (pc % PPP) * RL));
+#pragma unroll
+                    for (int e = 0; e < RL; ++e) raw[i][e] = v[e];
+                }
+                return;
+            }
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
                 const int pc = lane + WAVE * i;
-                const int p = pc / PPP, f0 = kc + (pc % PPP) * RL;
-                const int64_t pt = row0 + p;
-                const T* src = X + pt * ldx + f0;
-                if (pt < m && f0 + RL <= k) {
-                    typedef typename VecOf<T, RL>::mem V;
-                    const V v = LINE ? __builtin_nontemporal_load(reinterpret_cast<const V*>(src))
-                                     : *reinterpret_cast<const V*>(src);
+                const int64_t pt = row0 + pc / PPP;
+                const int f0 = kc + (pc % PPP) * RL;
+                if (pt < m && f0 < k) {
+                    const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(X + pt * ldx + f0));
 #pragma unroll
                     for (int e = 0; e < RL; ++e) raw[i][e] = v[e];
                 } else {
 #pragma unroll
-                    for (int e = 0; e < RL; ++e)
-                        raw[i][e] = (pt < m && f0 + e < k) ? src[e] : T(0);
+                    for (int e = 0; e < RL; ++e) raw[i][e] = T(0);
                 }
+            }
+        } else if (ROWX == 2) {
+            // a piece that ends beyond the point's k values reads its last RL
+            // (stage puts them where they belong: no branch around a single
+            // load, the wait behind each would drain them all); points beyond
+            // m read point m - 1 (they are not stored)
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int pc = lane + WAVE * i;
+                const int64_t pt = row0 + pc / PPP;
+                const int f0 = kc + (pc % PPP) * RL;
+                typedef typename VecOf<T, RL>::mem V;
+                const V v = *reinterpret_cast<const V*>(X + (pt < m ? pt : m - 1) * ldx +
+                                                        (f0 + RL <= k ? f0 : k - RL));
+#pragma unroll
+                for (int e = 0; e < RL; ++e) raw[i][e] = v[e];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int pc = lane + WAVE * i;
+                const int64_t pt = row0 + pc / PPP;
+                const int f0 = kc + (pc % PPP) * RL;
+#pragma unroll
+                for (int e = 0; e < RL; ++e)
+                    raw[i][e] = (pt < m && f0 + e < k) ? X[pt * ldx + f0 + e] : T(0);
             }
         }
     };
     // stage: the registers of the MFMA layout, xv[st][g][q] = X[row, kc + 4 st + kk]
     // with row = row0 + 16*RL*g + RL*rl + q
-    auto stage = [&](const Raw& raw, T (&xv)[KS][RG][RL]) {
+    auto stage = [&](const Raw& raw, int kc, T (&xv)[KS][RG][RL]) {
         if constexpr (!ROWX) {
 #pragma unroll
             for (int st = 0; st < KS; ++st)
@@ -216,16 +251,18 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                 for (int g = 0; g < RG; ++g)
 #pragma unroll
                     for (int q = 0; q < RL; ++q) xv[st][g][q] = raw[st * RG + g][q];
-            return;
         } else {
         T (*tl)[SROW] = lds[w];
         wave_lds_fence();
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int pc = lane + WAVE * i;
-            const int p = pc / PPP, f = (pc % PPP) * RL;
+            const int p = pc / PPP;
+            const int f0 = (pc % PPP) * RL;
+            const int f = ROWX != 2 || kc + f0 + RL <= k ? f0 : k - RL - kc;
 #pragma unroll
-            for (int e = 0; e < RL; ++e) tl[f + e][p] = raw[i][e];
+            for (int e = 0; e < RL; ++e)
+                if (ROWX != 2 || RES || f + e >= 0) tl[f + e][p] = raw[i][e];
         }
         wave_lds_fence();
         typedef typename VecOf<T, RL>::type V;
@@ -236,6 +273,17 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                 const V v = *reinterpret_cast<const V*>(&tl[4 * st + kk][16 * RL * g + RL * rl]);
 #pragma unroll
                 for (int q = 0; q < RL; ++q) xv[st][g][q] = v[q];
+            }
+        }
+        // columns at or beyond k (the tile may hold anything there)
+        if (ROWX == 2 && kc + KC > k) {
+#pragma unroll
+            for (int st = 0; st < KS; ++st) {
+                const bool live = kc + 4 * st + kk < k;
+#pragma unroll
+                for (int g = 0; g < RG; ++g)
+#pragma unroll
+                    for (int q = 0; q < RL; ++q) xv[st][g][q] = live ? xv[st][g][q] : T(0);
             }
         }
     };
@@ -332,7 +380,7 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
             Raw nxt;
             if (more) fetch(tile + stride, 0, nxt);
             T xv[KS][RG][RL];
-            stage(cur, xv);
+            stage(cur, 0, xv);
             T bv[R], x2[R];
             int bc[R];
             init(bv, bc, x2);
@@ -373,7 +421,7 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(
                 Raw raw;
                 fetch(tile, kc, raw);
                 T xv[KS][RG][RL];
-                stage(raw, xv);
+                stage(raw, kc, xv);
                 accumulate(xv, acc, x2, c0 == 0);
             }
             panel_min(acc, c0, bv, bc);
@@ -390,7 +438,7 @@ static int km_occupancy(K kernel) {
     return nb;
 }
 
-template <typename T, int KS, int NT16, bool RES, bool ROWX>
+template <typename T, int KS, int NT16, bool RES, int ROWX>
 static int km_launch(const LaunchKM& L, hipStream_t st) {
     // row groups per lane: one for float (64-point wave tiles) keeps the
     // registers at four waves per SIMD, which measured 10 % faster on
@@ -400,7 +448,10 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
     static const int occ = km_occupancy(kmeans_assign_kernel<T, KS, NT16, RG, true, RES, ROWX>);
     const int64_t ntiles = (L.m + TR - 1) / TR;
-    int64_t bx = (int64_t)L.cus * occ;
+    // whole row-major pieces of several chunks or panels, float: two workgroups
+    // per CU stream faster than the three that fit (2000000 x 64, n = 64: 344
+    // and 367 us)
+    int64_t bx = (int64_t)L.cus * (!RES && ROWX == 1 && sizeof(T) == 4 && occ > 2 ? 2 : occ);
     const int64_t need = (ntiles + 3) / 4;
     if (bx > need) bx = need;
     if (bx < 1) bx = 1;
@@ -413,10 +464,10 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
     TSM_LAUNCH((kmeans_assign_kernel<T, KS, NT16, RG, LINE, RES, ROWX>), g, b, 0, st, L.m,      \
                (int)L.k, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Mu, L.ldm, (const T*)L.mu2, \
                L.labels, (T*)L.dist)
-    // points whose columns (row-major: whose rows) do not fill 128-byte lines
-    // share lines between loads: not non-temporal then
-    if (line_aligned(L.X, ROWX ? 128 : L.ldx * (int64_t)sizeof(T))) TSM_K(true);
-    else TSM_K(false);
+    // column-major points: non-temporal loads where every column starts on a
+    // 128-byte line (others would fetch the shared lines twice)
+    if (ROWX != 0 || line_aligned(L.X, L.ldx * (int64_t)sizeof(T))) TSM_K(true);
+    else TSM_K(ROWX != 0);
 #undef TSM_K
     return hipGetLastError() != hipSuccess;
 }
@@ -424,11 +475,19 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
 template <typename T, int KS, int NT16>
 static int km_res(const LaunchKM& L, hipStream_t st) {
     const bool res = L.k <= 4 * KS && L.n <= 16 * NT16;
-    if (L.x_rowmajor)
-        return res ? km_launch<T, KS, NT16, true, true>(L, st)
-                   : km_launch<T, KS, NT16, false, true>(L, st);
-    return res ? km_launch<T, KS, NT16, true, false>(L, st)
-               : km_launch<T, KS, NT16, false, false>(L, st);
+    if (!L.x_rowmajor)
+        return res ? km_launch<T, KS, NT16, true, 0>(L, st) : km_launch<T, KS, NT16, false, 0>(L, st);
+    // row-major points: rows of whole aligned 16-byte pieces (1); clamped
+    // pieces (2; value by value, k = 23, FP32 4000001 points 145 us, so 127,
+    // FP64 348 and 265; k = 50, FP64 2000000 points 1005 and 614; whole
+    // pieces ran 5-10 % slower so); value by value for k <= 3 (3), where
+    // most of the clamped pieces would be duplicates
+    const int64_t es = sizeof(T);
+    if ((uintptr_t)L.X % 16 == 0 && L.ldx * es % 16 == 0 && L.k * es % 16 == 0)
+        return res ? km_launch<T, KS, NT16, true, 1>(L, st) : km_launch<T, KS, NT16, false, 1>(L, st);
+    if (KS > 2 || L.k > 3)
+        return res ? km_launch<T, KS, NT16, true, 2>(L, st) : km_launch<T, KS, NT16, false, 2>(L, st);
+    return res ? km_launch<T, 2, NT16, true, 3>(L, st) : km_launch<T, 2, NT16, false, 3>(L, st);
 }
 
 template <typename T>

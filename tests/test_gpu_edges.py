@@ -8,6 +8,7 @@ import torch
 import oracle
 import paper_2002_03258_amd as tsm
 import seeded_inputs as si
+from paper_2002_03258_amd import kmeans
 
 from helpers import TOL, dev_matrix, err, host_matrix, to_np
 
@@ -169,3 +170,24 @@ def test_short_and_long_product(dev, dtype, R, ma, n):
     C = tsm.tsmttsm(X, torch.ones((R, n), dtype=dtype, device=dev))
     assert torch.isinf(C[ma - 1]).all()
     assert torch.isfinite(C).sum().item() == (ma - 1) * n
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("k,n", [(1, 3), (2, 40), (3, 5), (4, 5), (5, 40), (7, 3), (13, 16), (23, 23),
+                                 (31, 40), (33, 5), (34, 40), (63, 17), (65, 33)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_rowmajor_points_ragged_pieces(dev, dtype, k, n, shift):
+    """Row-major points whose k values end inside a 16-byte piece, from an
+    aligned base and one element past it; integer data, labels and distances
+    exact; NaN around every point."""
+    m = 1000 + k
+    seed = 3500 + k + n
+    store = torch.full((m, k + 2 * shift), float("nan"), dtype=dtype, device=dev)
+    X = store[:, shift:shift + k]
+    X.copy_(dev_matrix(seed, si.STREAM_A, m, k, dtype, dev, dist="int", r=6))
+    Mu = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev, dist="int", r=6)
+    lab, dist = kmeans.assign(X, Mu.t())
+    rlab, rdist = oracle.kmeans_assign(host_matrix(seed, si.STREAM_A, m, k, dtype, dist="int", r=6),
+                                       host_matrix(seed, si.STREAM_B, k, n, dtype, dist="int", r=6))
+    assert np.array_equal(lab.cpu().numpy(), rlab)
+    assert np.array_equal(to_np(dist), rdist)
