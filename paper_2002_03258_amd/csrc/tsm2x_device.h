@@ -199,47 +199,49 @@ __device__ __forceinline__ void tn_finish(int64_t ncols, int n, T* __restrict__ 
 
 // Ordered sum of split partials: O[g*W + r, p] = beta * O[g*W + r, p] + sum
 // over s of part[((g * S + s) * NP + p) * W + r], for rows g*W + r < rows and
-// p < n (O is read only if beta != 0).
-// One thread per output when S is small.  For many slices one wavefront
-// per output: lane l adds slices l, l+64, ... in order, then a butterfly in a
-// fixed pattern combines the lanes, so the result does not depend on timing.
-template <typename T, bool WIDE>
-__global__ __launch_bounds__(256) void split_reduce_kernel(int64_t groups, int S, int NP, int W,
+// p < n (O is read only if beta != 0).  EL neighbouring outputs per workgroup
+// of NTH threads, whose NTH / EL parts add every (NTH / EL)-th slice in
+// order, eight loads at a time; the parts are then added in a fixed order, so
+// the result does not depend on timing.
+template <typename T, int EL, int NTH>
+__global__ __launch_bounds__(NTH) void split_reduce_kernel(int64_t groups, int S, int NP, int W,
                                                            int64_t rows, int n,
                                                            const double* __restrict__ part,
                                                            T* __restrict__ O, int64_t ldo,
                                                            double beta) {
+    constexpr int NS = NTH / EL, U = 8;
+    __shared__ double sum[NS > 1 ? NS : 1][EL];
+    const int el = threadIdx.x % EL, sub = threadIdx.x / EL;
     const int64_t E = (int64_t)NP * W;
-    const int64_t total = groups * E;
-    if (!WIDE) {
-        for (int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; idx < total;
-             idx += (int64_t)gridDim.x * blockDim.x) {
-            const int64_t g = idx / E, e = idx % E;
-            const int p = (int)(e / W), r = (int)(e % W);
-            const int64_t row = g * W + r;
-            if (p < n && row < rows) {
-                double v = 0.0;
-                for (int s = 0; s < S; ++s) v += part[(g * S + s) * E + e];
-                O[row + p * ldo] = beta_out(v, beta, O + row + p * ldo);
-            }
-        }
-    } else {
-        const int lane = threadIdx.x & (WAVE - 1);
-        const int64_t wid = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / WAVE;
-        const int64_t nw = (int64_t)gridDim.x * blockDim.x / WAVE;
-        for (int64_t idx = wid; idx < total; idx += nw) {
-            const int64_t g = idx / E, e = idx % E;
-            const int p = (int)(e / W), r = (int)(e % W);
-            const int64_t row = g * W + r;
-            if (p < n && row < rows) {     // uniform across the wavefront
-                double v = 0.0;
-                for (int s = lane; s < S; s += WAVE) v += part[(g * S + s) * E + e];
+    const unsigned live = (unsigned)n * W;           // outputs of a group
+    const int64_t idx = blockIdx.x * (int64_t)EL + el;
+    const int64_t g = idx / live;
+    const unsigned e = (unsigned)(idx - g * live);
+    const unsigned p = e / W;
+    const int64_t row = g * W + (e - p * W);
+    const bool valid = g < groups && row < rows;
+    double v = 0.0;
+    if (valid) {
+        const double* src = part + g * S * E + e;
+        int s = sub;
+        for (; s + (U - 1) * NS < S; s += U * NS) {
+            double x[U];
 #pragma unroll
-                for (int off = WAVE / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-                if (lane == 0) O[row + p * ldo] = beta_out(v, beta, O + row + p * ldo);
-            }
+            for (int u = 0; u < U; ++u) x[u] = src[(int64_t)(s + u * NS) * E];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v += x[u];
+        }
+        for (; s < S; s += NS) v += src[(int64_t)s * E];
+    }
+    if (NS > 1) {
+        sum[sub][el] = v;
+#pragma unroll
+        for (int h = NS / 2; h > 0; h >>= 1) {
+            __syncthreads();
+            if (sub < h) sum[sub][el] = v = v + sum[sub + h][el];
         }
     }
+    if (valid && sub == 0) O[row + p * ldo] = beta_out(v, beta, O + row + p * ldo);
 }
 
 }  // namespace tsm

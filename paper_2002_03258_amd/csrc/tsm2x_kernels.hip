@@ -596,31 +596,25 @@ int launch_tn(const LaunchTN& L, int dtype, hipStream_t st) {
 
 int launch_split_reduce(int dtype, int64_t groups, int S, int NP, int W, int64_t rows, int n,
                         const double* part, void* O, int64_t ldo, double beta, hipStream_t st) {
-    const int64_t total = groups * NP * W;
-    // a wavefront per output only where there are too few outputs to fill the
-    // GPU with a thread each (2^18 outputs of 16 slices: the wavefront form's
-    // lanes read 16 partials 2^21 bytes apart, and the precision-form TSM2R
-    // at A 16384^2, n = 8 ran 14 % slower with 16 slices than with 15)
-    const bool wide = S >= 16 && total < (int64_t)1 << 16;
-    int64_t blocks = wide ? (total + 3) / 4 : (total + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    if (blocks < 1) blocks = 1;
-    const dim3 g((unsigned)blocks), b(256);
+    // Threads per output by the number of slices, so that each adds at most
+    // eight or so, all in flight at once (FP32 2048^2, n = 16, 16 slices: 20.0
+    // us with a wavefront per output, 14.4 with eight threads; 1500 x 28032,
+    // n = 24, 21 slices: 49 us with a thread per output, 41 with eight).
+    const int64_t total = groups * n * W;
+#define TSM_R(T, EL, NTH)                                                                         \
+    TSM_LAUNCH((split_reduce_kernel<T, EL, NTH>), dim3((unsigned)((total + EL - 1) / EL)),        \
+               dim3(NTH), 0, st, groups, S, NP, W, rows, n, part, (T*)O, ldo, beta)
+    const int threads = S > 64 ? 1024 : S > 8 ? 512 : 256;
     if (dtype == DT_F64) {
-        if (wide)
-            TSM_LAUNCH((split_reduce_kernel<double, true>), g, b, 0, st, groups, S, NP, W,
-                               rows, n, part, (double*)O, ldo, beta);
-        else
-            TSM_LAUNCH((split_reduce_kernel<double, false>), g, b, 0, st, groups, S, NP,
-                               W, rows, n, part, (double*)O, ldo, beta);
+        if (threads == 1024) TSM_R(double, 16, 1024);
+        else if (threads == 512) TSM_R(double, 64, 512);
+        else TSM_R(double, 256, 256);
     } else {
-        if (wide)
-            TSM_LAUNCH((split_reduce_kernel<float, true>), g, b, 0, st, groups, S, NP, W,
-                               rows, n, part, (float*)O, ldo, beta);
-        else
-            TSM_LAUNCH((split_reduce_kernel<float, false>), g, b, 0, st, groups, S, NP, W,
-                               rows, n, part, (float*)O, ldo, beta);
+        if (threads == 1024) TSM_R(float, 16, 1024);
+        else if (threads == 512) TSM_R(float, 64, 512);
+        else TSM_R(float, 256, 256);
     }
+#undef TSM_R
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
