@@ -347,12 +347,18 @@ static inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // 7/8 to all of the CUs exactly once (tiles * S in [7/8, 1] x CUs), that plan
 // is taken (A 10240^2 to 30720^2, n = 2..32: 0 to +14 %; grids of 320 on 256
 // CUs, two rounds with a third of the CUs holding two, lost 14-24 %, and are
-// never formed).  pf is also on for n > 16 and FP32 with n <= 4, with any
-// grid (tsm2r_nn_kernel).
+// never formed).  Where neither rule fills 7/8 of the CUs, for the 64 columns
+// per wavefront or the 4 % for the partials, the split goes on to two chunks
+// per wavefront: idle CUs cost more than partials do (FP32 3001^2, n = 20, 24
+// workgroups 60 us, 240 22; 512 x 28032, n = 8, 136 and 252: 33 and 17; FP64
+// 256 x 28032, n = 24, 136 and 252: 24 and 22).  pf is also on for n > 16 and
+// FP32 with n <= 4, with any grid (tsm2r_nn_kernel), and for every grid of at
+// most one workgroup per CU (FP64 4096^2, n = 8, 192 workgroups: 42 us without,
+// 26 with).
 static int nn_pf(int64_t n, int dtype, int tall, int64_t W, int cus) {
     if (tall) return 0;
     if (n > 16 || (dtype == DT_F32 && n <= 4)) return 1;
-    return (W <= cus && 8 * W >= 7 * (int64_t)cus) ? 1 : 0;
+    return W <= cus ? 1 : 0;
 }
 
 int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P,
@@ -420,25 +426,43 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
         NNInstance I{};
         if (line ? nn_pick<true>(dtype, np, false, &I) : nn_pick<false>(dtype, np, false, &I)) {
             const int64_t tiles = cdiv64(m, I.tile_rows);
-            int64_t S = cus / tiles;
-            const int64_t s_len = k / (WK * 64);
-            const int64_t s_cost = (k * es) / ((int64_t)np * 200);
-            if (S > s_len) S = s_len;
-            if (S > s_cost) S = s_cost;
-            if (S < 1) S = 1;
             const int64_t gran = (int64_t)WK * I.chunk;
-            int64_t ks = cdiv64(k, S);
-            ks = cdiv64(ks, gran) * gran;
-            S = cdiv64(k, ks);
-            const int64_t W = tiles * S;
-            if (W <= cus && 8 * W >= 7 * (int64_t)cus && I.occ >= 1) {
+            // the split that fills the CUs once, its cost capped as above,
+            // or (few) at least two chunks per wavefront and no more bytes
+            // of partials, written and read, than A has
+            auto split = [&](bool few) {
+                int64_t S = cus / tiles;
+                const int64_t s_len = few ? k / (2 * gran) : k / (WK * 64);
+                const int64_t s_cost = few ? (k * es) / (n * 16) : (k * es) / ((int64_t)np * 200);
+                if (S > s_len) S = s_len;
+                if (S > s_cost) S = s_cost;
+                return S < 1 ? 1 : S;
+            };
+            auto slice = [&](int64_t S) { return cdiv64(cdiv64(k, S), gran) * gran; };
+            int64_t ks = slice(split(false)), W = tiles * cdiv64(k, ks);
+            bool take = W <= cus && 8 * W >= 7 * (int64_t)cus;
+            const int64_t have = P->tiles * P->S;
+            if (!take && 8 * have < 7 * (int64_t)cus) {
+                // the plan so far leaves CUs idle
+                ks = slice(split(true));
+                W = tiles * cdiv64(k, ks);
+                // time of either in bytes at the streaming rate: its share of
+                // the CUs, two chunks to fill the pipeline, the partials, and
+                // the second launch if it is a new one (4 to 5 us)
+                const double a = 1.05 * cus * (double)m * k * es;
+                const double len = (double)ks / gran;
+                const double cost = a / W * (len + 2) / len + (double)m * n * 16 * cdiv64(k, ks) +
+                                    (P->S == 1 && ks < k ? 30e6 : 0.0);
+                take = W <= cus && (W > have || P->tall) && cost < a / have;
+            }
+            if (take) {
                 P->fn = I.fn;
                 P->name = I.name;
                 P->tiles = tiles;
                 P->tile_rows = I.tile_rows;
                 P->kslice = ks;
-                P->S = (int)S;
-                P->ws = S > 1 ? (size_t)tiles * S * np * I.tile_rows * 8 : 0;
+                P->S = (int)cdiv64(k, ks);
+                P->ws = P->S > 1 ? (size_t)tiles * P->S * np * I.tile_rows * 8 : 0;
                 P->tall = 0;
                 P->occ = I.occ;
             }
