@@ -26,7 +26,9 @@ _DT = {torch.float64: F64, torch.float32: F32}
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """hipStream_t of the current stream of the current device, as an integer
+    (the raw handle: a torch.cuda.Stream object costs 3 us to make)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def is_colmajor(x: torch.Tensor) -> bool:
@@ -42,7 +44,8 @@ def colmajor(x: torch.Tensor) -> torch.Tensor:
 
 
 def empty_colmajor(rows: int, cols: int, dtype, device) -> torch.Tensor:
-    return torch.empty((cols, rows), dtype=dtype, device=device).t()
+    return torch.empty_strided((rows, cols), (1, rows if rows > 0 else 1), dtype=dtype,
+                               device=device)
 
 
 def _ld(x: torch.Tensor) -> int:

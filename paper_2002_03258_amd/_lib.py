@@ -96,8 +96,8 @@ def lib():
 
 
 def call(fn: str, *args) -> None:
-    L = lib()
-    rc = getattr(L, fn)(*args)
+    L = _lib or lib()
+    rc = getattr(L, fn)(*args)      # the library object keeps each function it has looked up
     if rc != 0:
         raise TSMError(fn, rc, L)
 

@@ -22,7 +22,11 @@ intended use: A kept in HBM as its planes across calls.
 """
 from __future__ import annotations
 
+import sys
+
 import torch
+
+_tsm = sys.modules[__package__]     # the package, which imports this module last
 
 _LOWP = {"bf16": ("bf16", False), "bf16_split": ("bf16", True),
          "f16": ("f16", False), "f16_split": ("f16", True)}
@@ -39,7 +43,6 @@ class TSMMatmul(torch.autograd.Function):
     @staticmethod
     def forward(ctx, A: torch.Tensor, B: torch.Tensor, mode: str = "f32", kind: str = "auto",
                 planes=None):
-        from . import split, tsm2l, tsm2r
         kd = _kind(tuple(A.shape), kind)
         if mode in _LOWP:
             if A.dtype != torch.float32 or B.dtype != torch.float32:
@@ -50,7 +53,7 @@ class TSMMatmul(torch.autograd.Function):
                     raise ValueError("the planes do not match mode %s and A's shape" % mode)
                 Aop = planes
             else:
-                Aop = split(A, fmt, lo)
+                Aop = _tsm.split(A, fmt, lo)
         elif planes is not None:
             raise ValueError("planes are only used by the low-precision modes")
         else:
@@ -58,7 +61,7 @@ class TSMMatmul(torch.autograd.Function):
             if A.dtype != want or B.dtype != want:
                 raise ValueError("mode %s needs %s A and B" % (mode, want))
             Aop = A
-        C = tsm2l(Aop, B) if kd == "L" else tsm2r(Aop, B)
+        C = _tsm.tsm2l(Aop, B) if kd == "L" else _tsm.tsm2r(Aop, B)
         if mode in _LOWP:
             ctx.save_for_backward(B)
             ctx.planes = Aop     # A's stored planes (dB uses the stored values)
@@ -70,7 +73,6 @@ class TSMMatmul(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, dC: torch.Tensor):
-        from . import grad_a, grad_b, tsm2l_backward
         saved = ctx.saved_tensors
         B = saved[0]
         Aop = ctx.planes if ctx.planes is not None else saved[1]
@@ -78,12 +80,12 @@ class TSMMatmul(torch.autograd.Function):
         dC = dC.to(B.dtype)
         if ctx.fused and ctx.needs_input_grad[0] and ctx.needs_input_grad[1]:
             # one pass over A and dC for both gradients of a TSM2L product
-            dA, dB = tsm2l_backward(Aop, B, dC)
+            dA, dB = _tsm.tsm2l_backward(Aop, B, dC)
             return dA, dB, None, None, None
         if ctx.needs_input_grad[0]:
-            dA = grad_a(dC, B)
+            dA = _tsm.grad_a(dC, B)
         if ctx.needs_input_grad[1]:
-            dB = grad_b(Aop, dC)
+            dB = _tsm.grad_b(Aop, dC)
         return dA, dB, None, None, None
 
 
@@ -92,8 +94,7 @@ def matmul(A, B: torch.Tensor, mode: str | None = None, kind: str = "auto") -> t
     "f32"), or for a SplitA A to its storage form ("bf16_split", ...); kind
     "R" (TSM2R), "L" (TSM2L) or "auto" (by shape).  For a SplitA the gradient
     with respect to A goes to the float32 matrix it was split from."""
-    from . import SplitA
-    if isinstance(A, SplitA):
+    if isinstance(A, _tsm.SplitA):
         own = A.fmt + ("_split" if A.has_lo else "")
         if mode is None:
             mode = own
