@@ -96,8 +96,9 @@ enum {
  * C m-by-n (ldc >= max(1,m)).  A is streamed from memory once (outer-product
  * form of Algorithm 2 with the on-chip B tile of Algorithms 3-4); the k range
  * is split across wavefronts and workgroups and the partial sums are added in
- * double precision in a fixed order.  n > 32 runs in panels of 32 columns of
- * B and C (A read once per panel, as the paper's t2 < n).
+ * double precision in a fixed order.  n > 64 runs in panels of 64 columns of
+ * B and C (A read once per panel, as the paper's t2 < n), n > 32 in panels of
+ * 32 for the 16-bit forms and transposed A.
  * dtype: any tsm_dtype.  Errors: -1..-11 for arguments 1..11. */
 int tsm2r(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
           const void* B, int64_t ldb, void* C, int64_t ldc, int dtype,
@@ -299,7 +300,8 @@ int tsm2x_tsm2r_plan(int64_t m, int64_t k, int64_t n, int dtype, int* slices, in
  * are the same product for any plan, up to the order of the k sums (the
  * split sums are added in slice order, in double).  A larger S needs more
  * workspace: query tsm2x_workspace_size after pinning.  Products wider than
- * 32 columns run in panels of 32 columns, each looked up by its own width.
+ * 32 columns run in panels of 32 columns, each looked up by its own width,
+ * where one of those widths is pinned.
  * Host only, no HIP call.  Returns 0; -1 m <= 0, -2 k <= 0, -3 n outside
  * 1..32, -4 dtype not F64/F32, -5 slices outside 0..k, -6 tall outside
  * -1..1. */

@@ -414,6 +414,25 @@ size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool
     return a > b ? (a > c ? a : c) : (b > c ? b : c);
 }
 
+// Columns of B and C per pass over A.  A column-major A on the TSM2R kernel
+// takes 64: with two passes of 32 the second reads A again, and the kernel is
+// bound by the matrix cores at 64 (20480^2, n = 64: FP64 1313 us in two
+// passes, 946 in one, FP32 659 and 551; n = 33: 1119 and 722, 544 and 397).  32 elsewhere, for a caller's workspace that holds
+// the partials of 32 columns only, and where a plan of a narrower panel is
+// pinned.
+int64_t panel_width(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
+                    const void* A, int64_t lda, int dtype, const void* ws, size_t ws_bytes) {
+    if (n <= 32 || transA || !plain_dtype(dtype) || (lform && k <= 32) || m <= 32) return 32;
+    auto pinned = [&](int64_t w) {
+        const NNPin p = pin_of(m, k, w, dtype);
+        return p.S > 0 || p.tall >= 0;
+    };
+    if (pinned(32) || (n % 32 && pinned(n % 32))) return 32;
+    if (ws && ws_bytes < tsm2r_ws(0, m, k, n < 64 ? n : 64, dtype, transB, aligned(A, lda, dtype)))
+        return 32;
+    return 64;
+}
+
 // C := beta*C + op(A)*op(B) on validated arguments.  `lform` asks for the TSM2L
 // kernels (all of B on chip) for a column-major A with k <= 32; other shapes
 // run on the TSM2R kernels, which are correct for any k.  A row-major A with
@@ -421,8 +440,9 @@ size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool
 // contiguous dimension over its lanes and wavefronts, and one of at most 32
 // elements leaves most of them idle (FP32 4194304 x 16, n = 16: 1499 us
 // there, 105 here; 17 columns, n = 28: 2.1 ms and 158 us; a column-major A
-// takes 103 and 152).  n > 32 is
-// done in panels of 32 columns of B and C, A being read once per panel.
+// takes 103 and 152).  More
+// columns than one pass takes (panel_width) run in panels of B and C, A being
+// read once per panel.
 int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n, const void* A,
             int64_t lda, const void* B, int64_t ldb, double beta, void* C, int64_t ldc,
             int dtype, void* ws, size_t ws_bytes, hipStream_t st) {
@@ -434,9 +454,10 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         launch_fill_scale(m, n, C, ldc, beta, cdt, st);
         return check_launch("fill_scale_kernel");
     }
-    if (n > 32) {
-        for (int64_t p0 = 0; p0 < n; p0 += 32) {
-            const int64_t np = n - p0 < 32 ? n - p0 : 32;
+    const int64_t panel = panel_width(lform, transA, transB, m, k, n, A, lda, dtype, ws, ws_bytes);
+    if (n > panel) {
+        for (int64_t p0 = 0; p0 < n; p0 += panel) {
+            const int64_t np = n - p0 < panel ? n - p0 : panel;
             const char* Bp = (const char*)B + (transB ? p0 : p0 * ldb) * ce;
             char* Cp = (char*)C + p0 * ldc * ce;
             int rc = product(lform, transA, transB, m, k, np, A, lda, Bp, ldb, beta, Cp, ldc,
@@ -843,11 +864,22 @@ size_t tsm2x_workspace_size(int op, int64_t m, int64_t k, int64_t n, int dtype) 
         return (m >= 0 && k >= 1 && n >= 1 && plain_dtype(dtype)) ? align256((size_t)n * esize(dtype)) : 0;
     if (m <= 0 || k <= 0 || n <= 0 || !valid_dtype(dtype)) return 0;
     const int64_t np = n < 32 ? n : 32;      // panels of 32 columns reuse one workspace
-    // products: enough for a B given transposed as well
+    // products: enough for a B given transposed as well, and for panels of 64
+    // columns and the narrower last one
+    auto nn = [&]() {
+        size_t w = tsm2r_ws_max(0, m, k, np, dtype, true);
+        if (n > 32 && plain_dtype(dtype) && m > 32) {
+            for (const int64_t p : {n < 64 ? n : (int64_t)64, n > 64 ? n % 64 : (int64_t)0}) {
+                const size_t a = p > 0 ? tsm2r_ws_max(0, m, k, p, dtype, true) : 0;
+                if (a > w) w = a;
+            }
+        }
+        return w;
+    };
     switch (op) {
-        case TSM_OP_TSM2R: return tsm2r_ws_max(0, m, k, np, dtype, true);
+        case TSM_OP_TSM2R: return nn();
         case TSM_OP_TSM2R_ROWMAJOR: return plain_dtype(dtype) ? tsm2r_ws_max(1, m, k, np, dtype, true) : 0;
-        case TSM_OP_TSM2L: return k <= 32 ? 0 : tsm2r_ws_max(0, m, k, np, dtype, true);
+        case TSM_OP_TSM2L: return k <= 32 ? 0 : nn();
         case TSM_OP_GRAD_B: return n <= 32 ? plan_tn(m, k, n, dtype, cu_count()).ws : 0;
         default: return 0;
     }

@@ -39,7 +39,7 @@ namespace tsm {
 #define TSM2X_NN_PREFETCH 1
 #endif
 // Waves per SIMD each instance is compiled for: three for n <= 16 (the
-// register budget is then 168), two for n <= 32.
+// register budget is then 168), two beyond.
 template <typename T, int NT16>
 constexpr int nn_waves() { return NT16 == 1 ? 3 : 2; }
 
@@ -309,10 +309,21 @@ static NNInstance nn_instance() {
                       16 * (16 / (int)sizeof(T)) * RG, 4 * ST, occ, name};
 }
 
-// Two tile heights per type: 16*RL*2 rows with 16-column chunks, and twice
+// n <= 32: two tile heights per type, 16*RL*2 rows with 16-column chunks, and twice
 // the rows with 8-column chunks.  Both keep 8 KB of A in flight per wavefront.
 template <bool LINE>
 static bool nn_pick(int dtype, int np, bool tall, NNInstance* out) {
+    if (np > 32) {
+        // half of a chunk (double) or of a tile (float) leaves two wavefronts
+        // per SIMD room for the sums of 64 columns, so that one's matrix
+        // instructions run behind the other's loads: 20480^2, n = 64, FP64 992 us
+        // with whole ones at one wavefront, 946 so; FP32 587 and 551
+        if (dtype == DT_F64)
+            *out = np == 48 ? nn_instance<double, 3, 2, 2, LINE>() : nn_instance<double, 4, 2, 2, LINE>();
+        else if (dtype == DT_F32)
+            *out = np == 48 ? nn_instance<float, 3, 1, 4, LINE>() : nn_instance<float, 4, 1, 4, LINE>();
+        return dtype == DT_F64 || dtype == DT_F32;
+    }
     if (dtype == DT_F64) {
         if (tall)
             *out = np <= 16 ? nn_instance<double, 1, 4, 2, LINE>() : nn_instance<double, 2, 4, 2, LINE>();
@@ -363,8 +374,8 @@ static int nn_pf(int64_t n, int dtype, int tall, int64_t W, int cus) {
 
 int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P,
                const NNPin* pin) {
-    // partial sums are stored at the kernel's padded width (16 or 32 columns)
-    const int np = n <= 16 ? 16 : 32;
+    // partial sums are stored at the kernel's padded width (16, 32, 48 or 64)
+    const int np = (int)((n + 15) / 16) * 16;
     const int es = dtype == DT_F64 ? 8 : 4;
     const int WK = 4;
     int64_t target = (int64_t)cus * 15 / 8;
@@ -378,6 +389,38 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
     if (pin && pin->S > 0) s_pin = pin->S;
     if (pin && pin->tall >= 0) tall_force = pin->tall;
 
+    if (np > 32) {
+        // bound by the matrix cores: the split whose grid lasts least, counting
+        // full rounds of one workgroup per CU, two chunks to fill a
+        // wavefront's pipeline and the partials, written and read
+        NNInstance I{};
+        if (!(line ? nn_pick<true>(dtype, np, false, &I) : nn_pick<false>(dtype, np, false, &I)))
+            return 1;
+        const int64_t tiles = cdiv64(m, I.tile_rows), gran = (int64_t)WK * I.chunk;
+        double best = 0;
+        for (int64_t S = 1; S == 1 || (S <= k / (2 * gran) && tiles * S <= 8 * (int64_t)cus); ++S) {
+            const int64_t ks = cdiv64(cdiv64(k, S), gran) * gran, s = cdiv64(k, ks);
+            const int64_t W = tiles * s;
+            const double len = (double)ks / gran;
+            double t = (double)m * k * es * ((double)(cdiv64(W, cus) * cus) / (double)W) * (len + 2) / len;
+            if (s > 1) t += 30e6 + (double)s * m * n * 16;
+            if (S == 1 || t < best) {
+                best = t;
+                P->S = (int)s;
+                P->kslice = ks;
+            }
+        }
+        P->np = np;
+        P->fn = I.fn;
+        P->name = I.name;
+        P->tiles = tiles;
+        P->tile_rows = I.tile_rows;
+        P->ws = P->S > 1 ? (size_t)tiles * P->S * np * I.tile_rows * 8 : 0;
+        P->tall = 0;
+        P->occ = I.occ;
+        P->pf = 1;
+        return 0;
+    }
     bool found = false;
     double best_dev = 0;
     for (int tall = 0; tall < 2; ++tall) {

@@ -191,3 +191,35 @@ def test_rowmajor_points_ragged_pieces(dev, dtype, k, n, shift):
                                        host_matrix(seed, si.STREAM_B, k, n, dtype, dist="int", r=6))
     assert np.array_equal(lab.cpu().numpy(), rlab)
     assert np.array_equal(to_np(dist), rdist)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(33, 40, 33), (65, 130, 64), (63, 2049, 48), (1025, 1000, 49),
+                                   (4097, 4099, 63), (300, 9001, 65), (2000, 700, 130)])
+def test_wide_products(dev, dtype, m, k, n):
+    """More than 32 columns: one pass over A up to 64; a beta applied once; a
+    caller's workspace, also one that holds the partials of 32 columns only,
+    and a pinned 32-column plan, which keeps passes of 32."""
+    seed = 3600 + m + k + n
+    A = _odd_ld(dev_matrix(seed, si.STREAM_A, m, k, dtype, dev))
+    B = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev)
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype),
+                        host_matrix(seed, si.STREAM_B, k, n, dtype))
+    got = tsm.tsm2r(A, B)
+    assert err(to_np(got), ref) <= TOL[dtype]
+    assert err(to_np(tsm.tsm2r(A, B.contiguous())), ref) <= TOL[dtype]
+    C = torch.ones((n, m), dtype=dtype, device=dev).t()
+    tsm.gemm(A, B, out=C, beta=-2.0)
+    assert err(to_np(C), ref - 2.0) <= TOL[dtype]
+    code = tsm.F64 if dtype == torch.float64 else tsm.F32
+    ws = torch.empty(tsm.workspace_size(tsm.OP_TSM2R, m, k, n, code) + 256, dtype=torch.uint8,
+                     device=dev)
+    assert torch.equal(tsm.tsm2r(A, B, workspace=ws), got)
+    small = max(tsm.workspace_size(tsm.OP_TSM2R, m, k, w, code) for w in {32, n % 32 or 32})
+    if small > 0:
+        assert err(to_np(tsm.tsm2r(A, B, workspace=ws[:small])), ref) <= TOL[dtype]
+    tsm.pin_tsm2r(m, k, 32, code, 1, 0)
+    try:
+        assert err(to_np(tsm.tsm2r(A, B)), ref) <= TOL[dtype]
+    finally:
+        tsm.unpin_tsm2r(m, k, 32, code)
