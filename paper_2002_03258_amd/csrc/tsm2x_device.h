@@ -113,6 +113,21 @@ template <> struct Mfma<double> {
     }
 };
 
+// Float sums of many products: after every FLUSH steps the accumulators are
+// added to a second set and start again, so that no chain of float additions
+// is longer than FLUSH steps or the number of flushes (the error of a sum
+// grows with the root of the chain: FP32 TSM2R with one slice, k = 30720,
+// 1.6e-6 unflushed).  The plans may then give a wavefront long ranges.
+constexpr int FLUSH = 32;
+template <int N, typename Acc>
+__device__ __forceinline__ void flush(Acc (&acc)[N], Acc (&sum)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        sum[i] += acc[i];
+        acc[i] = Acc{0, 0, 0, 0};
+    }
+}
+
 // An output element: v, or v + beta * (old value) when beta != 0 (the old
 // value is read only then), added in double and rounded once to T.
 template <typename T>

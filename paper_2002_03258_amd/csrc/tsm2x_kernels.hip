@@ -290,6 +290,16 @@ __global__ __launch_bounds__(256) void tn_kernel(
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int t = 0; t < NT16; ++t) acc[ct][t] = Acc{0, 0, 0, 0};
+    constexpr bool FL = sizeof(T) == 4;
+    constexpr int NA = CT * NT16;
+    typedef Acc Flat[NA];
+    Acc tot[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) tot[i] = Acc{0, 0, 0, 0};
+    auto flush_at = [&](int64_t done) {        // after `done` whole steps
+        if (FL && done % (FLUSH / 8) == 0)
+            flush<NA>(reinterpret_cast<Flat&>(acc), reinterpret_cast<Flat&>(tot));
+    };
 
     // staged column sc: sc < NX -> X column c0 + sc, else Y column sc - NX
     auto load = [&](int64_t rb, T (&v)[G][NC / 4][RL]) {
@@ -412,6 +422,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
             load_full(at(it + 2), va);
             __builtin_amdgcn_sched_barrier(0);
             stage_mul(vb, true);
+            flush_at(it + 2);
         }
         if (it + 1 < nit) {
             load_full(at(it + 1), vb);
@@ -421,6 +432,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
         } else {
             stage_mul(va, true);
         }
+        flush_at(nit);
         if (at(nit) < wb1) {
             load(at(nit), va);
             stage_mul(va, false);
@@ -433,6 +445,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
             T vn[G][NC / 4][RL];
             if (it + 1 < all) load(at(it + 1), vn);
             stage_mul(v, false);
+            if (it < nit) flush_at(it + 1);
 #pragma unroll
             for (int gs = 0; gs < G; ++gs)
 #pragma unroll
@@ -440,6 +453,11 @@ __global__ __launch_bounds__(256) void tn_kernel(
 #pragma unroll
                     for (int q = 0; q < RL; ++q) v[gs][cg][q] = vn[gs][cg][q];
         }
+    }
+
+    if (FL) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) reinterpret_cast<Flat&>(acc)[i] += tot[i];
     }
 
     // one 16-column output tile at a time

@@ -85,6 +85,18 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         for (int q = 0; q < RL; ++q)
 #pragma unroll
             for (int t = 0; t < NT16; ++t) acc[g][q][t] = Acc{0, 0, 0, 0};
+    // the second set of sums, where registers allow it (n = 17..32 has none
+    // to spare; 49..64 spills 11 of them, 3 %)
+    constexpr bool FL = sizeof(T) == 4 && RG <= 2 && (NT16 == 1 || RG == 1);
+    constexpr int NA = RG * RL * NT16;
+    typedef Acc Flat[NA];
+    Acc tot[FL ? NA : 1];
+#pragma unroll
+    for (int i = 0; i < (FL ? NA : 1); ++i) tot[i] = Acc{0, 0, 0, 0};
+    auto flush_at = [&](int done) {            // after `done` chunks
+        if constexpr (FL)
+            if (done % FLUSH == 0) flush<NA>(reinterpret_cast<Flat&>(acc), reinterpret_cast<Flat&>(tot));
+    };
 
     auto loadA = [&](int64_t j0, T (&av)[ST][RG][RL]) {
 #pragma unroll
@@ -207,6 +219,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
             loadA_full(wk0 + CW * (gc + 2), aa);
             __builtin_amdgcn_sched_barrier(0);
             mul_live(ab, bb);
+            flush_at(gc + 2);
         }
         if (gc + 1 < ng) {
             loadB_full(wk0 + CW * (gc + 1), bb);
@@ -217,6 +230,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         } else {
             mul_live(aa, ba);
         }
+        flush_at(ng);
         if (wk0 + (int64_t)CW * ng < wk1) {
             loadB(wk0 + (int64_t)CW * ng, ba);
             loadA_tail(wk0 + (int64_t)CW * ng, aa);
@@ -239,6 +253,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
                 loadB(wk0 + CW * (gc + 1), bn);
             }
             mul(av, bv);
+            if (full) flush_at(gc + 1);
             if (PF) {
 #pragma unroll
                 for (int st = 0; st < ST; ++st)
@@ -254,6 +269,10 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         }
     }
 
+    if constexpr (FL) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) reinterpret_cast<Flat&>(acc)[i] += tot[i];
+    }
     nn_finish<T, NP, WK, TR, PG>(m, n, C, ldc, beta, tile, row0, s, nsl, part,
                                  reinterpret_cast<double*>(smem), [&](int pg, double* red) {
         const int t = pg / 16;
@@ -498,6 +517,10 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
                                     (P->S == 1 && ks < k ? 30e6 : 0.0);
                 take = W <= cus && (W > have || P->tall) && cost < a / have;
             }
+            // float sums of 17..32 columns are not flushed (tsm2r_nn_kernel):
+            // no longer chains than the plan without the prefetch gave an A
+            // off the 128-byte lines
+            if (dtype == DT_F32 && np == 32 && !line && cdiv64(k, ks) < P->S) take = false;
             if (take) {
                 P->fn = I.fn;
                 P->name = I.name;

@@ -109,6 +109,14 @@ __global__ __launch_bounds__(WAVE * TT_WK) void tt_kernel(
                 for (int b = 0; b < NTB; ++b) acc[a][b] = M::op(x[u][a], y[u][b], acc[a][b]);
     };
 
+    constexpr bool FL = sizeof(T) == 4;
+    constexpr int NA = NTA * NTB;
+    typedef Acc Flat[NA];
+    Acc tot[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) tot[i] = Acc{0, 0, 0, 0};
+    int done = 0;
+
     // whole steps go round the wavefronts of the grid; the next one is in
     // flight while this one is multiplied (the barriers keep the compiler
     // from sinking its loads below the waits)
@@ -126,6 +134,9 @@ __global__ __launch_bounds__(WAVE * TT_WK) void tt_kernel(
             load((i + 2 * stride) * SR, x0, y0);
             __builtin_amdgcn_sched_barrier(0);
             mul(x1, y1);
+            done += 2;
+            if (FL && done % (FLUSH / 4) == 0)
+                flush<NA>(reinterpret_cast<Flat&>(acc), reinterpret_cast<Flat&>(tot));
         }
         if (i + stride < nst) {
             load((i + stride) * SR, x1, y1);
@@ -140,6 +151,10 @@ __global__ __launch_bounds__(WAVE * TT_WK) void tt_kernel(
     if (nst * SR < R && nst % stride == first) {
         load_tail(nst * SR, x0, y0);
         mul(x0, y0);
+    }
+    if (FL) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) reinterpret_cast<Flat&>(acc)[i] += tot[i];
     }
 
 #pragma unroll
