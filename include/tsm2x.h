@@ -258,6 +258,17 @@ int tsm_kmeans_assign(int64_t m, int64_t k, int64_t n, const void* X, int64_t ld
 int tsm2x_split(int64_t m, int64_t k, const float* A, int64_t lda, void* hi,
                 void* lo, int64_t ldh, int fmt, void* stream);
 
+/* tsm2x_split and tsm2l on the planes in one pass, for a tall A kept in float
+ * between calls: hi (and lo, if not NULL) as tsm2x_split writes them, and
+ * C = A'*B with A' = hi (+ lo), m-by-k by k-by-n, k, n <= 32; the same bits
+ * as the two calls.  B transposed (transB 1) as in tsm2l_ex.  hi and lo 8-byte
+ * aligned, ldh a multiple of 4 (TSM_ERR_UNSUPPORTED otherwise).
+ * Arguments: 1 transB, 2 m, 3 k, 4 n, 5 A, 6 lda, 7 B, 8 ldb, 9 C, 10 ldc,
+ * 11 hi, 12 lo, 13 ldh, 14 fmt, 15 stream. */
+int tsm2l_split(int transB, int64_t m, int64_t k, int64_t n, const float* A, int64_t lda,
+                const float* B, int64_t ldb, float* C, int64_t ldc, void* hi, void* lo,
+                int64_t ldh, int fmt, void* stream);
+
 /* Bytes of workspace the call (op, m, k, n, dtype) needs; 0 if none. */
 size_t tsm2x_workspace_size(int op, int64_t m, int64_t k, int64_t n,
                             int dtype);

@@ -144,6 +144,24 @@ def split(A: torch.Tensor, fmt: str = "bf16", lo: bool = True) -> SplitA:
     return SplitA(planes, m, k, fmt, lo, source=src)
 
 
+def _split_tsm2l(A: torch.Tensor, B: torch.Tensor, fmt: str, lo: bool):
+    """(split(A, fmt, lo), tsm2l of it and B) in one pass over A; k, n <= 32."""
+    _check_device(A, B)
+    src = A
+    A = colmajor(A)
+    m, k = A.shape
+    n = B.shape[1]
+    B, tb, ldb = _operand(B)
+    ld = plane_ld(m, k)
+    planes = torch.empty((2 if lo else 1, k, ld), dtype=torch.bfloat16 if fmt == "bf16" else
+                         torch.float16, device=A.device)
+    C = empty_colmajor(m, n, torch.float32, A.device)
+    hi = planes.data_ptr()
+    _lib.call("tsm2l_split", tb, m, k, n, A.data_ptr(), _ld(A), B.data_ptr(), ldb, C.data_ptr(),
+              _ld(C), hi, hi + 2 * k * ld if lo else None, ld, 0 if fmt == "bf16" else 1, _stream())
+    return SplitA(planes, m, k, fmt, lo, source=src), C
+
+
 def _layout(x: torch.Tensor):
     """(trans, ld) of a 2-D tensor held column-major (trans 0) or row-major
     (trans 1: the column-major storage of its transpose); None otherwise."""

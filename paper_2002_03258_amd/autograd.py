@@ -44,6 +44,7 @@ class TSMMatmul(torch.autograd.Function):
     def forward(ctx, A: torch.Tensor, B: torch.Tensor, mode: str = "f32", kind: str = "auto",
                 planes=None):
         kd = _kind(tuple(A.shape), kind)
+        C = None
         if mode in _LOWP:
             if A.dtype != torch.float32 or B.dtype != torch.float32:
                 raise ValueError("low-precision modes take float32 A and B")
@@ -52,6 +53,9 @@ class TSMMatmul(torch.autograd.Function):
                 if (planes.fmt, planes.has_lo) != (fmt, lo) or planes.shape != tuple(A.shape):
                     raise ValueError("the planes do not match mode %s and A's shape" % mode)
                 Aop = planes
+            elif kd == "L" and A.dim() == 2 and B.dim() == 2 and A.shape[1] <= 32 and \
+                    B.shape[1] <= 32 and B.shape[0] == A.shape[1]:
+                Aop, C = _tsm._split_tsm2l(A, B, fmt, lo)     # one pass over A
             else:
                 Aop = _tsm.split(A, fmt, lo)
         elif planes is not None:
@@ -61,7 +65,8 @@ class TSMMatmul(torch.autograd.Function):
             if A.dtype != want or B.dtype != want:
                 raise ValueError("mode %s needs %s A and B" % (mode, want))
             Aop = A
-        C = _tsm.tsm2l(Aop, B) if kd == "L" else _tsm.tsm2r(Aop, B)
+        if C is None:
+            C = _tsm.tsm2l(Aop, B) if kd == "L" else _tsm.tsm2r(Aop, B)
         if mode in _LOWP:
             ctx.save_for_backward(B)
             ctx.planes = Aop     # A's stored planes (dB uses the stored values)

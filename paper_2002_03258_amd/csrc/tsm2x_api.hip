@@ -831,6 +831,39 @@ int tsm2x_split(int64_t m, int64_t k, const float* A, int64_t lda, void* hi, voi
     return check_launch("split_kernel");
 }
 
+int tsm2l_split(int transB, int64_t m, int64_t k, int64_t n, const float* A, int64_t lda,
+                const float* B, int64_t ldb, float* C, int64_t ldc, void* hi, void* lo,
+                int64_t ldh, int fmt, void* stream) {
+    if (transB != 0 && transB != 1) return -1;
+    if (m < 0) return -2;
+    if (k < 0) return -3;
+    if (n < 0) return -4;
+    if (!A && m > 0 && k > 0) return -5;
+    if (lda < (m > 1 ? m : 1)) return -6;
+    if (!B && k > 0 && n > 0) return -7;
+    if (ldb < ((transB ? n : k) > 1 ? (transB ? n : k) : 1)) return -8;
+    if (!C && m > 0 && n > 0) return -9;
+    if (ldc < (m > 1 ? m : 1)) return -10;
+    if (!hi && m > 0 && k > 0) return -11;
+    if (ldh < (m > 1 ? m : 1)) return -13;
+    if (fmt != 0 && fmt != 1) return -14;
+    if (k > 32 || n > 32 || ((uintptr_t)hi & 7u) || ((uintptr_t)lo & 7u) || ldh % 4)
+        return TSM_ERR_UNSUPPORTED;
+    if (m == 0) return TSM_SUCCESS;
+    hipStream_t st = (hipStream_t)stream;
+    if (n == 0 || k == 0) {
+        if (n > 0) launch_fill_scale(m, n, C, ldc, 0.0, TSM_F32, st);
+        if (k > 0) launch_split(m, k, A, lda, hi, lo, ldh, fmt, st);
+        return check_launch("split_kernel");
+    }
+    LaunchLS L{};
+    L.m = m; L.k = (int)k; L.n = (int)n; L.A = A; L.lda = lda; L.hi = (uint16_t*)hi;
+    L.lo = (uint16_t*)lo; L.ldh = ldh; L.B = B; L.bsj = transB ? ldb : 1; L.bsp = transB ? 1 : ldb;
+    L.C = C; L.ldc = ldc;
+    launch_tsm2l_split(L, fmt, st);
+    return check_launch("tsm2l_split_kernel");
+}
+
 int tsm_kmeans_assign(int64_t m, int64_t k, int64_t n, const void* X, int64_t ldx,
                       int x_rowmajor, const void* Mu, int64_t ldm, int32_t* labels, void* dist,
                       int dtype, void* ws, size_t ws_bytes, void* stream) {

@@ -138,6 +138,16 @@ int launch_tsm2l_lp(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
                     int64_t bsj, int64_t bsp, float beta, float* C, int64_t ldc, int dtype,
                     int cus, hipStream_t st);
 
+struct LaunchLS {           // planes of a float A (m x k) and C = (hi + lo)*B, k, n <= 32
+    int64_t m; int k, n;
+    const float* A; int64_t lda;
+    uint16_t* hi; uint16_t* lo; int64_t ldh;     // lo null: the single form
+    const float* B; int64_t bsj, bsp;            // B(j, p) = B[j*bsj + p*bsp]
+    float* C; int64_t ldc;
+};
+// the planes 8-byte aligned, ldh a multiple of 4
+int launch_tsm2l_split(const LaunchLS& L, int fmt, hipStream_t st);
+
 struct LaunchBwd {          // fused TSM2L backward: dA = dC*B^T, dB = A^T*dC
     int64_t m, k, n;
     const void* A; int64_t lda;

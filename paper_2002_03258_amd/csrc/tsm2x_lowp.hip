@@ -537,6 +537,113 @@ __attribute__((amdgpu_waves_per_eu(lp_l_waves<KS, NT16>(), 8))) void tsm2l_lp_ke
 }
 
 // --------------------------------------------------------------------------
+// tsm2l_split: the planes of a tall float A (m x k, k <= 32) and C = (hi + lo)*B
+// on them in one pass: what split_kernel and then tsm2l_lp compute, bit for
+// bit, with A read once and its planes written but not read back (a training
+// step that is given A in float keeps the planes for its backward pass).  A
+// wavefront takes one 128-row tile; a lane holds rows 64 h + 4 rl .. + 3 of its
+// columns, so every load of A and store of C covers 256 contiguous bytes of a
+// column and every store of a plane 128.  Bound by memory: per element 4
+// bytes in, 2 or 4 out, and C's.  8388608 x 16, n = 16, bfloat16 hi + lo: 288 us,
+// 207 + 211 in the two passes.
+// --------------------------------------------------------------------------
+template <int FMT, int KS, int NT16, bool SPLIT, bool LINE>
+__global__ __launch_bounds__(256) void tsm2l_split_kernel(
+    int64_t m, int k, int n, const float* __restrict__ A, int64_t lda, uint16_t* __restrict__ hi,
+    uint16_t* __restrict__ lo, int64_t ldh, const float* __restrict__ B, int64_t bsj, int64_t bsp,
+    float* __restrict__ C, int64_t ldc) {
+    typedef Mfma<float> M;
+    constexpr int TR = 128, WPB = 4;
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int rl = lane & 15, kk = lane >> 4;
+    const int64_t row0 = ((int64_t)blockIdx.x * WPB + threadIdx.x / WAVE) * TR;
+    if (row0 >= m) return;
+    const bool full = row0 + TR <= m;
+
+    float a[KS][2][4], bv[KS][NT16];
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+        const int j = 4 * st + kk;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t r = row0 + 64 * h + 4 * rl;
+            if (j < k)
+                load_run<float, 4, LINE>(A + r + (int64_t)j * lda, m - r, full, a[st][h]);
+            else
+#pragma unroll
+                for (int q = 0; q < 4; ++q) a[st][h][q] = 0.f;
+        }
+    }
+    // S operand: B[4 st + kk, 16 t + rl]
+#pragma unroll
+    for (int st = 0; st < KS; ++st)
+#pragma unroll
+        for (int t = 0; t < NT16; ++t) {
+            const int j = 4 * st + kk, p = 16 * t + rl;
+            bv[st][t] = (j < k && p < n) ? B[j * bsj + (int64_t)p * bsp] : 0.f;
+        }
+
+    f32x4 acc[8][NT16];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int t = 0; t < NT16; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+        const int j = 4 * st + kk;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint32_t hb[4], lb[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                // as split_kernel: a - hi is exact; a non-finite hi is carried on
+                hb[q] = rne16<FMT>(a[st][h][q]);
+                const float hv = val16<FMT>(hb[q]);
+                lb[q] = SPLIT ? rne16<FMT>(__builtin_isfinite(hv) ? a[st][h][q] - hv : hv) : 0u;
+                a[st][h][q] = SPLIT ? hv + val16<FMT>(lb[q]) : hv;
+            }
+            const int64_t r = row0 + 64 * h + 4 * rl;
+            const int64_t off = r + (int64_t)j * ldh;
+            if (j < k && full) {
+                __builtin_nontemporal_store(u32x2{hb[0] | hb[1] << 16, hb[2] | hb[3] << 16},
+                                            reinterpret_cast<u32x2*>(hi + off));
+                if (SPLIT)
+                    __builtin_nontemporal_store(u32x2{lb[0] | lb[1] << 16, lb[2] | lb[3] << 16},
+                                                reinterpret_cast<u32x2*>(lo + off));
+            } else if (j < k) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (r + q < m) {
+                        hi[off + q] = (uint16_t)hb[q];
+                        if (SPLIT) lo[off + q] = (uint16_t)lb[q];
+                    }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int t = 0; t < NT16; ++t)
+                acc[q][t] = M::op(bv[st][t], a[st][q / 4][q % 4], acc[q][t]);
+    }
+#pragma unroll
+    for (int t = 0; t < NT16; ++t)
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+            const int col = 16 * t + M::mrow(kk, rr);
+            if (col < n) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int64_t r = row0 + 64 * h + 4 * rl;
+                    float v[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[q] = acc[4 * h + q][t][rr];
+                    store_run<float, 4, LINE>(C + r + (int64_t)col * ldc, m - r, full, v);
+                }
+            }
+        }
+}
+
+// --------------------------------------------------------------------------
 // tn_lp: O(ncols x n) = X^T * Y with X (R x ncols) in the low-precision form
 // and Y (R x n) float: the gradient dB = A^T * dC of the low-precision form.
 // As tn_kernel: per wavefront step of 128 rows, a lane loads 8 rows of one X
@@ -1300,6 +1407,35 @@ int launch_split(int64_t m, int64_t k, const float* A, int64_t lda, void* hi, vo
         else { if (vec) TSM_SPLIT(FMT_F16, false, true); else TSM_SPLIT(FMT_F16, false, false); }
     }
 #undef TSM_SPLIT
+    return 0;
+}
+
+template <int FMT, bool SPLIT>
+static void tsm2l_split_go(const LaunchLS& L, hipStream_t st) {
+    const dim3 g((unsigned)cdiv_lp(L.m, 512)), b(256);
+    const bool line = line_aligned(L.A, L.lda * 4) && line_aligned(L.C, L.ldc * 4);
+#define TSM_S(KS, NT)                                                                             \
+    {                                                                                             \
+        if (line)                                                                                 \
+            TSM_LAUNCH((tsm2l_split_kernel<FMT, KS, NT, SPLIT, true>), g, b, 0, st, L.m, L.k, L.n, \
+                       L.A, L.lda, L.hi, L.lo, L.ldh, L.B, L.bsj, L.bsp, L.C, L.ldc);             \
+        else                                                                                      \
+            TSM_LAUNCH((tsm2l_split_kernel<FMT, KS, NT, SPLIT, false>), g, b, 0, st, L.m, L.k,    \
+                       L.n, L.A, L.lda, L.hi, L.lo, L.ldh, L.B, L.bsj, L.bsp, L.C, L.ldc);        \
+        return;                                                                                   \
+    }
+    if (L.k <= 8) { if (L.n <= 16) TSM_S(2, 1) else TSM_S(2, 2) }
+    if (L.k <= 16) { if (L.n <= 16) TSM_S(4, 1) else TSM_S(4, 2) }
+    if (L.n <= 16) TSM_S(8, 1) else TSM_S(8, 2)
+#undef TSM_S
+}
+
+int launch_tsm2l_split(const LaunchLS& L, int fmt, hipStream_t st) {
+    if (fmt == 0) {
+        if (L.lo) tsm2l_split_go<FMT_BF16, true>(L, st); else tsm2l_split_go<FMT_BF16, false>(L, st);
+    } else {
+        if (L.lo) tsm2l_split_go<FMT_F16, true>(L, st); else tsm2l_split_go<FMT_F16, false>(L, st);
+    }
     return 0;
 }
 

@@ -223,3 +223,29 @@ def test_wide_products(dev, dtype, m, k, n):
         assert err(to_np(tsm.tsm2r(A, B)), ref) <= TOL[dtype]
     finally:
         tsm.unpin_tsm2r(m, k, 32, code)
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "f16"])
+@pytest.mark.parametrize("lo", [False, True])
+@pytest.mark.parametrize("m,k,n", [(1, 1, 1), (127, 3, 5), (128, 8, 16), (129, 9, 17), (513, 16, 16),
+                                   (4097, 17, 32), (100003, 31, 7), (640, 32, 32)])
+def test_split_and_product_in_one_pass(dev, fmt, lo, m, k, n):
+    """The forward of a float A in a 16-bit mode: planes and product equal
+    split() and tsm2l() on them bit for bit, also for values that overflow
+    or are not numbers, from any alignment of A and either order of B."""
+    seed = 3700 + m + k + n
+    A = _odd_ld(dev_matrix(seed, si.STREAM_A, m, k, torch.float32, dev))
+    if m > 8:
+        A[3, 0], A[4, k - 1], A[5, 0] = float("inf"), float("nan"), 1e30
+        A[6, 0], A[7, k - 1] = 1e-41, -0.0
+    B = dev_matrix(seed, si.STREAM_B, k, n, torch.float32, dev)
+    for a in (A, A.t().contiguous().t(), A.contiguous()):
+        for b in (B, B.contiguous()):
+            S = tsm.split(a, fmt, lo=lo)
+            want = tsm.tsm2l(S, b)
+            got_s, got = tsm._split_tsm2l(a, b, fmt, lo)
+            assert got_s.planes[:, :, :m].view(torch.int16).equal(S.planes[:, :, :m].view(torch.int16))
+            assert got.view(torch.int32).equal(want.view(torch.int32))
+            mode = fmt + ("_split" if lo else "")
+            C = tsm.matmul(a, b, mode=mode, kind="L")
+            assert C.view(torch.int32).equal(want.view(torch.int32))
