@@ -121,8 +121,9 @@ int tsm2l(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
  *              max(1,k)), i.e. A stored row-major.  The 16-bit forms of A
  *              (planes written by tsm2x_split) must have transA = 0.
  *   transB  0: B is k-by-n (ldb >= max(1,k));
- *           1: B is given as its transpose, n-by-k (ldb >= max(1,n)).  The
- *              TSM2R kernels first copy B into the workspace column-major.
+ *           1: B is given as its transpose, n-by-k (ldb >= max(1,n)).  With
+ *              transA = 1 a large product first copies B into the workspace
+ *              column-major.
  *   beta    C is read only when beta != 0.  Where the kernel finishes in
  *           double (TSM2R, transA = 1) beta*C is added in double and the
  *           sum rounded once; the TSM2L kernels add it in C's type.

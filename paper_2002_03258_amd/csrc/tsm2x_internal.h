@@ -37,6 +37,7 @@ enum { DT_F64 = 0, DT_F32 = 1, DT_BF16 = 2, DT_F16 = 3, DT_BF16_SPLIT = 4, DT_F1
 // J*NP accumulators per lane, at most 64.
 struct NNPlan {             // TSM2R launch plan (column-major A)
     const void* fn;         // kernel instance
+    const void* fn_bt;      // plain types: the same for a row-major B
     const char* name;       // its name as profilers print it
     int np;                 // padded n
     int tile_rows;
@@ -97,6 +98,7 @@ struct LaunchTN {           // tn: O = X^T*Y, X R x ncols, Y R x n
     int64_t R, ncols, n;
     const void* X; int64_t ldx;
     const void* Y; int64_t ldy;
+    int y_rowmajor;         // plain types: row r of Y at Y + r*ldy
     void* O; int64_t ldo;
     int64_t groups;         // 16-column tiles of the output (gridDim.x)
     int S;                  // reduction slices (gridDim.y)

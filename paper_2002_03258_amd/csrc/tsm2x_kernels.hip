@@ -221,7 +221,8 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
 // --------------------------------------------------------------------------
 // tn: O(ncols x n) = X^T * Y with X (R x ncols) and Y (R x n) column-major:
 // a reduction along the contiguous dimension.  TSM2R with a row-major A
-// (X = A^T) and the gradient dB = A^T * dC.
+// (X = A^T) and the gradient dB = A^T * dC.  (YR: Y row-major, n <= 16, loaded
+// value by value; for small products.)
 //
 // D = O tile: S[rl][kk] = X[r, c0 + rl], T[kk][rl] = Y[r, 16 t + rl] with the
 // reduction index r = rb + RL*kk + q for step q, so lane l needs RL
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(256) void rowtile_kernel(
 // fixed order (workgroup level here, across workgroups by
 // split_reduce_kernel).
 // --------------------------------------------------------------------------
-template <typename T, int NT16, int G, int CT, bool LINE, bool YC>
+template <typename T, int NT16, int G, int CT, bool LINE, bool YC, bool YR>
 __global__ __launch_bounds__(256) void tn_kernel(
     int64_t R, int64_t ncols, int n, const T* __restrict__ X, int64_t ldx,
     const T* __restrict__ Y, int64_t ldy, T* __restrict__ O, int64_t ldo,
@@ -319,7 +320,11 @@ __global__ __launch_bounds__(256) void tn_kernel(
                         for (int q = 0; q < RL; ++q) v[gs][cg][q] = T(0);
                 } else {
                     const T* src = Y + r + (int64_t)(sc - NX) * ldy;
-                    if (YC && sc - NX < n && full) {
+                    if (YR) {
+#pragma unroll
+                        for (int q = 0; q < RL; ++q)
+                            v[gs][cg][q] = sc - NX < n && q < valid ? Y[(r + q) * ldy + sc - NX] : T(0);
+                    } else if (YC && sc - NX < n && full) {
                         typedef typename VecOf<T, RL>::mem V;
                         const V y = *reinterpret_cast<const V*>(src);
 #pragma unroll
@@ -386,6 +391,11 @@ __global__ __launch_bounds__(256) void tn_kernel(
                     load_run<T, RL, LINE>(X + r + (c0 + sc) * ldx, RL, true, v[gs][cg]);
                 } else {
                     const int p = sc - NX < n ? sc - NX : n - 1;
+                    if (YR) {
+#pragma unroll
+                        for (int q = 0; q < RL; ++q) v[gs][cg][q] = Y[(r + q) * ldy + p];
+                        continue;
+                    }
                     const V* src = reinterpret_cast<const V*>(Y + r + (int64_t)p * ldy);
                     const V y = !YC && LINE ? __builtin_nontemporal_load(src) : *src;
 #pragma unroll
@@ -580,14 +590,21 @@ static int tn_launch(const LaunchTN& L, hipStream_t st) {
     dim3 grid((unsigned)gx, (unsigned)L.S), block(256);
     const int64_t es = sizeof(T);
     const bool line = line_aligned(L.X, L.ldx * es) && line_aligned(L.Y, L.ldy * es);
-#define TSM_TN(LINE, YC)                                                                          \
-    TSM_LAUNCH((tn_kernel<T, NT16, G, CT, LINE, YC>), grid, block, 0, st, L.R, L.ncols, (int)L.n, \
-               (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O, L.ldo, L.rslice, L.part,      \
-               L.beta, L.pf)
-    if (gx > 1) {
-        if (line) TSM_TN(true, true); else TSM_TN(false, true);
+#define TSM_TN(LINE, YC, YR)                                                                  \
+    TSM_LAUNCH((tn_kernel<T, NT16, G, CT, LINE, YC, YR>), grid, block, 0, st, L.R, L.ncols,   \
+               (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Y, L.ldy, (T*)L.O, L.ldo, L.rslice, \
+               L.part, L.beta, L.pf)
+    if (L.y_rowmajor) {
+        if constexpr (NT16 == 1) {
+            if (line_aligned(L.X, L.ldx * es)) TSM_TN(true, true, true);
+            else TSM_TN(false, true, true);
+        } else {
+            return 1;
+        }
+    } else if (gx > 1) {
+        if (line) TSM_TN(true, true, false); else TSM_TN(false, true, false);
     } else {
-        if (line) TSM_TN(true, false); else TSM_TN(false, false);
+        if (line) TSM_TN(true, false, false); else TSM_TN(false, false, false);
     }
 #undef TSM_TN
     return 0;

@@ -43,7 +43,8 @@ namespace tsm {
 template <typename T, int NT16>
 constexpr int nn_waves() { return NT16 == 1 ? 3 : 2; }
 
-template <typename T, int NT16, int RG, int ST, int WK, bool LINE, bool PF = TSM2X_NN_PREFETCH>
+template <typename T, int NT16, int RG, int ST, int WK, bool LINE, bool BT,
+          bool PF = TSM2X_NN_PREFETCH>
 __global__ __launch_bounds__(WAVE * WK)
 __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kernel(
     int64_t m, int64_t k, int n, const T* __restrict__ A, int64_t lda,
@@ -120,8 +121,8 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         for (int t = 0; t < NT16; ++t) {
             const int p = 16 * t + rl;
             const int64_t jb = j0 + ST * kk;
-            const T* __restrict__ src = B + jb + (int64_t)p * ldb;
-            if (p < n && jb + ST <= wk1) {
+            const T* __restrict__ src = B + (BT ? jb * ldb + p : jb + (int64_t)p * ldb);
+            if (!BT && p < n && jb + ST <= wk1) {
                 typedef typename VecOf<T, BW>::mem V;
 #pragma unroll
                 for (int h = 0; h < ST / BW; ++h) {
@@ -132,7 +133,7 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
             } else {
 #pragma unroll
                 for (int st = 0; st < ST; ++st)
-                    bv[t][st] = (p < n && jb + st < wk1) ? src[st] : T(0);
+                    bv[t][st] = (p < n && jb + st < wk1) ? src[BT ? st * ldb : st] : T(0);
             }
         }
     };
@@ -162,8 +163,14 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
         typedef typename VecOf<T, BW>::mem V;
 #pragma unroll
         for (int t = 0; t < NT16; ++t) {
-            const int p = 16 * t + rl;
-            const T* __restrict__ src = B + j0 + ST * kk + (int64_t)(p < n ? p : n - 1) * ldb;
+            const int p = 16 * t + rl, pc = p < n ? p : n - 1;
+            const int64_t jb = j0 + ST * kk;
+            if (BT) {
+#pragma unroll
+                for (int st = 0; st < ST; ++st) bv[t][st] = B[(jb + st) * ldb + pc];
+                continue;
+            }
+            const T* __restrict__ src = B + jb + (int64_t)pc * ldb;
 #pragma unroll
             for (int h = 0; h < ST / BW; ++h) {
                 const V v = *reinterpret_cast<const V*>(src + h * BW);
@@ -302,6 +309,7 @@ static int occupancy(K kernel, int threads) {
 
 struct NNInstance {
     const void* fn;
+    const void* fn_bt;      // the same for a row-major B
     int tile_rows;
     int chunk;        // columns per chunk of a wavefront
     int occ;          // resident workgroups per CU
@@ -317,14 +325,15 @@ struct NNInstance {
 // ran 2.5 % slower with neighbours on one XCD, others within 1.5 % either way).
 template <typename T, int NT16, int RG, int ST, bool LINE>
 static NNInstance nn_instance() {
-    static const int occ = occupancy(tsm2r_nn_kernel<T, NT16, RG, ST, 4, LINE>, 256);
+    static const int occ = occupancy(tsm2r_nn_kernel<T, NT16, RG, ST, 4, LINE, false>, 256);
     static char name[80];
     static const bool named =
-        std::snprintf(name, sizeof name, "tsm2r_nn_kernel<%s, %d, %d, %d, 4, %s, %s>",
+        std::snprintf(name, sizeof name, "tsm2r_nn_kernel<%s, %d, %d, %d, 4, %s, false, %s>",
                       sizeof(T) == 8 ? "double" : "float", NT16, RG, ST, LINE ? "true" : "false",
                       TSM2X_NN_PREFETCH ? "true" : "false") > 0;
     (void)named;
-    return NNInstance{(const void*)tsm2r_nn_kernel<T, NT16, RG, ST, 4, LINE>,
+    return NNInstance{(const void*)tsm2r_nn_kernel<T, NT16, RG, ST, 4, LINE, false>,
+                      (const void*)tsm2r_nn_kernel<T, NT16, RG, ST, 4, LINE, true>,
                       16 * (16 / (int)sizeof(T)) * RG, 4 * ST, occ, name};
 }
 
@@ -431,6 +440,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
         }
         P->np = np;
         P->fn = I.fn;
+        P->fn_bt = I.fn_bt;
         P->name = I.name;
         P->tiles = tiles;
         P->tile_rows = I.tile_rows;
@@ -470,6 +480,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
             best_dev = dev;
             P->np = np;
             P->fn = I.fn;
+            P->fn_bt = I.fn_bt;
             P->name = I.name;
             P->tiles = tiles;
             P->tile_rows = I.tile_rows;
@@ -523,6 +534,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
             if (dtype == DT_F32 && np == 32 && !line && cdiv64(k, ks) < P->S) take = false;
             if (take) {
                 P->fn = I.fn;
+                P->fn_bt = I.fn_bt;
                 P->name = I.name;
                 P->tiles = tiles;
                 P->tile_rows = I.tile_rows;
