@@ -167,6 +167,11 @@ int tsm_grad_a(int64_t m, int64_t k, int64_t n, const void* dC, int64_t lddc,
                const void* B, int64_t ldb, void* dA, int64_t ldda, int dtype,
                void* stream);
 
+/* tsm_grad_a with B given as in tsm2l_ex (transB 1: as its transpose, n-by-k,
+ * ldb >= max(1,n)).  Arguments: 1 transB, then those of tsm_grad_a. */
+int tsm_grad_a_ex(int transB, int64_t m, int64_t k, int64_t n, const void* dC, int64_t lddc,
+                  const void* B, int64_t ldb, void* dA, int64_t ldda, int dtype, void* stream);
+
 /* Gradient with respect to B of L = <dC, A*B>:  dB = A^T * dC.
  * A m-by-k (lda >= max(1,m)), dC m-by-n (lddc >= max(1,m)),
  * dB k-by-n (lddb >= max(1,k)); n <= 32, any m and k.  The reduction over
@@ -202,6 +207,14 @@ int tsm2l_backward(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
                    const void* B, int64_t ldb, const void* dC, int64_t lddc,
                    void* dA, int64_t ldda, void* dB, int64_t lddb, int dtype,
                    void* ws, size_t ws_bytes, void* stream);
+
+/* tsm2l_backward with B given as in tsm2l_ex (transB 1: as its transpose,
+ * n-by-k, ldb >= max(1,n)).  Arguments: 1 transB, then those of
+ * tsm2l_backward. */
+int tsm2l_backward_ex(int transB, int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
+                      const void* B, int64_t ldb, const void* dC, int64_t lddc, void* dA,
+                      int64_t ldda, void* dB, int64_t lddb, int dtype, void* ws, size_t ws_bytes,
+                      void* stream);
 
 /* tsm2l_backward for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same

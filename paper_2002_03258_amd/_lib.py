@@ -53,6 +53,11 @@ def lib():
             L.tsm_grad_a.argtypes = mm
             L.tsm_grad_b.argtypes = [i64, i64, i64, vp, i64, vp, i64, vp, i64, i32, vp, sz, vp]
             L.tsm2x_split.argtypes = [i64, i64, vp, i64, vp, vp, i64, i32, vp]
+            L.tsm_grad_a_ex.argtypes = [i32] + mm
+            L.tsm_grad_a_ex.restype = i32
+            L.tsm2l_backward_ex.argtypes = [i32] + [i64, i64, i64, vp, i64, vp, i64, vp, i64, vp,
+                                                    i64, vp, i64, i32, vp, sz, vp]
+            L.tsm2l_backward_ex.restype = i32
             L.tsm2l_split.argtypes = [i32, i64, i64, i64, vp, i64, vp, i64, vp, i64, vp, vp, i64,
                                       i32, vp]
             L.tsm2l_split.restype = i32
@@ -107,7 +112,7 @@ def call(fn: str, *args) -> None:
 
 EXPORTS = ("tsm2r", "tsm2r_ex", "tsm2l", "tsm2l_ex", "tsm2x_gemm", "tsm_grad_a", "tsm_grad_b",
            "tsm2l_backward", "tsm2l_backward_noalloc", "tsm_kmeans_assign",
-           "tsm2x_split", "tsm2l_split",
+           "tsm2x_split", "tsm2l_split", "tsm_grad_a_ex", "tsm2l_backward_ex",
            "tsm2x_workspace_size", "tsm2x_kernel_name", "tsm2x_tsm2r_plan", "tsm2x_tsm2r_pin",
            "tsm2x_timing_start", "tsm2x_timing_stop", "tsm2x_timing_tag", "tsm2x_timing_collect",
            "tsm2x_timing_row", "tsm2x_probe_stream", "tsm2x_probe_tiles",

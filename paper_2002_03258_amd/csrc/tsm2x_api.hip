@@ -626,6 +626,42 @@ int tsm2l(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const voi
                    (hipStream_t)stream);
 }
 
+// tsm_grad_a on B(j, p) = B[j*bsj + p*bsp], arguments checked
+static int run_grad_a(int64_t m, int64_t k, int64_t n, const void* dC, int64_t lddc, const void* B,
+                      int64_t bsj, int64_t bsp, void* dA, int64_t ldda, int dtype, hipStream_t st) {
+    if (n > 32 || !plain_dtype(dtype)) return TSM_ERR_UNSUPPORTED;
+    if (m == 0 || k == 0) return TSM_SUCCESS;
+    if (n == 0) {
+        launch_fill_scale(m, k, dA, ldda, 0.0, dtype, st);
+        return check_launch("fill_scale_kernel");
+    }
+    // dA = dC * B^T: X = dC (m x n), Y(p, j) = B(j, p)
+    RTPlan P = plan_rowtile(m, n, k, dtype, cu_count());
+    LaunchRT L{};
+    L.m = m; L.kin = (int)n; L.nout = k; L.X = dC; L.ldx = lddc; L.Y = B; L.ys_in = bsp;
+    L.ys_out = bsj; L.O = dA; L.ldo = ldda; L.kp = P.kp; L.cols_per_block = (int)P.cpb;
+    L.blocks_x = P.bx; L.blocks_y = P.by; L.cus = cu_count();
+    if (launch_rowtile(L, dtype, st)) return TSM_ERR_UNSUPPORTED;
+    return check_launch("rowtile_kernel");
+}
+
+int tsm_grad_a_ex(int transB, int64_t m, int64_t k, int64_t n, const void* dC, int64_t lddc,
+                  const void* B, int64_t ldb, void* dA, int64_t ldda, int dtype, void* stream) {
+    if (transB != 0 && transB != 1) return -1;
+    if (m < 0) return -2;
+    if (k < 0) return -3;
+    if (n < 0) return -4;
+    if (!dC && m > 0 && n > 0) return -5;
+    if (lddc < (m > 1 ? m : 1)) return -6;
+    if (!B && k > 0 && n > 0) return -7;
+    if (ldb < ((transB ? n : k) > 1 ? (transB ? n : k) : 1)) return -8;
+    if (!dA && m > 0 && k > 0) return -9;
+    if (ldda < (m > 1 ? m : 1)) return -10;
+    if (!valid_dtype(dtype)) return -11;
+    return run_grad_a(m, k, n, dC, lddc, B, transB ? ldb : 1, transB ? 1 : ldb, dA, ldda, dtype,
+                      (hipStream_t)stream);
+}
+
 int tsm_grad_a(int64_t m, int64_t k, int64_t n, const void* dC, int64_t lddc, const void* B,
                int64_t ldb, void* dA, int64_t ldda, int dtype, void* stream) {
     if (m < 0) return -1;
@@ -638,21 +674,7 @@ int tsm_grad_a(int64_t m, int64_t k, int64_t n, const void* dC, int64_t lddc, co
     if (!dA && m > 0 && k > 0) return -8;
     if (ldda < (m > 1 ? m : 1)) return -9;
     if (!valid_dtype(dtype)) return -10;
-    if (n > 32 || !plain_dtype(dtype)) return TSM_ERR_UNSUPPORTED;
-    if (m == 0 || k == 0) return TSM_SUCCESS;
-    hipStream_t st = (hipStream_t)stream;
-    if (n == 0) {
-        launch_fill_scale(m, k, dA, ldda, 0.0, dtype, st);
-        return check_launch("fill_scale_kernel");
-    }
-    // dA = dC * B^T: X = dC (m x n), Y(p, j) = B[j + p*ldb].
-    RTPlan P = plan_rowtile(m, n, k, dtype, cu_count());
-    LaunchRT L{};
-    L.m = m; L.kin = (int)n; L.nout = k; L.X = dC; L.ldx = lddc; L.Y = B; L.ys_in = ldb;
-    L.ys_out = 1; L.O = dA; L.ldo = ldda; L.kp = P.kp; L.cols_per_block = (int)P.cpb;
-    L.blocks_x = P.bx; L.blocks_y = P.by; L.cus = cu_count();
-    if (launch_rowtile(L, dtype, st)) return TSM_ERR_UNSUPPORTED;
-    return check_launch("rowtile_kernel");
+    return run_grad_a(m, k, n, dC, lddc, B, 1, ldb, dA, ldda, dtype, (hipStream_t)stream);
 }
 
 int tsm_grad_b(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const void* dC,
@@ -709,7 +731,7 @@ namespace {
 
 // Argument checks of tsm2l_backward (positions 1..14).
 int check_bwd(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const void* B,
-              int64_t ldb, const void* dC, int64_t lddc, const void* dA, int64_t ldda,
+              int64_t ldb, int64_t minb, const void* dC, int64_t lddc, const void* dA, int64_t ldda,
               const void* dB, int64_t lddb, int dtype) {
     if (m < 0) return -1;
     if (k < 0) return -2;
@@ -717,7 +739,7 @@ int check_bwd(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const
     if (!A && m > 0 && k > 0) return -4;
     if (lda < (m > 1 ? m : 1)) return -5;
     if (!B && k > 0 && n > 0) return -6;
-    if (ldb < (k > 1 ? k : 1)) return -7;
+    if (ldb < (minb > 1 ? minb : 1)) return -7;
     if (!dC && m > 0 && n > 0) return -8;
     if (lddc < (m > 1 ? m : 1)) return -9;
     if (!dA && m > 0 && k > 0) return -10;
@@ -734,7 +756,7 @@ int check_bwd(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const
 // `need` bytes, or null with *rc set.
 template <typename PartFn>
 int run_bwd(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const void* B,
-            int64_t ldb, const void* dC, int64_t lddc, void* dA, int64_t ldda, void* dB,
+            int64_t bsj, int64_t bsp, const void* dC, int64_t lddc, void* dA, int64_t ldda, void* dB,
             int64_t lddb, int dtype, hipStream_t st, PartFn part) {
     if (k == 0) return TSM_SUCCESS;
     const int odt = plain_dtype(dtype) ? dtype : TSM_F32;      // B, dC, dA, dB
@@ -745,7 +767,7 @@ int run_bwd(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const v
         return check_launch("fill_scale_kernel");
     }
     LaunchBwd L{};
-    L.m = m; L.k = k; L.n = n; L.A = A; L.lda = lda; L.B = B; L.ldb = ldb; L.dC = dC;
+    L.m = m; L.k = k; L.n = n; L.A = A; L.lda = lda; L.B = B; L.bsj = bsj; L.bsp = bsp; L.dC = dC;
     L.lddc = lddc; L.dA = dA; L.ldda = ldda; L.dB = dB; L.lddb = lddb; L.cus = cu_count();
     int64_t blocks = 0;
     launch_tsm2l_bwd(L, dtype, &blocks, st, true);
@@ -796,9 +818,9 @@ extern "C" {
 int tsm2l_backward_noalloc(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
                            const void* B, int64_t ldb, const void* dC, int64_t lddc, void* dA,
                            int64_t ldda, void* dB, int64_t lddb, int dtype, void* stream) {
-    int rc = check_bwd(m, k, n, A, lda, B, ldb, dC, lddc, dA, ldda, dB, lddb, dtype);
+    int rc = check_bwd(m, k, n, A, lda, B, ldb, k, dC, lddc, dA, ldda, dB, lddb, dtype);
     if (rc) return rc;
-    return run_bwd(m, k, n, A, lda, B, ldb, dC, lddc, dA, ldda, dB, lddb, dtype,
+    return run_bwd(m, k, n, A, lda, B, 1, ldb, dC, lddc, dA, ldda, dB, lddb, dtype,
                    (hipStream_t)stream, [](size_t need, int* prc) -> void* {
                        if (need > kBwdScratchBytes) {
                            g_last_hip = "tsm2l_backward_noalloc: the dB partials need " +
@@ -811,12 +833,28 @@ int tsm2l_backward_noalloc(int64_t m, int64_t k, int64_t n, const void* A, int64
                    });
 }
 
+int tsm2l_backward_ex(int transB, int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
+                      const void* B, int64_t ldb, const void* dC, int64_t lddc, void* dA,
+                      int64_t ldda, void* dB, int64_t lddb, int dtype, void* ws, size_t ws_bytes,
+                      void* stream) {
+    if (transB != 0 && transB != 1) return -1;
+    const int rc = check_bwd(m, k, n, A, lda, B, ldb, transB ? n : k, dC, lddc, dA, ldda, dB, lddb,
+                             dtype);
+    if (rc) return rc < 0 ? rc - 1 : rc;
+    return run_bwd(m, k, n, A, lda, B, transB ? ldb : 1, transB ? 1 : ldb, dC, lddc, dA, ldda, dB,
+                   lddb, dtype, (hipStream_t)stream, [&](size_t need, int* prc) -> void* {
+                       void* w = nullptr;
+                       *prc = get_ws(need, ws, ws_bytes, &w);
+                       return w;
+                   });
+}
+
 int tsm2l_backward(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, const void* B,
                    int64_t ldb, const void* dC, int64_t lddc, void* dA, int64_t ldda, void* dB,
                    int64_t lddb, int dtype, void* ws, size_t ws_bytes, void* stream) {
-    int rc = check_bwd(m, k, n, A, lda, B, ldb, dC, lddc, dA, ldda, dB, lddb, dtype);
+    int rc = check_bwd(m, k, n, A, lda, B, ldb, k, dC, lddc, dA, ldda, dB, lddb, dtype);
     if (rc) return rc;
-    return run_bwd(m, k, n, A, lda, B, ldb, dC, lddc, dA, ldda, dB, lddb, dtype,
+    return run_bwd(m, k, n, A, lda, B, 1, ldb, dC, lddc, dA, ldda, dB, lddb, dtype,
                    (hipStream_t)stream, [&](size_t need, int* prc) -> void* {
                        void* w = nullptr;
                        *prc = get_ws(need, ws, ws_bytes, &w);

@@ -34,7 +34,7 @@ namespace tsm {
 template <typename T, int NTK, int NTN, int RG, bool LINE, bool PV, int AF, bool ASPLIT>
 __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
     int64_t m, int k, int n, const void* __restrict__ Av, const uint16_t* __restrict__ Alo,
-    int64_t lda, const T* __restrict__ B, int64_t ldb, const T* __restrict__ dC, int64_t lddc,
+    int64_t lda, const T* __restrict__ B, int64_t bsj, int64_t bsp, const T* __restrict__ dC, int64_t lddc,
     T* __restrict__ dA, int64_t ldda, double* __restrict__ part) {
     typedef Mfma<T> M;
     typedef typename M::acc Acc;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256) void tsm2l_bwd_kernel(
 #pragma unroll
         for (int t = 0; t < NTK; ++t) {
             const int j = 16 * t + rl, p = 4 * st + kk;
-            yv[st][t] = (j < k && p < n) ? B[j + (int64_t)p * ldb] : T(0);
+            yv[st][t] = (j < k && p < n) ? B[j * bsj + p * bsp] : T(0);
         }
 
     Acc accb[NTK][NTN];
@@ -293,7 +293,7 @@ static int bwd_launch(const LaunchBwd& L, int64_t* blocks_out, hipStream_t st, b
     dim3 g((unsigned)bx), b(256);
 #define TSM_B(LINE, PV)                                                                            \
     TSM_LAUNCH((tsm2l_bwd_kernel<T, NTK, NTN, RG, LINE, PV, AF, ASPLIT>), g, b, 0, st, L.m,        \
-               (int)L.k, (int)L.n, L.A, alo, L.lda, (const T*)L.B, L.ldb, (const T*)L.dC, L.lddc, \
+               (int)L.k, (int)L.n, L.A, alo, L.lda, (const T*)L.B, L.bsj, L.bsp, (const T*)L.dC, L.lddc, \
                (T*)L.dA, L.ldda, L.part)
     if (AF < 0 || pv) {
         if (line) TSM_B(true, true); else TSM_B(false, true);

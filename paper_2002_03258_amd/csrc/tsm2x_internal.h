@@ -153,7 +153,7 @@ int launch_tsm2l_split(const LaunchLS& L, int fmt, hipStream_t st);
 struct LaunchBwd {          // fused TSM2L backward: dA = dC*B^T, dB = A^T*dC
     int64_t m, k, n;
     const void* A; int64_t lda;
-    const void* B; int64_t ldb;
+    const void* B; int64_t bsj, bsp;      // B(j, p) = B[j*bsj + p*bsp]
     const void* dC; int64_t lddc;
     void* dA; int64_t ldda;
     void* dB; int64_t lddb;

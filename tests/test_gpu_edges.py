@@ -249,3 +249,22 @@ def test_split_and_product_in_one_pass(dev, fmt, lo, m, k, n):
             mode = fmt + ("_split" if lo else "")
             C = tsm.matmul(a, b, mode=mode, kind="L")
             assert C.view(torch.int32).equal(want.view(torch.int32))
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(1, 1, 1), (130, 7, 3), (4099, 16, 16), (1000, 32, 31),
+                                   (513, 1000, 8), (2000, 33, 32)])
+def test_gradients_rowmajor_b(dev, dtype, m, k, n):
+    """A row-major B (padded rows too) gives the bits of its column-major copy."""
+    seed = 3800 + m + k + n
+    A = dev_matrix(seed, si.STREAM_A, m, k, dtype, dev)
+    B = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev)
+    dC = dev_matrix(seed, si.STREAM_DC, m, n, dtype, dev, dist="normal")
+    rows = torch.full((k, n + 3), float("nan"), dtype=dtype, device=dev)
+    Bp = rows[:, 2:2 + n]
+    Bp.copy_(B)
+    for b in (B.contiguous(), Bp):
+        assert torch.equal(tsm.grad_a(dC, b), tsm.grad_a(dC, B))
+        if k <= 32:
+            for got, want in zip(tsm.tsm2l_backward(A, b, dC), tsm.tsm2l_backward(A, B, dC)):
+                assert torch.equal(got, want)
