@@ -240,13 +240,22 @@ __global__ __launch_bounds__(WAVE * WK) void tsm2r_lp_kernel(
     const int64_t tile = blockIdx.x;
     const int s = blockIdx.y, nsl = gridDim.y;
     const int64_t row0 = tile * TRW + (RS ? w * TR : 0);
-    const int64_t r = row0 + 8 * rl;     // this lane's 8 rows
     const bool full = (row0 + TR <= m);
+    // Columns at least m rounded up to 8 apart: the last tile's 16-byte runs
+    // may end in a column's padding, the very last column's excepted (nothing
+    // need follow it); runs beyond m read the last one.  Their rows are not
+    // stored.  (One wavefront reading its tile element by element held up the
+    // whole product: bfloat16 30878 x 32640, n = 2: 1717 us, 355 so.)
+    const bool pad = VEC && (full || lda >= (m + 7) / 8 * 8);
+    const int64_t rlast = (m - 1) / 8 * 8;
+    const int64_t r = !full && pad && row0 + 8 * rl > rlast ? rlast : row0 + 8 * rl;   // this lane's 8 rows
     const int64_t kb0 = (int64_t)s * kslice;
     const int64_t kb1 = (kb0 + kslice < k) ? kb0 + kslice : k;
     const int64_t lw = RS ? kslice : kslice / WK;
     const int64_t wk0 = kb0 + (RS ? 0 : w * lw);
     const int64_t wk1 = (wk0 + lw < kb1) ? wk0 + lw : kb1;
+
+    const int64_t wpad = wk1 < k ? wk1 : k - 1;     // columns whose padding may be read
 
     f32x4 acc[8][NT16];
 #pragma unroll
@@ -272,7 +281,7 @@ __global__ __launch_bounds__(WAVE * WK) void tsm2r_lp_kernel(
         }
     };
     auto loadA = [&](int64_t j0, uint32_t (&raw)[NPL][8][4]) {
-        if (VEC && full && j0 + 32 <= wk1) {
+        if (pad && j0 + 32 <= (full ? wk1 : wpad)) {
             loadA_full(j0, raw);
             return;
         }
@@ -283,7 +292,7 @@ __global__ __launch_bounds__(WAVE * WK) void tsm2r_lp_kernel(
             for (int pl = 0; pl < NPL; ++pl) {
                 const uint16_t* P = pl == 0 ? Ah : Al;
                 if (j < wk1)
-                    load8h<VEC>(P + r + j * lda, m - r, full, raw[pl][i]);
+                    load8h<VEC>(P + r + j * lda, m - r, full || (pad && j < wpad), raw[pl][i]);
                 else
 #pragma unroll
                     for (int d = 0; d < 4; ++d) raw[pl][i][d] = 0u;
@@ -336,7 +345,8 @@ __global__ __launch_bounds__(WAVE * WK) void tsm2r_lp_kernel(
     // chunk's loads below the waits and it gained nothing.
     if (wk1 > wk0 && row0 < m) {
         int64_t j1 = wk0;        // columns from here on one chunk at a time
-        if (PF && VEC && full && wk1 - wk0 >= 32 * U) {
+        const int64_t wlim = full ? wk1 : wpad;      // columns read in whole runs
+        if (PF && pad && wlim - wk0 >= 32 * U) {
             // whole steps: the next step in flight while this one is
             // multiplied, in straight-line code (no bounds branches, so the
             // waits for this step's operands leave the next step's loads
@@ -355,7 +365,7 @@ __global__ __launch_bounds__(WAVE * WK) void tsm2r_lp_kernel(
 #pragma unroll
                 for (int u = 0; u < U; ++u) chunk(r[u], b[u]);
             };
-            const int ns = (int)((wk1 - wk0) / (32 * U));
+            const int ns = (int)((wlim - wk0) / (32 * U));
             load_step(wk0, ra, ba);
             int g = 0;
             // (the scheduling barriers keep the next step's loads ahead of
@@ -1189,6 +1199,15 @@ int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec,
     if (S > s_len) S = s_len;
     if (S > s_cost) S = s_cost;
     if (S < 1) S = 1;
+    if (var >= 2 && 8 * P->tiles * S < 7 * (int64_t)cus) {
+        // CUs left idle by those caps: on to two steps per wavefront and as
+        // many bytes of partials, written and read, as A has (bfloat16 3779 x
+        // 3905, n = 11: 43 us with 32 workgroups, 24 with 248)
+        int64_t s2 = cus / P->tiles;
+        if (s2 > k / 128) s2 = k / 128;
+        if (s2 > k * (split ? 4 : 2) / (n * 16)) s2 = k * (split ? 4 : 2) / (n * 16);
+        if (s2 > S) S = s2;
+    }
     const char* fs = std::getenv("TSM2X_LP_S");
     if (fs && *fs && std::strtoll(fs, nullptr, 10) > 0) S = std::strtoll(fs, nullptr, 10);
     const int64_t gran = rs ? 32 : (int64_t)WK * 32;
