@@ -136,8 +136,11 @@ RTPlan plan_rowtile(int64_t m, int64_t kin, int64_t nout, int dt, int cus) {
         P.cpb = nout;
         P.by = 1;
     } else {
-        // enough column ranges to fill the machine, each a multiple of 32
-        int64_t by = cdiv(cap, wblocks);
+        // as many column ranges, each a multiple of 32, as fit the cap with
+        // every wavefront on the same number of row tiles (a range more, and
+        // some took two: FP32 dA 20096 x 20011, n = 8: 441 us,
+        // 309 so; 20011 x 20011: 973 and 470)
+        int64_t by = cap / wblocks;
         if (by < 1) by = 1;
         int64_t cpb = cdiv(nout, by);
         cpb = cdiv(cpb, 32) * 32;
@@ -148,7 +151,7 @@ RTPlan plan_rowtile(int64_t m, int64_t kin, int64_t nout, int dt, int cus) {
     int64_t bx = wblocks;
     int64_t lim = cap / P.by;
     if (lim < 1) lim = 1;
-    if (bx > lim) bx = lim;
+    if (bx > lim) bx = nout > 32 ? cdiv(wblocks, cdiv(wblocks, lim)) : lim;
     if (bx < 1) bx = 1;
     P.bx = bx;
     return P;
@@ -325,6 +328,26 @@ int get_ws(size_t need, void* user, size_t user_bytes, void** out) {
     return TSM_SUCCESS;
 }
 
+// The library's buffer would have to grow while the stream is being captured,
+// where nothing can be allocated: the plain products then run unsplit.
+bool cold_capture(size_t need, const void* user, hipStream_t st) {
+    if (need == 0 || user) return false;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        DevState* d = dev_state(nullptr);
+        if (!d || d->ws_bytes >= need) return false;
+    }
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &s) == hipSuccess && s == hipStreamCaptureStatusActive;
+}
+
+// A tn plan with one slice and no workspace.
+void unsplit(int64_t R, TNPlan* P) {
+    P->S = 1;
+    P->rslice = cdiv(R, 1024) * 1024;     // a whole number of any instance's steps
+    P->ws = 0;
+}
+
 // Validation of (m, k, n, A, lda, B, ldb, C, ldc, dtype) for C = A*B with
 // column-major (or, for `rowA`, row-major) A.  `base` is the position of m.
 int check_mm(int base, int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
@@ -497,7 +520,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         // and they run if it is too small for this kernel's partials
         const size_t need = tt_ws(k, (int)m, (int)n, cus);
         const size_t nn = tsm2r_ws(transA, m, k, n, dtype, transB, true);
-        if (!ws || ws_bytes >= (nn > need ? nn : need)) {
+        if (ws ? ws_bytes >= (nn > need ? nn : need) : !cold_capture(need, ws, st)) {
             void* w = nullptr;
             const int rc = get_ws(ws && nn > need ? nn : need, ws, ws_bytes, &w);
             if (rc) return rc;
@@ -512,8 +535,13 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     // TSM2R kernels; workspace = [split partials][B copied column-major, or
     // B's packed 16-bit terms for the precision form]
     const bool avec = aligned(A, lda, dtype);
+    const bool direct = plain_dtype(dtype) && transB && (!transA || (n <= 16 && m * k <= (int64_t)1 << 20));
     void* w = nullptr;
-    int rc = get_ws(tsm2r_ws(transA, m, k, n, dtype, transB, avec), ws, ws_bytes, &w);
+    int rc = TSM_SUCCESS;
+    const size_t need = ws ? tsm2r_ws(transA, m, k, n, dtype, transB, avec)
+                           : tsm2r_ws(transA, m, k, n, dtype, transB && !direct, avec);
+    const bool cold = plain_dtype(dtype) && (!transB || direct) && cold_capture(need, ws, st);
+    if (!cold) rc = get_ws(need, ws, ws_bytes, &w);
     if (rc) return rc;
     if (!plain_dtype(dtype)) {
         // A: 16-bit hi plane (and lo plane lda*k elements after it); B, C float
@@ -539,7 +567,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     // copy and its launch (1024^2, n = 4: FP64 13.1 us with the copy, 9.9
     // without, FP32 13.4 and 11.0), and copies B beyond (FP32 2048^2, n = 16: 12.8 and
     // 18.6; 1024^2, n = 30: 13.4 and 20.4).
-    const bool copy = transB && transA && (n > 16 || m * k > (int64_t)1 << 20);
+    const bool copy = transB && !direct;
     if (copy) {
         void* bc = (char*)w + align256(tsm2r_part(transA, m, k, n, dtype, avec));
         launch_transpose(k, n, B, ldb, bc, bt_ld(k, ce), cdt, st);
@@ -552,6 +580,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         // A given transposed is the column-major k x m matrix X = A^T (ld lda):
         // C = X^T * B, a reduction along the contiguous dimension.
         TNPlan P = plan_tn(k, m, n, dtype, cus);
+        if (cold) unsplit(k, &P);
         LaunchTN L{};
         L.R = k; L.ncols = m; L.n = n;
         L.X = A; L.ldx = lda; L.Y = Bk; L.ldy = ldbk; L.O = C; L.ldo = ldc;
@@ -564,7 +593,10 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         return check_launch("tn_kernel");
     }
     NNPlan P{};
-    if (plan_nn(m, k, n, dtype, cus, avec, &P)) return TSM_ERR_UNSUPPORTED;
+    const NNPin one{1, -1};
+    if (cold ? plan_tsm2r(m, k, n, dtype, cus, avec, &P, &one)
+             : plan_nn(m, k, n, dtype, cus, avec, &P))
+        return TSM_ERR_UNSUPPORTED;
     LaunchNN L{};
     L.fn = transB ? P.fn_bt : P.fn;
     L.m = m; L.k = k; L.n = n; L.A = A; L.lda = lda; L.B = Bk; L.ldb = ldbk; L.C = C; L.ldc = ldc;
@@ -699,6 +731,7 @@ int tsm_grad_b(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, cons
     }
     // dB = A^T * dC: X = A (R = m rows, k columns), Y = dC.
     TNPlan P = plan_tn(m, k, n, dtype, cu_count());
+    if (plain_dtype(dtype) && cold_capture(P.ws, ws, st)) unsplit(m, &P);
     void* w = nullptr;
     int rc = get_ws(P.ws, ws, ws_bytes, &w);
     if (rc) return rc;

@@ -437,6 +437,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
                 P->S = (int)s;
                 P->kslice = ks;
             }
+            if (pin && pin->S == 1) break;
         }
         P->np = np;
         P->fn = I.fn;

@@ -268,3 +268,33 @@ def test_gradients_rowmajor_b(dev, dtype, m, k, n):
         if k <= 32:
             for got, want in zip(tsm.tsm2l_backward(A, b, dC), tsm.tsm2l_backward(A, B, dC)):
                 assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_products_captured_before_any_workspace(dev, dtype):
+    """Captured before the library owns a workspace, where none can be
+    allocated, the plain products run unsplit; every replay equals the eager
+    result within rounding."""
+    from paper_2002_03258_amd import _lib
+    shapes = [(3001, 3001, 20, False), (1024, 1000, 4, True), (1000, 2000, 50, False),
+              (16, 5000, 16, False)]
+    ins = []
+    for i, (m, k, n, row) in enumerate(shapes):
+        A = dev_matrix(3900 + i, si.STREAM_A, m, k, dtype, dev)
+        A = A.contiguous() if row else A
+        ins.append((A, dev_matrix(3900 + i, si.STREAM_B, k, n, dtype, dev).contiguous()))
+    outs = [tsm.empty_colmajor(a.shape[0], b.shape[1], dtype, dev) for a, b in ins]
+    torch.cuda.synchronize()
+    _lib.lib().tsm2x_finalize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for (a, b), o in zip(ins, outs):
+            tsm.tsm2r(a, b, out=o)
+    for _ in range(3):
+        for o in outs:
+            o.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for (a, b), o in zip(ins, outs):
+            want = tsm.tsm2r(a, b)
+            assert err(to_np(o), to_np(want)) <= TOL[dtype]
