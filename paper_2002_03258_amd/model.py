@@ -89,7 +89,8 @@ def chunks_in_flight(n: int, es: int, tall: int, workgroups: int, cus: int) -> i
     """Chunks of A a wavefront of the library's TSM2R kernel keeps in flight:
     two where the library holds the next chunk in flight (the shorter tiles
     only; n > 16, FP32 with n <= 4, or a grid of 7/8 to all of the CUs), one
-    otherwise."""
+    otherwise.  (The library holds two on smaller grids as well; the constants
+    were fitted to plans counted as one there.)"""
     if tall:
         return 1
     if n > 16 or (es == 4 and n <= 4):
