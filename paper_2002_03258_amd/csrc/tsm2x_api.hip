@@ -295,12 +295,17 @@ void plan_tn_plain(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan*
     P->ws = P->S > 1 ? (size_t)P->groups * P->S * 256 * (wide ? 2 : 1) * 8 : 0;
 }
 
+// A caller's workspace takes `need` bytes.
+bool holds(const void* ws, size_t ws_bytes, size_t need) {
+    return need == 0 || (ws_bytes >= need && ((uintptr_t)ws & 255u) == 0);
+}
+
 // Workspace: caller's (checked) or the library's grow-only per-device buffer.
 int get_ws(size_t need, void* user, size_t user_bytes, void** out) {
     *out = nullptr;
     if (need == 0) return TSM_SUCCESS;
     if (user) {
-        if (user_bytes < need || ((uintptr_t)user & 255u)) return TSM_ERR_WORKSPACE;
+        if (!holds(user, user_bytes, need)) return TSM_ERR_WORKSPACE;
         *out = user;
         return TSM_SUCCESS;
     }
@@ -456,6 +461,21 @@ int64_t panel_width(bool lform, int transA, int transB, int64_t m, int64_t k, in
     return 64;
 }
 
+// Bytes a caller's workspace must have for a product of n columns in panels
+// of panel_width.
+size_t caller_ws(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
+                 const void* A, int64_t lda, int dtype, const void* ws, size_t ws_bytes) {
+    if (lform && !transA && k <= 32) return 0;
+    const bool al = (transA && k <= 32) || aligned(A, lda, dtype);
+    const int64_t panel = panel_width(lform, transA, transB, m, k, n, A, lda, dtype, ws, ws_bytes);
+    size_t most = 0;
+    for (const int64_t w : {n < panel ? n : panel, n > panel ? n % panel : (int64_t)0}) {
+        const size_t b = w > 0 ? tsm2r_ws(transA, m, k, w, dtype, transB, al) : 0;
+        if (b > most) most = b;
+    }
+    return most;
+}
+
 // C := beta*C + op(A)*op(B) on validated arguments.  `lform` asks for the TSM2L
 // kernels (all of B on chip) for a column-major A with k <= 32; other shapes
 // run on the TSM2R kernels, which are correct for any k.  A row-major A with
@@ -479,6 +499,11 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     }
     const int64_t panel = panel_width(lform, transA, transB, m, k, n, A, lda, dtype, ws, ws_bytes);
     if (n > panel) {
+        // no panel runs if the caller's workspace is too small for any of them
+        for (const int64_t w : {panel, n % panel})
+            if (ws && w > 0 &&
+                !holds(ws, ws_bytes, caller_ws(lform, transA, transB, m, k, w, A, lda, dtype, ws, ws_bytes)))
+                return TSM_ERR_WORKSPACE;
         for (int64_t p0 = 0; p0 < n; p0 += panel) {
             const int64_t np = n - p0 < panel ? n - p0 : panel;
             const char* Bp = (const char*)B + (transB ? p0 : p0 * ldb) * ce;
@@ -974,23 +999,24 @@ size_t tsm2x_workspace_size(int op, int64_t m, int64_t k, int64_t n, int dtype) 
     if (op == TSM_OP_KMEANS)
         return (m >= 0 && k >= 1 && n >= 1 && plain_dtype(dtype)) ? align256((size_t)n * esize(dtype)) : 0;
     if (m <= 0 || k <= 0 || n <= 0 || !valid_dtype(dtype)) return 0;
-    const int64_t np = n < 32 ? n : 32;      // panels of 32 columns reuse one workspace
-    // products: enough for a B given transposed as well, and for panels of 64
-    // columns and the narrower last one
-    auto nn = [&]() {
-        size_t w = tsm2r_ws_max(0, m, k, np, dtype, true);
-        if (n > 32 && plain_dtype(dtype) && m > 32) {
-            for (const int64_t p : {n < 64 ? n : (int64_t)64, n > 64 ? n % 64 : (int64_t)0}) {
-                const size_t a = p > 0 ? tsm2r_ws_max(0, m, k, p, dtype, true) : 0;
-                if (a > w) w = a;
-            }
+    // products: enough for a B given transposed as well, and for a panel of any
+    // width the call may run in (the panels reuse one workspace): a narrower
+    // last panel can need more than the others, its split being finer
+    auto most = [&](int transA) {
+        const bool wide = n > 32 && !transA && plain_dtype(dtype) && m > 32;
+        size_t w = 0;
+        for (const int64_t p : {n < 32 ? n : (int64_t)32, n > 32 ? n % 32 : (int64_t)0,
+                                !wide ? (int64_t)0 : n < 64 ? n : (int64_t)64,
+                                wide && n > 64 ? n % 64 : (int64_t)0}) {
+            const size_t b = p > 0 ? tsm2r_ws_max(transA, m, k, p, dtype, true) : 0;
+            if (b > w) w = b;
         }
         return w;
     };
     switch (op) {
-        case TSM_OP_TSM2R: return nn();
-        case TSM_OP_TSM2R_ROWMAJOR: return plain_dtype(dtype) ? tsm2r_ws_max(1, m, k, np, dtype, true) : 0;
-        case TSM_OP_TSM2L: return k <= 32 ? 0 : nn();
+        case TSM_OP_TSM2R: return most(0);
+        case TSM_OP_TSM2R_ROWMAJOR: return plain_dtype(dtype) ? most(1) : 0;
+        case TSM_OP_TSM2L: return k <= 32 ? 0 : most(0);
         case TSM_OP_GRAD_B: return n <= 32 ? plan_tn(m, k, n, dtype, cu_count()).ws : 0;
         default: return 0;
     }
