@@ -40,7 +40,9 @@
  *  partial sums to a workspace of tsm2x_workspace_size() bytes and add them
  *  in a second, ordered pass.  tsm2r_ex and tsm_grad_b take the workspace
  *  from the caller when ws != NULL: device memory, 256-byte aligned, any
- *  contents.  Otherwise the library uses a grow-only per-device buffer it
+ *  contents.  (A smaller one is refused only if it does not hold the partials
+ *  of the coarsest split the shape is given either.)
+ *  Otherwise the library uses a grow-only per-device buffer it
  *  owns (allocated with hipMalloc on first need, released by
  *  tsm2x_finalize).  Two calls that share one workspace must not run
  *  concurrently (e.g. on two streams).

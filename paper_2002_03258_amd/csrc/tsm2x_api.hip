@@ -101,9 +101,10 @@ NNPin pin_of(int64_t m, int64_t k, int64_t n, int dtype) {
     return it == g_pins.end() ? NNPin{0, -1} : it->second;
 }
 
-int plan_nn(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P) {
+int plan_nn(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P,
+            bool fine = true) {
     const NNPin pin = pin_of(m, k, n, dtype);
-    return plan_tsm2r(m, k, n, dtype, cus, line, P, &pin);
+    return plan_tsm2r(m, k, n, dtype, cus, line, P, &pin, fine);
 }
 
 struct RTPlan {
@@ -190,10 +191,25 @@ double grid_time(int64_t W, int cus) {
 // 14; 3001^2: 43 and 13; FP64 20011^2, n = 16: 868 and 643.)
 void plan_tn_plain(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan* P);
 
-TNPlan plan_tn(int64_t R, int64_t ncols, int64_t n, int dt, int cus) {
+// Plain types with `fine` false, for a caller's workspace that does not hold
+// those partials: at least eight steps per wavefront, two workgroups per CU.
+void plan_tn_coarse(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan* P) {
+    P->pf = (int)env_int("TSM2X_TN_PF", 1);
+    P->ct = ncols > 16 ? 2 : 1;
+    P->groups = cdiv(cdiv(ncols, 16), P->ct) * P->ct;
+    const int64_t RB = 16 * (16 / esize(dt)) * (P->ct == 2 ? 1 : 2);
+    int64_t S = cdiv(2 * (int64_t)cus, P->groups / P->ct);
+    if (S > R / (RB * 4 * 8)) S = R / (RB * 4 * 8);
+    if (S < 1) S = 1;
+    P->rslice = cdiv(cdiv(R, S), RB * 4) * (RB * 4);
+    P->S = (int)cdiv(R, P->rslice);
+    P->ws = P->S > 1 ? (size_t)P->groups * P->S * 256 * (n > 16 ? 2 : 1) * 8 : 0;
+}
+
+TNPlan plan_tn(int64_t R, int64_t ncols, int64_t n, int dt, int cus, bool fine = true) {
     TNPlan P{};
     if (plain_dtype(dt)) {
-        plan_tn_plain(R, ncols, n, dt, cus, &P);
+        fine ? plan_tn_plain(R, ncols, n, dt, cus, &P) : plan_tn_coarse(R, ncols, n, dt, cus, &P);
         return P;
     }
     // 16-bit forms.  Output tiles per workgroup: two share each Y tile when
@@ -398,24 +414,26 @@ int check_ex(int transA, int transB, int64_t m, int64_t k, int64_t n, const void
 int64_t bt_ld(int64_t k, int ce) { return cdiv(k, 16 / ce) * (16 / ce); }
 
 // Bytes of split partials of a TSM2R-kernel product of at most 32 columns,
-// for the kernel instance the call launches (`vec`: A is aligned()).
-size_t tsm2r_part(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool vec) {
+// for the kernel instance the call launches (`vec`: A is aligned()); `fine` as
+// in the planners.
+size_t tsm2r_part(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool vec, bool fine) {
     const int cus = cu_count();
     if (!plain_dtype(dtype)) {
         NNPlan P{};
-        plan_tsm2r_lp(m, k, n, dtype, cus, vec, &P);
+        plan_tsm2r_lp(m, k, n, dtype, cus, vec, &P, fine);
         return P.ws;
     }
-    if (transA) return plan_tn(k, m, n, dtype, cus).ws;
+    if (transA) return plan_tn(k, m, n, dtype, cus, fine).ws;
     NNPlan P{};
-    return plan_nn(m, k, n, dtype, cus, vec, &P) ? 0 : P.ws;
+    return plan_nn(m, k, n, dtype, cus, vec, &P, fine) ? 0 : P.ws;
 }
 
 // Workspace of a TSM2R-kernel product of at most 32 columns: the split
 // partials, then room for B when it is given transposed (plain types) or for
 // B's packed 16-bit terms (precision form, B read in either order).
-size_t tsm2r_ws(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool transB, bool vec) {
-    const size_t part = align256(tsm2r_part(transA, m, k, n, dtype, vec));
+size_t tsm2r_ws(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool transB, bool vec,
+                bool fine = true) {
+    const size_t part = align256(tsm2r_part(transA, m, k, n, dtype, vec, fine));
     if (!plain_dtype(dtype)) return part + lp_bterms_bytes(k, n);
     const int ce = esize(dtype);
     return part + (transB ? (size_t)bt_ld(k, ce) * n * ce : 0);
@@ -456,13 +474,14 @@ int64_t panel_width(bool lform, int transA, int transB, int64_t m, int64_t k, in
         return p.S > 0 || p.tall >= 0;
     };
     if (pinned(32) || (n % 32 && pinned(n % 32))) return 32;
-    if (ws && ws_bytes < tsm2r_ws(0, m, k, n < 64 ? n : 64, dtype, transB, aligned(A, lda, dtype)))
+    if (ws && !holds(ws, ws_bytes, tsm2r_ws(0, m, k, n < 64 ? n : 64, dtype, transB,
+                                            aligned(A, lda, dtype))))
         return 32;
     return 64;
 }
 
 // Bytes a caller's workspace must have for a product of n columns in panels
-// of panel_width.
+// of panel_width: those of the finer or the coarser split, whichever is less.
 size_t caller_ws(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
                  const void* A, int64_t lda, int dtype, const void* ws, size_t ws_bytes) {
     if (lform && !transA && k <= 32) return 0;
@@ -470,7 +489,10 @@ size_t caller_ws(bool lform, int transA, int transB, int64_t m, int64_t k, int64
     const int64_t panel = panel_width(lform, transA, transB, m, k, n, A, lda, dtype, ws, ws_bytes);
     size_t most = 0;
     for (const int64_t w : {n < panel ? n : panel, n > panel ? n % panel : (int64_t)0}) {
-        const size_t b = w > 0 ? tsm2r_ws(transA, m, k, w, dtype, transB, al) : 0;
+        if (w == 0) continue;
+        const size_t fine = tsm2r_ws(transA, m, k, w, dtype, transB, al);
+        const size_t coarse = tsm2r_ws(transA, m, k, w, dtype, transB, al, false);
+        const size_t b = fine < coarse ? fine : coarse;
         if (b > most) most = b;
     }
     return most;
@@ -545,7 +567,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         // and they run if it is too small for this kernel's partials
         const size_t need = tt_ws(k, (int)m, (int)n, cus);
         const size_t nn = tsm2r_ws(transA, m, k, n, dtype, transB, true);
-        if (ws ? ws_bytes >= (nn > need ? nn : need) : !cold_capture(need, ws, st)) {
+        if (ws ? holds(ws, ws_bytes, nn > need ? nn : need) : !cold_capture(need, ws, st)) {
             void* w = nullptr;
             const int rc = get_ws(ws && nn > need ? nn : need, ws, ws_bytes, &w);
             if (rc) return rc;
@@ -563,15 +585,17 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     const bool direct = plain_dtype(dtype) && transB && (!transA || (n <= 16 && m * k <= (int64_t)1 << 20));
     void* w = nullptr;
     int rc = TSM_SUCCESS;
-    const size_t need = ws ? tsm2r_ws(transA, m, k, n, dtype, transB, avec)
-                           : tsm2r_ws(transA, m, k, n, dtype, transB && !direct, avec);
+    size_t need = ws ? tsm2r_ws(transA, m, k, n, dtype, transB, avec)
+                     : tsm2r_ws(transA, m, k, n, dtype, transB && !direct, avec);
+    const bool fine = !ws || holds(ws, ws_bytes, need);
+    if (!fine) need = tsm2r_ws(transA, m, k, n, dtype, transB, avec, false);
     const bool cold = plain_dtype(dtype) && (!transB || direct) && cold_capture(need, ws, st);
     if (!cold) rc = get_ws(need, ws, ws_bytes, &w);
     if (rc) return rc;
     if (!plain_dtype(dtype)) {
         // A: 16-bit hi plane (and lo plane lda*k elements after it); B, C float
         NNPlan P{};
-        plan_tsm2r_lp(m, k, n, dtype, cus, avec, &P);
+        plan_tsm2r_lp(m, k, n, dtype, cus, avec, &P, fine);
         void* bt = (char*)w + align256(P.ws);
         launch_split_b(k, n, (const float*)B, transB ? ldb : 1, transB ? 1 : ldb, dtype, bt, st);
         rc = check_launch("split_b_kernel");
@@ -594,7 +618,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     // 18.6; 1024^2, n = 30: 13.4 and 20.4).
     const bool copy = transB && !direct;
     if (copy) {
-        void* bc = (char*)w + align256(tsm2r_part(transA, m, k, n, dtype, avec));
+        void* bc = (char*)w + align256(tsm2r_part(transA, m, k, n, dtype, avec, fine));
         launch_transpose(k, n, B, ldb, bc, bt_ld(k, ce), cdt, st);
         rc = check_launch("transpose_kernel");
         if (rc) return rc;
@@ -604,7 +628,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     if (transA) {
         // A given transposed is the column-major k x m matrix X = A^T (ld lda):
         // C = X^T * B, a reduction along the contiguous dimension.
-        TNPlan P = plan_tn(k, m, n, dtype, cus);
+        TNPlan P = plan_tn(k, m, n, dtype, cus, fine);
         if (cold) unsplit(k, &P);
         LaunchTN L{};
         L.R = k; L.ncols = m; L.n = n;
@@ -620,7 +644,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     NNPlan P{};
     const NNPin one{1, -1};
     if (cold ? plan_tsm2r(m, k, n, dtype, cus, avec, &P, &one)
-             : plan_nn(m, k, n, dtype, cus, avec, &P))
+             : plan_nn(m, k, n, dtype, cus, avec, &P, fine))
         return TSM_ERR_UNSUPPORTED;
     LaunchNN L{};
     L.fn = transB ? P.fn_bt : P.fn;
@@ -756,6 +780,7 @@ int tsm_grad_b(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, cons
     }
     // dB = A^T * dC: X = A (R = m rows, k columns), Y = dC.
     TNPlan P = plan_tn(m, k, n, dtype, cu_count());
+    if (ws && !holds(ws, ws_bytes, P.ws)) P = plan_tn(m, k, n, dtype, cu_count(), false);
     if (plain_dtype(dtype) && cold_capture(P.ws, ws, st)) unsplit(m, &P);
     void* w = nullptr;
     int rc = get_ws(P.ws, ws, ws_bytes, &w);

@@ -59,10 +59,11 @@ struct NNPin {
 
 // Plan of tsm2r for (m, k, n, dtype) on a device with `cus` compute units;
 // `line`: every column of A starts on a 128-byte line;
-// `pin` (may be null) overrides the planner's choices.
+// `pin` (may be null) overrides the planner's choices; `fine` false: the split
+// does not go on to fill idle CUs (a caller's workspace may be too small for it).
 // Returns nonzero if no kernel instance covers the request.
 int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P,
-               const NNPin* pin);
+               const NNPin* pin, bool fine = true);
 
 struct LaunchNN {           // tsm2r_nn: C = A*B, column-major A
     const void* fn;
@@ -125,7 +126,8 @@ int launch_tt(const LaunchTT& L, int dtype, hipStream_t st);
 
 // Low-precision storage forms of A (bf16 / f16, single or split planes);
 // `vec`: the planes are 16-byte aligned with a 16-byte multiple leading dimension.
-int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P);
+int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P,
+                  bool fine = true);
 // L.B: the packed terms of B written by launch_split_b (L.ldb unused)
 int launch_tsm2r_lp(const LaunchNN& L, int dtype, hipStream_t st);
 // B (k x n <= 32, B(j, p) = B[j*bsj + p*bsp]) split into three 16-bit terms

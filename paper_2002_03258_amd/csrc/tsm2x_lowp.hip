@@ -1159,7 +1159,8 @@ static const void* lp_pick(int fmt, bool split, int nt16, int var, int* occ) {
 
 static inline int64_t cdiv_lp(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P) {
+int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec, NNPlan* P,
+                  bool fine) {
     const int fmt = (dtype == DT_BF16 || dtype == DT_BF16_SPLIT) ? FMT_BF16 : FMT_F16;
     const bool split = dtype == DT_BF16_SPLIT || dtype == DT_F16_SPLIT;
     const int nt16 = n <= 16 ? 1 : 2;
@@ -1199,7 +1200,7 @@ int plan_tsm2r_lp(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool vec,
     if (S > s_len) S = s_len;
     if (S > s_cost) S = s_cost;
     if (S < 1) S = 1;
-    if (var >= 2 && 8 * P->tiles * S < 7 * (int64_t)cus) {
+    if (fine && var >= 2 && 8 * P->tiles * S < 7 * (int64_t)cus) {
         // CUs left idle by those caps: on to two steps per wavefront and as
         // many bytes of partials, written and read, as A has (bfloat16 3779 x
         // 3905, n = 11: 43 us with 32 workgroups, 24 with 248)

@@ -401,7 +401,7 @@ static int nn_pf(int64_t n, int dtype, int tall, int64_t W, int cus) {
 }
 
 int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, NNPlan* P,
-               const NNPin* pin) {
+               const NNPin* pin, bool fine) {
     // partial sums are stored at the kernel's padded width (16, 32, 48 or 64)
     const int np = (int)((n + 15) / 16) * 16;
     const int es = dtype == DT_F64 ? 8 : 4;
@@ -516,7 +516,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
             int64_t ks = slice(split(false)), W = tiles * cdiv64(k, ks);
             bool take = W <= cus && 8 * W >= 7 * (int64_t)cus;
             const int64_t have = P->tiles * P->S;
-            if (!take && 8 * have < 7 * (int64_t)cus) {
+            if (fine && !take && 8 * have < 7 * (int64_t)cus) {
                 // the plan so far leaves CUs idle
                 ks = slice(split(true));
                 W = tiles * cdiv64(k, ks);
