@@ -42,10 +42,15 @@
  *  from the caller when ws != NULL: device memory, 256-byte aligned, any
  *  contents.  (A smaller one is refused only if it does not hold the partials
  *  of the coarsest split the shape is given either.)
- *  Otherwise the library uses a grow-only per-device buffer it
- *  owns (allocated with hipMalloc on first need, released by
- *  tsm2x_finalize).  Two calls that share one workspace must not run
- *  concurrently (e.g. on two streams).
+ *  Two calls that share one workspace must not run concurrently (e.g. on two
+ *  streams).  Otherwise the library uses a grow-only buffer of its own for
+ *  each device and stream (hipMalloc on first need, also while the stream is
+ *  being captured; at most 64 streams' buffers at a time beyond those that
+ *  captured calls were given): calls on different streams, and calls of
+ *  several threads on one stream, are independent.  A captured call's buffer
+ *  stays valid until tsm2x_finalize, which releases all of them; graphs
+ *  captured from one stream share its buffer, so pass a workspace to calls
+ *  of graphs that are to run at the same time.
  */
 #ifndef TSM2X_H
 #define TSM2X_H

@@ -5,6 +5,11 @@ current stream; the products themselves run in the library's HIP kernels.
 Matrices are column-major: a torch tensor ``X`` of shape (rows, cols) with
 ``X.stride(0) == 1`` and ``X.stride(1) = ld >= rows`` (e.g. ``Y.t()`` for a
 row-major ``Y``).  Outputs are allocated column-major.
+
+A product whose reduction is split needs a workspace.  Without ``workspace=``
+the library keeps one per stream (calls on different streams and threads are
+independent); a ``workspace`` given by the caller must not be in use by
+another call at the same time.
 """
 from __future__ import annotations
 
@@ -203,9 +208,19 @@ def _plain_dtype(x: torch.Tensor) -> int:
     return _DT[x.dtype]
 
 
-def _ws(workspace):
-    return (workspace.data_ptr(), workspace.numel() * workspace.element_size()) \
-        if workspace is not None else (None, 0)
+def _ws(workspace, device, *call):
+    """(workspace, pointer, bytes) for a call (op, m, k, n, dtype).  None: the
+    library's own, which belongs to the stream; under capture one from torch,
+    whose memory belongs to the graph, so that graphs captured from one stream
+    may run at the same time."""
+    if workspace is None:
+        if not torch._C._cuda_isCurrentStreamCapturing():
+            return None, None, 0
+        need = workspace_size(*call)
+        if need == 0:
+            return None, None, 0
+        workspace = torch.empty(need, dtype=torch.uint8, device=device)
+    return workspace, workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def _product(fn: str, A, B: torch.Tensor, out, beta: float, workspace) -> torch.Tensor:
@@ -236,7 +251,8 @@ def _product(fn: str, A, B: torch.Tensor, out, beta: float, workspace) -> torch.
         out = empty_colmajor(m, n, cdt, dev)
     else:
         _check_out(out, m, n, cdt, dev)
-    ws, wsb = _ws(workspace)
+    op = OP_TSM2R_ROWMAJOR if ta else OP_TSM2R if fn == "tsm2r_ex" else OP_TSM2L
+    workspace, ws, wsb = _ws(workspace, dev, op, m, k, n, code)
     _lib.call(fn, ta, tb, m, k, n, a_ptr, lda, B.data_ptr(), ldb, float(beta), out.data_ptr(),
               _ld(out), code, ws, wsb, _stream())
     return out
@@ -313,8 +329,7 @@ def grad_b(A, dC: torch.Tensor, out: torch.Tensor | None = None,
             _check_out(out, k, n, torch.float32, dC.device)
         dC = colmajor(dC)
         dB = out if out is not None else empty_colmajor(k, n, torch.float32, dC.device)
-        ws, wsb = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) \
-            if workspace is not None else (None, 0)
+        workspace, ws, wsb = _ws(workspace, A.device, OP_GRAD_B, m, k, n, A.dtype_code)
         _lib.call("tsm_grad_b", m, k, n, A.planes.data_ptr(), A.ld, dC.data_ptr(), _ld(dC),
                   dB.data_ptr(), _ld(dB), A.dtype_code, ws, wsb, _stream())
         return dB
@@ -330,8 +345,7 @@ def grad_b(A, dC: torch.Tensor, out: torch.Tensor | None = None,
     A = colmajor(A)
     dC = colmajor(dC)
     dB = out if out is not None else empty_colmajor(k, n, A.dtype, A.device)
-    ws, wsb = (workspace.data_ptr(), workspace.numel() * workspace.element_size()) \
-        if workspace is not None else (None, 0)
+    workspace, ws, wsb = _ws(workspace, A.device, OP_GRAD_B, m, k, n, dt)
     _lib.call("tsm_grad_b", m, k, n, A.data_ptr(), _ld(A), dC.data_ptr(), _ld(dC),
               dB.data_ptr(), _ld(dB), dt, ws, wsb, _stream())
     return dB

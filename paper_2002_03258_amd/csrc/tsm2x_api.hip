@@ -6,7 +6,9 @@
 
 #include <cstdlib>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <tuple>
 #include <string>
 #include <vector>
@@ -31,12 +33,28 @@ int check_launch(const char* what) {
     return TSM_SUCCESS;
 }
 
+// A workspace buffer of the library.  Every stream has its own, so that calls
+// on different streams stay independent.
+struct WsBuf {
+    std::mutex mu;           // held until a call has enqueued its last launch
+    void* p = nullptr;
+    size_t bytes = 0;
+    bool captured = false;   // a graph may hold p
+    bool dead = false;       // taken out of the table
+    uint64_t used = 0;
+};
+// (stream, tag of the calling thread for the one handle that names a stream
+// per thread)
+typedef std::pair<hipStream_t, const void*> WsKey;
+constexpr size_t kMaxWsBufs = 64;
+
 struct DevState {
-    void* ws = nullptr;
-    size_t ws_bytes = 0;
+    std::map<WsKey, std::shared_ptr<WsBuf>> bufs;
+    std::vector<void*> retired;      // outgrown, but held by captured graphs
+    uint64_t clock = 0;
     int cus = 0;
 };
-std::mutex g_mu;
+std::mutex g_mu;             // may be taken with a WsBuf's mutex held; the other way round only tried
 std::vector<DevState> g_dev;
 
 DevState* dev_state(int* dev_out) {
@@ -316,8 +334,72 @@ bool holds(const void* ws, size_t ws_bytes, size_t need) {
     return need == 0 || (ws_bytes >= need && ((uintptr_t)ws & 255u) == 0);
 }
 
-// Workspace: caller's (checked) or the library's grow-only per-device buffer.
-int get_ws(size_t need, void* user, size_t user_bytes, void** out) {
+// Within its scope this thread may allocate and free although a stream is
+// being captured.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~RelaxedCapture() {
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+// Keeps a stream's buffer for one call: the launches that write and read the
+// partials are enqueued with no other thread's between them.
+struct WsHold {
+    std::shared_ptr<WsBuf> buf;
+    std::unique_lock<std::mutex> lock;
+};
+
+// The stream's entry of the table, locked.  The table is bounded: beyond
+// kMaxWsBufs streams the one longest unused gives its buffer back (hipFree
+// waits for the work on it), unless a graph may hold it.
+hipError_t hold_buf(hipStream_t st, bool capturing, WsHold* h) {
+    static thread_local char tag;
+    const WsKey key(st, st == hipStreamPerThread ? &tag : nullptr);
+    for (;;) {
+        std::shared_ptr<WsBuf> old;
+        {
+            std::lock_guard<std::mutex> lk(g_mu);
+            DevState* d = dev_state(nullptr);
+            if (!d) return hipErrorInvalidDevice;
+            std::shared_ptr<WsBuf>& e = d->bufs[key];
+            if (!e) e = std::make_shared<WsBuf>();
+            e->used = ++d->clock;
+            h->buf = e;
+            if (d->bufs.size() > kMaxWsBufs && !capturing) {
+                auto lru = d->bufs.end();
+                for (auto it = d->bufs.begin(); it != d->bufs.end(); ++it)
+                    if (it->second != e && (lru == d->bufs.end() || it->second->used < lru->second->used)) {
+                        std::unique_lock<std::mutex> l(it->second->mu, std::try_to_lock);
+                        if (l && !it->second->captured) lru = it;
+                    }
+                if (lru != d->bufs.end()) {
+                    std::unique_lock<std::mutex> l(lru->second->mu, std::try_to_lock);
+                    if (l && !lru->second->captured) {
+                        old = lru->second;
+                        old->dead = true;
+                        d->bufs.erase(lru);
+                    }
+                }
+            }
+        }
+        if (old && old->p) {
+            RelaxedCapture relaxed;
+            (void)hipFree(old->p);
+        }
+        h->lock = std::unique_lock<std::mutex>(h->buf->mu);
+        if (!h->buf->dead) return hipSuccess;
+        h->lock.unlock();
+    }
+}
+
+// Workspace: caller's (checked) or the library's buffer of the stream, which
+// grows as calls need it.  A buffer that a captured launch was given is never
+// freed before tsm2x_finalize, as a graph may hold its address: outgrown, it
+// is retired, and its successor has at least twice its size, so that the
+// retired ones together take no more than the one in use.
+int get_ws(size_t need, void* user, size_t user_bytes, hipStream_t st, WsHold* h, void** out) try {
     *out = nullptr;
     if (need == 0) return TSM_SUCCESS;
     if (user) {
@@ -325,48 +407,45 @@ int get_ws(size_t need, void* user, size_t user_bytes, void** out) {
         *out = user;
         return TSM_SUCCESS;
     }
-    std::lock_guard<std::mutex> lk(g_mu);
-    DevState* d = dev_state(nullptr);
-    if (!d) return hip_fail(hipErrorInvalidDevice, "hipGetDevice");
-    if (d->ws_bytes < need) {
-        if (d->ws) {
-            hipError_t e = hipFree(d->ws);
-            d->ws = nullptr;
-            d->ws_bytes = 0;
-            if (e != hipSuccess) return hip_fail(e, "hipFree(workspace)");
-        }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;     // the null stream is never captured
+    if (st && hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    hipError_t e = hold_buf(st, capturing, h);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    WsBuf& b = *h->buf;
+    if (b.bytes < need) {
+        RelaxedCapture relaxed;
         size_t bytes = need < ((size_t)1 << 20) ? ((size_t)1 << 20) : need;
-        void* p = nullptr;
-        hipError_t e = hipMalloc(&p, bytes);
+        const size_t twice = b.captured && 2 * b.bytes > bytes ? 2 * b.bytes : bytes;
+        if (b.p && (b.captured || capturing)) {
+            std::lock_guard<std::mutex> lk(g_mu);
+            if (DevState* d = dev_state(nullptr)) d->retired.push_back(b.p);
+        } else if (b.p) {
+            e = hipFree(b.p);
+        }
+        b.p = nullptr;
+        b.bytes = 0;
+        b.captured = false;
+        if (e != hipSuccess) return hip_fail(e, "hipFree(workspace)");
+        e = hipMalloc(&b.p, twice);
+        if (e == hipSuccess) {
+            bytes = twice;
+        } else if (twice > bytes) {
+            (void)hipGetLastError();
+            e = hipMalloc(&b.p, bytes);
+        }
         if (e != hipSuccess) {
+            b.p = nullptr;
             g_last_hip = std::string("hipMalloc(workspace): ") + hipGetErrorString(e);
             return TSM_ERR_ALLOC;
         }
-        d->ws = p;
-        d->ws_bytes = bytes;
+        b.bytes = bytes;
     }
-    *out = d->ws;
+    b.captured |= capturing;
+    *out = b.p;
     return TSM_SUCCESS;
-}
-
-// The library's buffer would have to grow while the stream is being captured,
-// where nothing can be allocated: the plain products then run unsplit.
-bool cold_capture(size_t need, const void* user, hipStream_t st) {
-    if (need == 0 || user) return false;
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        DevState* d = dev_state(nullptr);
-        if (!d || d->ws_bytes >= need) return false;
-    }
-    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &s) == hipSuccess && s == hipStreamCaptureStatusActive;
-}
-
-// A tn plan with one slice and no workspace.
-void unsplit(int64_t R, TNPlan* P) {
-    P->S = 1;
-    P->rslice = cdiv(R, 1024) * 1024;     // a whole number of any instance's steps
-    P->ws = 0;
+} catch (const std::bad_alloc&) {
+    return TSM_ERR_ALLOC;
 }
 
 // Validation of (m, k, n, A, lda, B, ldb, C, ldc, dtype) for C = A*B with
@@ -541,9 +620,8 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     if (rowx && ws) {
         // nothing is put there, but a workspace that this product's size
         // query would not have given is refused all the same
-        void* w = nullptr;
-        const int rc = get_ws(tsm2r_ws(transA, m, k, n, dtype, transB, true), ws, ws_bytes, &w);
-        if (rc) return rc;
+        if (!holds(ws, ws_bytes, tsm2r_ws(transA, m, k, n, dtype, transB, true)))
+            return TSM_ERR_WORKSPACE;
     }
     if ((lform && !transA && k <= 32) || rowx) {
         // B(j, p) at B[j*bsj + p*bsp]: both orders of B are plain strides here
@@ -562,14 +640,15 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         if (launch_rowtile(L, dtype, st)) return TSM_ERR_UNSUPPORTED;
         return check_launch("rowtile_kernel");
     }
+    WsHold hold;
     if (tt_shape(transA, m, k, n, dtype)) {
         // a caller's workspace of the size the TSM2R kernels need is accepted,
         // and they run if it is too small for this kernel's partials
         const size_t need = tt_ws(k, (int)m, (int)n, cus);
         const size_t nn = tsm2r_ws(transA, m, k, n, dtype, transB, true);
-        if (ws ? holds(ws, ws_bytes, nn > need ? nn : need) : !cold_capture(need, ws, st)) {
+        if (!ws || holds(ws, ws_bytes, nn > need ? nn : need)) {
             void* w = nullptr;
-            const int rc = get_ws(ws && nn > need ? nn : need, ws, ws_bytes, &w);
+            const int rc = get_ws(need, ws, ws_bytes, st, &hold, &w);
             if (rc) return rc;
             LaunchTT L{};
             L.R = k; L.ma = (int)m; L.n = (int)n; L.X = A; L.ldx = lda; L.Y = B; L.ldy = ldb;
@@ -589,8 +668,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
                      : tsm2r_ws(transA, m, k, n, dtype, transB && !direct, avec);
     const bool fine = !ws || holds(ws, ws_bytes, need);
     if (!fine) need = tsm2r_ws(transA, m, k, n, dtype, transB, avec, false);
-    const bool cold = plain_dtype(dtype) && (!transB || direct) && cold_capture(need, ws, st);
-    if (!cold) rc = get_ws(need, ws, ws_bytes, &w);
+    rc = get_ws(need, ws, ws_bytes, st, &hold, &w);
     if (rc) return rc;
     if (!plain_dtype(dtype)) {
         // A: 16-bit hi plane (and lo plane lda*k elements after it); B, C float
@@ -629,7 +707,6 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         // A given transposed is the column-major k x m matrix X = A^T (ld lda):
         // C = X^T * B, a reduction along the contiguous dimension.
         TNPlan P = plan_tn(k, m, n, dtype, cus, fine);
-        if (cold) unsplit(k, &P);
         LaunchTN L{};
         L.R = k; L.ncols = m; L.n = n;
         L.X = A; L.ldx = lda; L.Y = Bk; L.ldy = ldbk; L.O = C; L.ldo = ldc;
@@ -642,10 +719,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
         return check_launch("tn_kernel");
     }
     NNPlan P{};
-    const NNPin one{1, -1};
-    if (cold ? plan_tsm2r(m, k, n, dtype, cus, avec, &P, &one)
-             : plan_nn(m, k, n, dtype, cus, avec, &P, fine))
-        return TSM_ERR_UNSUPPORTED;
+    if (plan_nn(m, k, n, dtype, cus, avec, &P, fine)) return TSM_ERR_UNSUPPORTED;
     LaunchNN L{};
     L.fn = transB ? P.fn_bt : P.fn;
     L.m = m; L.k = k; L.n = n; L.A = A; L.lda = lda; L.B = Bk; L.ldb = ldbk; L.C = C; L.ldc = ldc;
@@ -781,9 +855,9 @@ int tsm_grad_b(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, cons
     // dB = A^T * dC: X = A (R = m rows, k columns), Y = dC.
     TNPlan P = plan_tn(m, k, n, dtype, cu_count());
     if (ws && !holds(ws, ws_bytes, P.ws)) P = plan_tn(m, k, n, dtype, cu_count(), false);
-    if (plain_dtype(dtype) && cold_capture(P.ws, ws, st)) unsplit(m, &P);
     void* w = nullptr;
-    int rc = get_ws(P.ws, ws, ws_bytes, &w);
+    WsHold hold;
+    int rc = get_ws(P.ws, ws, ws_bytes, st, &hold, &w);
     if (rc) return rc;
     LaunchTN L{};
     L.R = m; L.ncols = k; L.n = n; L.X = A; L.ldx = lda; L.Y = dC; L.ldy = lddc; L.O = dB;
@@ -924,10 +998,11 @@ int tsm2l_backward_ex(int transB, int64_t m, int64_t k, int64_t n, const void* A
     const int rc = check_bwd(m, k, n, A, lda, B, ldb, transB ? n : k, dC, lddc, dA, ldda, dB, lddb,
                              dtype);
     if (rc) return rc < 0 ? rc - 1 : rc;
+    WsHold hold;
     return run_bwd(m, k, n, A, lda, B, transB ? ldb : 1, transB ? 1 : ldb, dC, lddc, dA, ldda, dB,
                    lddb, dtype, (hipStream_t)stream, [&](size_t need, int* prc) -> void* {
                        void* w = nullptr;
-                       *prc = get_ws(need, ws, ws_bytes, &w);
+                       *prc = get_ws(need, ws, ws_bytes, (hipStream_t)stream, &hold, &w);
                        return w;
                    });
 }
@@ -937,10 +1012,11 @@ int tsm2l_backward(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda, 
                    int64_t lddb, int dtype, void* ws, size_t ws_bytes, void* stream) {
     int rc = check_bwd(m, k, n, A, lda, B, ldb, k, dC, lddc, dA, ldda, dB, lddb, dtype);
     if (rc) return rc;
+    WsHold hold;
     return run_bwd(m, k, n, A, lda, B, 1, ldb, dC, lddc, dA, ldda, dB, lddb, dtype,
                    (hipStream_t)stream, [&](size_t need, int* prc) -> void* {
                        void* w = nullptr;
-                       *prc = get_ws(need, ws, ws_bytes, &w);
+                       *prc = get_ws(need, ws, ws_bytes, (hipStream_t)stream, &hold, &w);
                        return w;
                    });
 }
@@ -1007,7 +1083,8 @@ int tsm_kmeans_assign(int64_t m, int64_t k, int64_t n, const void* X, int64_t ld
     if (!plain_dtype(dtype)) return -11;
     if (m == 0) return TSM_SUCCESS;
     void* w = nullptr;
-    int rc = get_ws(align256((size_t)n * esize(dtype)), ws, ws_bytes, &w);
+    WsHold hold;
+    int rc = get_ws(align256((size_t)n * esize(dtype)), ws, ws_bytes, (hipStream_t)stream, &hold, &w);
     if (rc) return rc;
     LaunchKM L{};
     L.m = m; L.k = k; L.n = n; L.X = X; L.ldx = ldx; L.x_rowmajor = x_rowmajor; L.Mu = Mu;
@@ -1104,16 +1181,26 @@ const char* tsm2x_last_hip_error(void) { return g_last_hip.c_str(); }
 int tsm2x_version(void) { return 100; }
 
 void tsm2x_finalize(void) {
-    std::lock_guard<std::mutex> lk(g_mu);
     int cur = 0;
     (void)hipGetDevice(&cur);
-    for (size_t d = 0; d < g_dev.size(); ++d) {
-        if (g_dev[d].ws) {
-            (void)hipSetDevice((int)d);
-            (void)hipFree(g_dev[d].ws);
-            g_dev[d].ws = nullptr;
-            g_dev[d].ws_bytes = 0;
+    for (size_t d = 0;; ++d) {
+        std::map<WsKey, std::shared_ptr<WsBuf>> bufs;
+        std::vector<void*> retired;
+        {
+            std::lock_guard<std::mutex> lk(g_mu);
+            if (d >= g_dev.size()) break;
+            bufs.swap(g_dev[d].bufs);
+            retired.swap(g_dev[d].retired);
         }
+        if (bufs.empty() && retired.empty()) continue;
+        (void)hipSetDevice((int)d);
+        for (auto& e : bufs) {
+            std::lock_guard<std::mutex> lk(e.second->mu);
+            e.second->dead = true;
+            if (e.second->p) (void)hipFree(e.second->p);
+            e.second->p = nullptr;
+        }
+        for (void* p : retired) (void)hipFree(p);
     }
     (void)hipSetDevice(cur);
 }

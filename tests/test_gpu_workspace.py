@@ -1,11 +1,15 @@
 """Workspaces, the caller's and the library's: results against the FP64 oracle
 at the tolerances of the forms."""
+import ctypes
+import threading
+
 import pytest
 import torch
 
 import oracle
 import paper_2002_03258_amd as tsm
 import seeded_inputs as si
+from paper_2002_03258_amd import _lib
 
 from helpers import TOL, dev_matrix, err, host_matrix, to_np
 
@@ -100,3 +104,161 @@ def test_small_caller_workspace_grad_b(dev, form, m, k, n):
     for w in (ws, behind[16:32]):
         assert err(to_np(tsm.grad_b(A, dC, workspace=w)), ref) <= TOL[dtype]
     assert bool((behind == 0xA5).all())
+
+
+# shapes whose split needs a workspace only to fill the GPU, one per kernel
+SPLIT = [(3001, 3001, 20, False), (1500, 1000, 8, True), (16, 5000, 16, False)]
+
+
+def _many(dtype, dev, count, seed):
+    """[(A, B, eager result)] over the shapes of SPLIT"""
+    out = []
+    for i in range(count):
+        m, k, n, row = SPLIT[i % len(SPLIT)]
+        A = dev_matrix(seed + i, si.STREAM_A, m, k, dtype, dev)
+        A = A.contiguous() if row else A
+        B = dev_matrix(seed + i, si.STREAM_B, k, n, dtype, dev)
+        out.append((A, B, tsm.tsm2r(A, B)))
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("dtype", list(DT))
+def test_streams_are_independent(dev, dtype):
+    """Products on several streams at a time, each on its stream's buffer, give
+    the bits of the products one after the other."""
+    ins = _many(dtype, dev, 6, 4300)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    outs = []
+    for _ in range(20):
+        for i, (A, B, want) in enumerate(ins):
+            with torch.cuda.stream(streams[i % 2 if i % 3 else 2]):
+                outs.append((tsm.tsm2r(A, B), want))
+    torch.cuda.synchronize()
+    assert all(torch.equal(got, want) for got, want in outs)
+
+
+@pytest.mark.parametrize("dtype", list(DT))
+def test_threads_on_one_stream(dev, dtype):
+    """Threads that share a stream: the launches of one product are enqueued
+    together."""
+    ins = _many(dtype, dev, 4, 4400)
+    outs = [[] for _ in ins]
+
+    def work(i):
+        for _ in range(50):
+            outs[i].append(tsm.tsm2r(ins[i][0], ins[i][1]))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(ins))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for got, (_, _, want) in zip(outs, ins):
+        assert len(got) == 50 and all(torch.equal(g, want) for g in got)
+
+
+def _direct(A, B, out):
+    """The C entry without a workspace, column-major A and B."""
+    rc = _lib.lib().tsm2r(A.shape[0], A.shape[1], B.shape[1], A.data_ptr(), A.stride(1),
+                          B.data_ptr(), B.stride(1), out.data_ptr(), out.stride(1),
+                          DT[A.dtype], torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, rc
+
+
+@pytest.mark.parametrize("dtype", list(DT))
+@pytest.mark.parametrize("direct", [False, True])
+def test_captured_products_outlive_a_growing_buffer(dev, dtype, direct):
+    """Captured before the library owns a buffer, then larger eager products on
+    the same stream, whose buffer grows past the captured one: every replay
+    gives the eager bits.  Through the binding (the graph owns the workspace)
+    and through the C entry (the library keeps it)."""
+    m, k, n = 3001, 3001, 20
+    A = dev_matrix(4500, si.STREAM_A, m, k, dtype, dev)
+    B = dev_matrix(4500, si.STREAM_B, k, n, dtype, dev)
+    want = tsm.tsm2r(A, B)
+    big = [(dev_matrix(4501 + i, si.STREAM_A, s, s, dtype, dev), dev_matrix(4501 + i, si.STREAM_B, s, w, dtype, dev))
+           for i, (s, w) in enumerate([(4099, 64), (6001, 64), (9001, 48)])]
+    wants = [tsm.tsm2r(a, b) for a, b in big]
+    out = tsm.empty_colmajor(m, n, dtype, dev)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    _lib.lib().tsm2x_finalize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        if direct:
+            _direct(A, B, out)
+        else:
+            tsm.tsm2r(A, B, out=out)
+    for (a, b), w in zip(big, wants):
+        out.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            got = tsm.tsm2r(a, b)
+        torch.cuda.synchronize()
+        assert torch.equal(got, w)
+        # memory given back in the meantime would be handed out here
+        filler = [torch.full((1 << 22,), float("nan"), device=dev) for _ in range(8)]
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        del filler
+        torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dtype", list(DT))
+def test_graphs_of_one_stream_replayed_together(dev, dtype):
+    ins = _many(dtype, dev, 4, 4600)
+    capture = torch.cuda.Stream()
+    graphs, outs = [], []
+    for A, B, want in ins:
+        outs.append(torch.zeros_like(want))
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=capture):
+            tsm.tsm2r(A, B, out=outs[-1])
+        graphs.append(g)
+    streams = [torch.cuda.Stream() for _ in graphs]
+    for _ in range(5):
+        for o in outs:
+            o.zero_()
+        torch.cuda.synchronize()
+        for _ in range(8):
+            for g, s in zip(graphs, streams):
+                with torch.cuda.stream(s):
+                    g.replay()
+        torch.cuda.synchronize()
+        for o, (_, _, want) in zip(outs, ins):
+            assert torch.equal(o, want)
+
+
+def test_buffers_of_many_streams_are_bounded(dev):
+    """More streams than the library keeps buffers for: the results are right,
+    and the buffers of the streams longest unused are given back."""
+    dtype = torch.float32
+    m, k, n = 3001, 3001, 20
+    A = dev_matrix(4700, si.STREAM_A, m, k, dtype, dev)
+    B = dev_matrix(4700, si.STREAM_B, k, n, dtype, dev)
+    want = tsm.tsm2r(A, B)
+    out = torch.zeros_like(want)
+    per = tsm.workspace_size(tsm.OP_TSM2R, m, k, n, tsm.F32)
+    hip = ctypes.CDLL(_lib.LIB_PATH)          # the runtime the library is linked with
+    torch.cuda.synchronize()
+    _lib.lib().tsm2x_finalize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    handles = []
+    for _ in range(100):
+        h = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(h)) == 0
+        handles.append(h)
+        with torch.cuda.stream(torch.cuda.ExternalStream(h.value)):
+            out.zero_()
+            _direct(A, B, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    kept = free - torch.cuda.mem_get_info()[0]
+    assert kept <= 80 * per, (kept, per)
+    _lib.lib().tsm2x_finalize()
+    for h in handles:
+        assert hip.hipStreamDestroy(h) == 0
