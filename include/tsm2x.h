@@ -295,17 +295,19 @@ size_t tsm2x_workspace_size(int op, int64_t m, int64_t k, int64_t n,
                             int dtype);
 
 /* Name of the main kernel a call (op, m, k, n, dtype) launches, as
- * profilers print it (for matching timings with profiler summaries).
- * Static storage; NULL
+ * profilers print it (for matching timings with profiler summaries), for
+ * column-major A and B, every column of A starting on a 128-byte line (other
+ * instances, with other names, serve the rest).  Static storage; NULL
  * for ops other than TSM_OP_TSM2R, the 16-bit forms, or empty or
  * unsupported shapes. */
 const char* tsm2x_kernel_name(int op, int64_t m, int64_t k, int64_t n, int dtype);
 
 /* Launch plan of a TSM2R product (tsm2r, or a TSM2R-class call of
  * tsm2x_gemm) of column-major F64/F32 A, m-by-k, and n <= 32 columns, on the
- * current device.  (An A of at most 32 rows and more than 32 columns runs on
- * a kernel of its own unless its plan is pinned; the plan reported is then the
- * TSM2R kernel's.)  The paper sizes its kernel from a performance model and
+ * current device, every column of A starting on a 128-byte line (the split
+ * can be another one otherwise).  (An A of at most 32 rows and more than 32 columns runs on
+ * a kernel of its own, the one tsm2x_kernel_name gives, unless its plan is
+ * pinned; the plan reported is then the TSM2R kernel's.)  The paper sizes its kernel from a performance model and
  * offline profiling (Section 3.6, Algorithm 5, and the t1 choice that
  * follows it); here the planner sizes the grid from the runtime's occupancy
  * query and a measured target, and a caller may replace its two choices per

@@ -390,15 +390,18 @@ def workspace_size(op: int, m: int, k: int, n: int, dtype: int) -> int:
 
 
 def kernel_name(op: int, m: int, k: int, n: int, dtype: int):
-    """Name of the main kernel the call launches (TSM2R, plain types), or None."""
+    """Name of the main kernel the call launches (TSM2R, plain types,
+    column-major A and B, A's columns on 128-byte lines), or None."""
     r = _lib.lib().tsm2x_kernel_name(op, m, k, n, dtype)
     return r.decode() if r else None
 
 
 def tsm2r_plan(m: int, k: int, n: int, dtype: int) -> dict:
-    """Launch plan of a TSM2R product on the current device (F64/F32, n <= 32):
-    k split ``slices``, tile height ``tall`` (0/1), ``tiles``, ``tile_rows``,
-    resident workgroups per CU ``occupancy``, ``cus`` and the kernel name."""
+    """Launch plan of a TSM2R product on the current device (F64/F32, n <= 32,
+    A's columns on 128-byte lines): k split ``slices``, tile height ``tall`` (0/1), ``tiles``, ``tile_rows``,
+    resident workgroups per CU ``occupancy``, ``cus`` and the kernel name (an A
+    of at most 32 rows and more than 32 columns runs on another kernel than the
+    plan's, the one named, unless pinned)."""
     import ctypes
     S, tall, rows, occ, cus = (ctypes.c_int() for _ in range(5))
     tiles = ctypes.c_int64()

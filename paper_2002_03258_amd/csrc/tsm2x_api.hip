@@ -1127,6 +1127,7 @@ size_t tsm2x_workspace_size(int op, int64_t m, int64_t k, int64_t n, int dtype) 
 const char* tsm2x_kernel_name(int op, int64_t m, int64_t k, int64_t n, int dtype) {
     if (op != TSM_OP_TSM2R || m <= 0 || k <= 0 || n <= 0 || n > 32 || !plain_dtype(dtype))
         return nullptr;
+    if (tt_shape(0, m, k, n, dtype)) return tt_name((int)m, (int)n, dtype);
     NNPlan P{};
     return plan_nn(m, k, n, dtype, cu_count(), true, &P) ? nullptr : P.name;
 }

@@ -123,6 +123,8 @@ struct LaunchTT {           // tt: O = X^T*Y, row-major X R x ma and Y R x n, ma
 };
 size_t tt_ws(int64_t R, int ma, int n, int cus);
 int launch_tt(const LaunchTT& L, int dtype, hipStream_t st);
+// the instance's name as profilers print it, column-major Y
+const char* tt_name(int ma, int n, int dtype);
 
 // Low-precision storage forms of A (bf16 / f16, single or split planes);
 // `vec`: the planes are 16-byte aligned with a 16-byte multiple leading dimension.

@@ -177,6 +177,15 @@ size_t tt_ws(int64_t R, int ma, int n, int cus) {
     return S > 1 ? (size_t)S * (ma <= 16 ? 1 : 2) * (n <= 16 ? 1 : 2) * 256 * 8 : 0;
 }
 
+const char* tt_name(int ma, int n, int dtype) {
+    static const char* const names[2][2][2] = {
+        {{"tt_kernel<double, 1, 1, false>", "tt_kernel<double, 1, 2, false>"},
+         {"tt_kernel<double, 2, 1, false>", "tt_kernel<double, 2, 2, false>"}},
+        {{"tt_kernel<float, 1, 1, false>", "tt_kernel<float, 1, 2, false>"},
+         {"tt_kernel<float, 2, 1, false>", "tt_kernel<float, 2, 2, false>"}}};
+    return names[dtype == DT_F64 ? 0 : 1][ma <= 16 ? 0 : 1][n <= 16 ? 0 : 1];
+}
+
 template <typename T, int NTA, int NTB>
 static int tt_launch(const LaunchTT& L, hipStream_t st) {
     const int S = tt_blocks(L.R, L.cus);

@@ -178,6 +178,21 @@ def test_kernel_name_query():
     assert tsm.kernel_name(tsm.OP_TSM2R, 4096, 4096, 8, tsm.BF16) is None
 
 
+@pytest.mark.parametrize("m,n,want", [(1, 1, "1, 1"), (16, 17, "1, 2"), (17, 16, "2, 1"),
+                                      (32, 32, "2, 2")])
+def test_kernel_name_of_few_rows(m, n, want):
+    """A column-major A of at most 32 rows runs on the tt kernel, unless pinned."""
+    for dt, tname in ((tsm.F64, "double"), (tsm.F32, "float")):
+        assert tsm.kernel_name(tsm.OP_TSM2R, m, 5000, n, dt) == "tt_kernel<%s, %s, false>" % (tname, want)
+        tsm.pin_tsm2r(m, 5000, n, dt, 1, 0)
+        try:
+            assert tsm.kernel_name(tsm.OP_TSM2R, m, 5000, n, dt).startswith("tsm2r_nn_kernel<")
+        finally:
+            tsm.unpin_tsm2r(m, 5000, n, dt)
+        assert tsm.kernel_name(tsm.OP_TSM2R, 33, 5000, n, dt).startswith("tsm2r_nn_kernel<")
+        assert tsm.kernel_name(tsm.OP_TSM2R, m, 32, n, dt).startswith("tsm2r_nn_kernel<")
+
+
 @pytest.mark.parametrize("args,expect", [
     ((0, 100, 8, 0, 1, 0), -1), ((100, 0, 8, 0, 1, 0), -2), ((100, 100, 0, 0, 1, 0), -3),
     ((100, 100, 33, 0, 1, 0), -3), ((100, 100, 8, 2, 1, 0), -4), ((100, 100, 8, 9, 1, 0), -4),

@@ -298,3 +298,15 @@ def test_products_captured_before_any_workspace(dev, dtype):
         for (a, b), o in zip(ins, outs):
             want = tsm.tsm2r(a, b)
             assert err(to_np(o), to_np(want)) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(5, 4000, 3), (32, 4000, 32), (64, 4000, 20), (1024, 1024, 8)])
+def test_kernel_name_is_the_launched_kernel(dev, dtype, m, k, n):
+    A = dev_matrix(4800, si.STREAM_A, m, k, dtype, dev, ld=(m + 31) // 32 * 32)
+    B = dev_matrix(4800, si.STREAM_B, k, n, dtype, dev)
+    tsm.timing_start()
+    tsm.tsm2r(A, B)
+    tsm.timing_stop()
+    names = [r["kernel"] for r in tsm.timing_collect()]
+    assert tsm.kernel_name(tsm.OP_TSM2R, m, k, n, tsm.F64 if dtype == torch.float64 else tsm.F32) in names
