@@ -18,7 +18,10 @@ by measurement on the caller's own operands:
    then timed in rounds, each in its own (seeded) random order so that no
    plan always follows the same one, each sample a block of back-to-back
    calls, and each plan's median is kept;
-4. pin the fastest for that shape (`pin_tsm2r`), so later calls use it.
+4. pin the fastest for that shape (`pin_tsm2r`), so later calls use it.  The
+   planner's own choice is timed as an unpinned call, whatever kernel that
+   runs (an A of at most 32 rows takes another one than the plans'), and left
+   unpinned where it is the fastest.
 
 Every candidate computes the same product (up to the order of the k sums), so
 tuning never changes results beyond rounding.
@@ -101,18 +104,24 @@ def autotune_tsm2r(A: torch.Tensor, B: torch.Tensor, top: int = 6, reps: int = 4
     Returns {"best": plan, "default": plan, "report": [...]}: each report
     entry is a plan with its model prediction (`pred_gbs`) and, for the timed
     ones, the measured rate (`gbs`, algorithmic bytes per second / 1e9).
-    With `pin`, the fastest plan is pinned for this shape; otherwise the
-    shape is left unpinned (a previous pin is removed either way)."""
+    Where the unpinned call runs another kernel than the plans', it has an
+    entry of its own, "default", without a prediction.  With `pin`, the
+    fastest plan is pinned for this shape, unless it is the planner's own;
+    otherwise the shape is left unpinned (a previous pin is removed either
+    way).  Products of more than 32 columns take one pass over A for up to 64
+    of them only while neither their 32-column shape nor that of their last
+    n % 32 columns is pinned."""
     if A.dtype not in (torch.float64, torch.float32):
         raise TypeError("autotune_tsm2r: F64 or F32 operands")
     m, k = A.shape
     n = B.shape[1]
     if n > 32:
-        raise ValueError("autotune_tsm2r: n <= 32 (wider products run in 32-column panels)")
+        raise ValueError("autotune_tsm2r: n <= 32 (wider products run in panels of their own plans)")
     dt = F64 if A.dtype == torch.float64 else F32
     es = A.element_size()
-    cands = candidates(m, k, n, dt)
+    cands = candidates(m, k, n, dt)          # leaves the shape unpinned
     default = tsm2r_plan(m, k, n, dt)
+    other = not default["kernel"].startswith("tsm2r_nn_kernel")
     if not any(p["tall"] == default["tall"] and p["slices"] == default["slices"] for p in cands):
         cands.append(default)
     ranked = model.rank(m, k, n, es, cands)
@@ -120,10 +129,22 @@ def autotune_tsm2r(A: torch.Tensor, B: torch.Tensor, top: int = 6, reps: int = 4
     if not any(p["tall"] == default["tall"] and p["slices"] == default["slices"] for p in chosen):
         chosen.append(next(p for p in ranked
                            if p["tall"] == default["tall"] and p["slices"] == default["slices"]))
+    planner = next(p for p in chosen
+                   if p["tall"] == default["tall"] and p["slices"] == default["slices"])
+    if other:                                    # not one of the plans
+        planner = default
+        chosen.append(planner)
+
+    def use(p):
+        if p is planner:
+            unpin_tsm2r(m, k, n, dt)
+        else:
+            pin_tsm2r(m, k, n, dt, p["slices"], p["tall"])
+
     C = empty_colmajor(m, n, A.dtype, A.device)
     alg = model.algorithmic_bytes(m, k, n, es)
     for p in chosen:                             # workspace at its final size
-        pin_tsm2r(m, k, n, dt, p["slices"], p["tall"])
+        use(p)
         tsm2r(A, B, out=C)
     unpin_tsm2r(m, k, n, dt)
     _warm(lambda: tsm2r(A, B, out=C), warm_seconds)
@@ -133,15 +154,16 @@ def autotune_tsm2r(A: torch.Tensor, B: torch.Tensor, top: int = 6, reps: int = 4
     for _ in range(rounds):
         rng.shuffle(order)
         for i in order:
-            p = chosen[i]
-            pin_tsm2r(m, k, n, dt, p["slices"], p["tall"])
+            use(chosen[i])
             tsm2r(A, B, out=C)                   # first call of this plan untimed
             times[i].append(_time_block(lambda: tsm2r(A, B, out=C), reps))
     report = []
-    for p in ranked:
+    for p in ranked + ([planner] if other else []):
         entry = {key: p[key] for key in ("tall", "slices", "tiles", "tile_rows", "occupancy",
                                           "workgroups", "kernel")}
-        entry["pred_gbs"] = p["pred"].gbs
+        entry["pred_gbs"] = p["pred"].gbs if "pred" in p else None
+        if p is planner:
+            own = entry
         for i, c in enumerate(chosen):
             if p is c:
                 ts = sorted(times[i])
@@ -150,10 +172,8 @@ def autotune_tsm2r(A: torch.Tensor, B: torch.Tensor, top: int = 6, reps: int = 4
         report.append(entry)
     timed = [e for e in report if "gbs" in e]
     best = max(timed, key=lambda e: e["gbs"])
-    if pin:
+    if pin and best is not own:
         pin_tsm2r(m, k, n, dt, best["slices"], best["tall"])
     else:
         unpin_tsm2r(m, k, n, dt)
-    d = next(e for e in timed
-             if e["tall"] == default["tall"] and e["slices"] == default["slices"])
-    return {"best": best, "default": d, "report": report}
+    return {"best": best, "default": own, "report": report}

@@ -135,3 +135,23 @@ def test_model_ranks_the_planner_choice_near_the_top(dev):
     d = tsm.tsm2r_plan(m, k, 16, tsm.F64)
     pos = [(p["tall"], p["slices"]) for p in ranked].index((d["tall"], d["slices"]))
     assert pos < 4
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_autotune_keeps_a_faster_kernel_of_another_kind(dev, dtype):
+    """An A of few rows runs on the tt kernel, several times faster than any
+    TSM2R plan: it is timed as the default and the shape stays unpinned."""
+    m, k, n = 16, 1 << 20, 16
+    dt = DT[dtype]
+    A = dev_matrix(66, si.STREAM_A, m, k, dtype, dev)
+    B = dev_matrix(66, si.STREAM_B, k, n, dtype, dev)
+    name = tsm.kernel_name(tsm.OP_TSM2R, m, k, n, dt)
+    assert name.startswith("tt_kernel<")
+    try:
+        r = tune.autotune_tsm2r(A, B, top=3, reps=2, rounds=3, warm_seconds=0.05)
+        assert r["default"]["kernel"] == name and r["default"]["pred_gbs"] is None
+        assert [e["kernel"].split("<")[0] for e in r["report"] if "gbs" in e].count("tt_kernel") == 1
+        assert r["best"] is r["default"]
+        assert tsm.kernel_name(tsm.OP_TSM2R, m, k, n, dt) == name
+    finally:
+        tsm.unpin_tsm2r(m, k, n, dt)
