@@ -507,15 +507,18 @@ size_t tsm2r_part(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool v
     return plan_nn(m, k, n, dtype, cus, vec, &P, fine) ? 0 : P.ws;
 }
 
-// Workspace of a TSM2R-kernel product of at most 32 columns: the split
-// partials, then room for B when it is given transposed (plain types) or for
-// B's packed 16-bit terms (precision form, B read in either order).
+// What follows the partials: room for B when it is given transposed (plain
+// types), or for B's packed 16-bit terms (precision form, B read in either
+// order).
+size_t behind_part(int64_t k, int64_t n, int dtype, bool transB) {
+    if (!plain_dtype(dtype)) return lp_bterms_bytes(k, n);
+    return transB ? (size_t)bt_ld(k, esize(dtype)) * n * esize(dtype) : 0;
+}
+
+// Workspace of a panel of a TSM2R-kernel product.
 size_t tsm2r_ws(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool transB, bool vec,
                 bool fine = true) {
-    const size_t part = align256(tsm2r_part(transA, m, k, n, dtype, vec, fine));
-    if (!plain_dtype(dtype)) return part + lp_bterms_bytes(k, n);
-    const int ce = esize(dtype);
-    return part + (transB ? (size_t)bt_ld(k, ce) * n * ce : 0);
+    return align256(tsm2r_part(transA, m, k, n, dtype, vec, fine)) + behind_part(k, n, dtype, transB);
 }
 
 // A column-major A of at most 32 rows, wider than the TSM2L kernels take:
@@ -662,19 +665,29 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     // B's packed 16-bit terms for the precision form]
     const bool avec = aligned(A, lda, dtype);
     const bool direct = plain_dtype(dtype) && transB && (!transA || (n <= 16 && m * k <= (int64_t)1 << 20));
+    NNPlan P{};
+    TNPlan T{};
+    size_t part = 0, need = 0;               // the partials' bytes, and with what follows them
+    auto plan = [&](bool fine) {
+        if (!plain_dtype(dtype)) {
+            plan_tsm2r_lp(m, k, n, dtype, cus, avec, &P, fine);
+        } else if (transA) {
+            T = plan_tn(k, m, n, dtype, cus, fine);
+        } else if (plan_nn(m, k, n, dtype, cus, avec, &P, fine)) {
+            return false;
+        }
+        part = align256(transA ? T.ws : P.ws);
+        need = part + behind_part(k, n, dtype, transB && (ws || !direct));
+        return true;
+    };
+    if (!plan(true)) return TSM_ERR_UNSUPPORTED;
+    if (ws && !holds(ws, ws_bytes, need) && !plan(false)) return TSM_ERR_UNSUPPORTED;
     void* w = nullptr;
-    int rc = TSM_SUCCESS;
-    size_t need = ws ? tsm2r_ws(transA, m, k, n, dtype, transB, avec)
-                     : tsm2r_ws(transA, m, k, n, dtype, transB && !direct, avec);
-    const bool fine = !ws || holds(ws, ws_bytes, need);
-    if (!fine) need = tsm2r_ws(transA, m, k, n, dtype, transB, avec, false);
-    rc = get_ws(need, ws, ws_bytes, st, &hold, &w);
+    int rc = get_ws(need, ws, ws_bytes, st, &hold, &w);
     if (rc) return rc;
     if (!plain_dtype(dtype)) {
         // A: 16-bit hi plane (and lo plane lda*k elements after it); B, C float
-        NNPlan P{};
-        plan_tsm2r_lp(m, k, n, dtype, cus, avec, &P, fine);
-        void* bt = (char*)w + align256(P.ws);
+        void* bt = (char*)w + part;
         launch_split_b(k, n, (const float*)B, transB ? ldb : 1, transB ? 1 : ldb, dtype, bt, st);
         rc = check_launch("split_b_kernel");
         if (rc) return rc;
@@ -696,7 +709,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     // 18.6; 1024^2, n = 30: 13.4 and 20.4).
     const bool copy = transB && !direct;
     if (copy) {
-        void* bc = (char*)w + align256(tsm2r_part(transA, m, k, n, dtype, avec, fine));
+        void* bc = (char*)w + part;
         launch_transpose(k, n, B, ldb, bc, bt_ld(k, ce), cdt, st);
         rc = check_launch("transpose_kernel");
         if (rc) return rc;
@@ -706,20 +719,17 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     if (transA) {
         // A given transposed is the column-major k x m matrix X = A^T (ld lda):
         // C = X^T * B, a reduction along the contiguous dimension.
-        TNPlan P = plan_tn(k, m, n, dtype, cus, fine);
         LaunchTN L{};
         L.R = k; L.ncols = m; L.n = n;
         L.X = A; L.ldx = lda; L.Y = Bk; L.ldy = ldbk; L.O = C; L.ldo = ldc;
         L.y_rowmajor = transB && !copy;
-        L.groups = P.groups; L.S = P.S; L.rslice = P.rslice; L.ct = P.ct;
-        L.pf = P.pf;
+        L.groups = T.groups; L.S = T.S; L.rslice = T.rslice; L.ct = T.ct;
+        L.pf = T.pf;
         L.beta = beta;
-        if (P.S > 1) L.part = (double*)w;
+        if (T.S > 1) L.part = (double*)w;
         if (launch_tn(L, dtype, st)) return TSM_ERR_UNSUPPORTED;
         return check_launch("tn_kernel");
     }
-    NNPlan P{};
-    if (plan_nn(m, k, n, dtype, cus, avec, &P, fine)) return TSM_ERR_UNSUPPORTED;
     LaunchNN L{};
     L.fn = transB ? P.fn_bt : P.fn;
     L.m = m; L.k = k; L.n = n; L.A = A; L.lda = lda; L.B = Bk; L.ldb = ldbk; L.C = C; L.ldc = ldc;

@@ -420,16 +420,20 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
     if (np > 32) {
         // bound by the matrix cores: the split whose grid lasts least, counting
         // full rounds of one workgroup per CU, two chunks to fill a
-        // wavefront's pipeline and the partials, written and read
+        // wavefront's pipeline and the partials, written and read.  Only the
+        // least S of each slice length is looked at (of up to 2048 splits in
+        // turn, three divisions each, the query of FP32 33 x 1048576, n = 33
+        // took 56 us of host time; 14 so)
         NNInstance I{};
         if (!(line ? nn_pick<true>(dtype, np, false, &I) : nn_pick<false>(dtype, np, false, &I)))
             return 1;
         const int64_t tiles = cdiv64(m, I.tile_rows), gran = (int64_t)WK * I.chunk;
+        const int64_t chunks = cdiv64(k, gran);
         double best = 0;
-        for (int64_t S = 1; S == 1 || (S <= k / (2 * gran) && tiles * S <= 8 * (int64_t)cus); ++S) {
-            const int64_t ks = cdiv64(cdiv64(k, S), gran) * gran, s = cdiv64(k, ks);
+        for (int64_t S = 1; S == 1 || (S <= k / (2 * gran) && tiles * S <= 8 * (int64_t)cus);) {
+            const int64_t lc = cdiv64(chunks, S), ks = lc * gran, s = cdiv64(k, ks);
             const int64_t W = tiles * s;
-            const double len = (double)ks / gran;
+            const double len = (double)lc;
             double t = (double)m * k * es * ((double)(cdiv64(W, cus) * cus) / (double)W) * (len + 2) / len;
             if (s > 1) t += 30e6 + (double)s * m * n * 16;
             if (S == 1 || t < best) {
@@ -437,7 +441,8 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
                 P->S = (int)s;
                 P->kslice = ks;
             }
-            if (pin && pin->S == 1) break;
+            if (lc == 1) break;
+            S = cdiv64(chunks, lc - 1);
         }
         P->np = np;
         P->fn = I.fn;
