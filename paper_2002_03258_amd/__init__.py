@@ -208,13 +208,14 @@ def _plain_dtype(x: torch.Tensor) -> int:
     return _DT[x.dtype]
 
 
-def _ws(workspace, device, *call):
-    """(workspace, pointer, bytes) for a call (op, m, k, n, dtype).  None: the
-    library's own, which belongs to the stream; under capture one from torch,
-    whose memory belongs to the graph, so that graphs captured from one stream
-    may run at the same time."""
+def _ws(workspace, stream, device, *call):
+    """(workspace, pointer, bytes) of a call (op, m, k, n, dtype) on `stream`
+    that is given a workspace or may be captured (on a stream other than the
+    default one, 0).  None: the library's own, which belongs to the stream;
+    under capture one from torch, whose memory belongs to the graph, so that
+    graphs captured from one stream may run at the same time."""
     if workspace is None:
-        if not torch._C._cuda_isCurrentStreamCapturing():
+        if not stream or not torch._C._cuda_isCurrentStreamCapturing():
             return None, None, 0
         need = workspace_size(*call)
         if need == 0:
@@ -251,10 +252,12 @@ def _product(fn: str, A, B: torch.Tensor, out, beta: float, workspace) -> torch.
         out = empty_colmajor(m, n, cdt, dev)
     else:
         _check_out(out, m, n, cdt, dev)
-    op = OP_TSM2R_ROWMAJOR if ta else OP_TSM2R if fn == "tsm2r_ex" else OP_TSM2L
-    workspace, ws, wsb = _ws(workspace, dev, op, m, k, n, code)
+    st, ws, wsb = _stream(), None, 0
+    if st or workspace is not None:
+        op = OP_TSM2R_ROWMAJOR if ta else OP_TSM2R if fn == "tsm2r_ex" else OP_TSM2L
+        workspace, ws, wsb = _ws(workspace, st, dev, op, m, k, n, code)
     _lib.call(fn, ta, tb, m, k, n, a_ptr, lda, B.data_ptr(), ldb, float(beta), out.data_ptr(),
-              _ld(out), code, ws, wsb, _stream())
+              _ld(out), code, ws, wsb, st)
     return out
 
 
@@ -329,9 +332,10 @@ def grad_b(A, dC: torch.Tensor, out: torch.Tensor | None = None,
             _check_out(out, k, n, torch.float32, dC.device)
         dC = colmajor(dC)
         dB = out if out is not None else empty_colmajor(k, n, torch.float32, dC.device)
-        workspace, ws, wsb = _ws(workspace, A.device, OP_GRAD_B, m, k, n, A.dtype_code)
+        st = _stream()
+        workspace, ws, wsb = _ws(workspace, st, A.device, OP_GRAD_B, m, k, n, A.dtype_code)
         _lib.call("tsm_grad_b", m, k, n, A.planes.data_ptr(), A.ld, dC.data_ptr(), _ld(dC),
-                  dB.data_ptr(), _ld(dB), A.dtype_code, ws, wsb, _stream())
+                  dB.data_ptr(), _ld(dB), A.dtype_code, ws, wsb, st)
         return dB
     _check_device(A, dC)
     dt = _plain_dtype(A)
@@ -345,9 +349,10 @@ def grad_b(A, dC: torch.Tensor, out: torch.Tensor | None = None,
     A = colmajor(A)
     dC = colmajor(dC)
     dB = out if out is not None else empty_colmajor(k, n, A.dtype, A.device)
-    workspace, ws, wsb = _ws(workspace, A.device, OP_GRAD_B, m, k, n, dt)
+    st = _stream()
+    workspace, ws, wsb = _ws(workspace, st, A.device, OP_GRAD_B, m, k, n, dt)
     _lib.call("tsm_grad_b", m, k, n, A.data_ptr(), _ld(A), dC.data_ptr(), _ld(dC),
-              dB.data_ptr(), _ld(dB), dt, ws, wsb, _stream())
+              dB.data_ptr(), _ld(dB), dt, ws, wsb, st)
     return dB
 
 

@@ -38,8 +38,9 @@ def assign(X: torch.Tensor, centroids: torch.Tensor, with_dist: bool = True,
     Mu = centroids.contiguous()              # n x k row-major = k x n column-major, ld k
     labels = torch.empty(m, dtype=torch.int32, device=X.device)
     dist = torch.empty(m, dtype=X.dtype, device=X.device) if with_dist else None
-    workspace, ws, wsb = _ws(workspace, X.device, OP_KMEANS, m, k, n, _DT[X.dtype])
+    st = _stream()
+    workspace, ws, wsb = _ws(workspace, st, X.device, OP_KMEANS, m, k, n, _DT[X.dtype])
     _lib.call("tsm_kmeans_assign", m, k, n, X.data_ptr(), ldx, rowmajor, Mu.data_ptr(), k,
               labels.data_ptr(), dist.data_ptr() if dist is not None else None, _DT[X.dtype],
-              ws, wsb, _stream())
+              ws, wsb, st)
     return labels, dist
