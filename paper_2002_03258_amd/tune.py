@@ -122,18 +122,18 @@ def autotune_tsm2r(A: torch.Tensor, B: torch.Tensor, top: int = 6, reps: int = 4
     cands = candidates(m, k, n, dt)          # leaves the shape unpinned
     default = tsm2r_plan(m, k, n, dt)
     other = not default["kernel"].startswith("tsm2r_nn_kernel")
-    if not any(p["tall"] == default["tall"] and p["slices"] == default["slices"] for p in cands):
+    own_plan = lambda p: p["tall"] == default["tall"] and p["slices"] == default["slices"]
+    if not other and not any(own_plan(p) for p in cands):
         cands.append(default)
     ranked = model.rank(m, k, n, es, cands)
     chosen = ranked[:top]
-    if not any(p["tall"] == default["tall"] and p["slices"] == default["slices"] for p in chosen):
-        chosen.append(next(p for p in ranked
-                           if p["tall"] == default["tall"] and p["slices"] == default["slices"]))
-    planner = next(p for p in chosen
-                   if p["tall"] == default["tall"] and p["slices"] == default["slices"])
-    if other:                                    # not one of the plans
+    if other:                                    # the planner's choice is not one of the plans
         planner = default
         chosen.append(planner)
+    else:
+        planner = next(p for p in ranked if own_plan(p))
+        if not any(p is planner for p in chosen):
+            chosen.append(planner)
 
     def use(p):
         if p is planner:
