@@ -26,9 +26,10 @@ struct LaunchTimer {
 
 namespace tsm {
 
-// Columns ld_bytes apart from p on all start on a 128-byte line.
-static inline bool line_aligned(const void* p, int64_t ld_bytes) {
-    return (uintptr_t)p % 128 == 0 && ld_bytes % 128 == 0;
+// Columns ld_bytes apart from p on all start on a 128-byte line, or on
+// another `unit`.
+static inline bool line_aligned(const void* p, int64_t ld_bytes, int64_t unit = 128) {
+    return (int64_t)((uintptr_t)p % unit) == 0 && ld_bytes % unit == 0;
 }
 
 enum { DT_F64 = 0, DT_F32 = 1, DT_BF16 = 2, DT_F16 = 3, DT_BF16_SPLIT = 4, DT_F16_SPLIT = 5 };

@@ -448,11 +448,18 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
     constexpr int64_t TR = 16 * (16 / (int64_t)sizeof(T)) * RG;
     static const int occ = km_occupancy(kmeans_assign_kernel<T, KS, NT16, RG, true, RES, ROWX>);
     const int64_t ntiles = (L.m + TR - 1) / TR;
-    // whole row-major pieces of several chunks or panels, float: two workgroups
-    // per CU stream faster than the three that fit (2000000 x 64, n = 64: 344
-    // and 367 us)
-    int64_t bx = (int64_t)L.cus * (!RES && ROWX == 1 && sizeof(T) == 4 && occ > 2 ? 2 : occ);
     const int64_t need = (ntiles + 3) / 4;
+    // whole row-major pieces of several chunks or panels, float, k >= 32: two
+    // workgroups per CU stream faster than the three that fit (k = 64, n = 64:
+    // 1000000 points 176 and 195 us, 3000000 477 and 537; k = 128, n = 16: 111
+    // and 116; k = 36..56, n <= 16 the other way, 25 and 23 us at 300000).  With
+    // less work per point more fit and serve better (3000000 points, n = 64:
+    // k = 4 113 and 82, k = 8 98 and 78, k = 28 272 and 248), for k = 16 up to 48
+    // centroids or few points (n = 33: 128 and 116; n = 64: 132 and 139, but 21.9
+    // and 19.9 at 300000)
+    const bool two = !RES && ROWX == 1 && sizeof(T) == 4 && occ > 2 &&
+                     (L.k >= 32 || (L.k == 16 && L.n > 48 && need >= 16 * (int64_t)L.cus));
+    int64_t bx = (int64_t)L.cus * (two ? 2 : occ);
     if (bx > need) bx = need;
     if (bx < 1) bx = 1;
     const unsigned nb = (unsigned)((L.n + 255) / 256);
@@ -464,9 +471,17 @@ static int km_launch(const LaunchKM& L, hipStream_t st) {
     TSM_LAUNCH((kmeans_assign_kernel<T, KS, NT16, RG, LINE, RES, ROWX>), g, b, 0, st, L.m,      \
                (int)L.k, (int)L.n, (const T*)L.X, L.ldx, (const T*)L.Mu, L.ldm, (const T*)L.mu2, \
                L.labels, (T*)L.dist)
-    // column-major points: non-temporal loads where every column starts on a
-    // 128-byte line (others would fetch the shared lines twice)
-    if (ROWX != 0 || line_aligned(L.X, L.ldx * (int64_t)sizeof(T))) TSM_K(true);
+    // column-major points: non-temporal loads, but for columns off the 128-byte
+    // lines where the grid goes round six times or more (double: eight), whose tiles find the
+    // lines that they share in the cache (float 2000000 x 128, n = 3, columns on
+    // 16 bytes: 241 us non-temporal, 224 cached; 4000000 x 16: 67 and 62).  On
+    // smaller grids the shared lines cost less than the detour (100000 x 194,
+    // n = 32: 68 and 90; double 49360 x 250: 91 and 120), and so they do with two
+    // centroid tiles and several chunks in double (2000000 x 128: 587 and 627).
+    const bool cached = ROWX == 0 && !line_aligned(L.X, L.ldx * (int64_t)sizeof(T)) &&
+                        need >= (sizeof(T) == 8 ? 8 : 6) * (int64_t)L.cus * occ &&
+                        !(sizeof(T) == 8 && KS == 8 && NT16 == 2);
+    if (!cached) TSM_K(true);
     else TSM_K(ROWX != 0);
 #undef TSM_K
     return hipGetLastError() != hipSuccess;

@@ -310,3 +310,20 @@ def test_kernel_name_is_the_launched_kernel(dev, dtype, m, k, n):
     tsm.timing_stop()
     names = [r["kernel"] for r in tsm.timing_collect()]
     assert tsm.kernel_name(tsm.OP_TSM2R, m, k, n, tsm.F64 if dtype == torch.float64 else tsm.F32) in names
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n,shift", [(1000, 3, 5, 1), (1027, 40, 16, 2), (2049, 70, 33, 1),
+                                         (130, 33, 17, 4), (4000003, 2, 3, 1)])
+def test_colmajor_points_off_lines(dev, dtype, m, k, n, shift):
+    """Column-major points whose columns start off the 128-byte lines: the
+    non-temporal instance, and the cached one on a grid that goes round often
+    enough; integer data, labels and distances exact."""
+    seed = 4900 + k + n
+    X = _odd_ld(dev_matrix(seed, si.STREAM_A, m, k, dtype, dev, dist="int", r=6), shift)
+    Mu = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev, dist="int", r=6)
+    lab, dist = kmeans.assign(X, Mu.t())
+    rlab, rdist = oracle.kmeans_assign(host_matrix(seed, si.STREAM_A, m, k, dtype, dist="int", r=6),
+                                       host_matrix(seed, si.STREAM_B, k, n, dtype, dist="int", r=6))
+    assert np.array_equal(lab.cpu().numpy(), rlab)
+    assert np.array_equal(to_np(dist), rdist)
