@@ -543,12 +543,26 @@ static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
 // wavefront instruction).  Otherwise the ends of every run share a line with
 // the next tile's: ordinary loads find it in the cache and ordinary stores
 // merge there (FP64 10302943 x 23, n = 23: 1249 us with
-// non-temporal accesses, 1002 without).  A next-tile register prefetch was measured and
+// non-temporal accesses, 1002 without).  On 64 bytes, what a write to memory
+// takes whole, non-temporal ones are the faster again for kin <= 16 (k = 6,
+// n = 32, 10000004 rows: FP64 676 us and 751, FP32 341 and 373), and for more on
+// up to 2^20 rows (500000 x 32, n = 8: FP32 17.5 and 19.6; 10000004: 354 and
+// 327); for a few columns in and out also on less (10000004 x 3, n = 2, on 16
+// bytes: FP32 59.9 and 62.3).  Wide outputs (dA of TSM2R), which a wavefront writes column after
+// column of one row tile: on 64 bytes (FP64 1000 x 100000, kin = 16: 150 and
+// 240; 10008 x 10000: 250 and 342 at kin = 32), and for kin > 16 on any
+// alignment, whose tiles are half as high (FP32 10001 x 3000: 44 and 61; kin =
+// 8: 57 and 41), but for a few tiles.  A next-tile register prefetch was measured and
 // dropped: the extra waves it costs hid the latency better.
 template <typename T, int KS, int NT16, int RG>
 static int rowtile_launch(const LaunchRT& L, hipStream_t st) {
     const int64_t es = sizeof(T);
-    const bool line = (L.x_rowmajor || line_aligned(L.X, L.ldx * es)) && line_aligned(L.O, L.ldo * es);
+    bool line = (L.x_rowmajor || line_aligned(L.X, L.ldx * es)) && line_aligned(L.O, L.ldo * es);
+    if (L.nout > 32)
+        line = line_aligned(L.O, L.ldo * es, 64) || (KS == 8 && L.m >= 256);
+    else if (!L.x_rowmajor && (KS < 8 || L.m <= (int64_t)1 << 20))
+        line = L.kin + L.nout <= 6 ||
+               (line_aligned(L.X, L.ldx * es, 64) && line_aligned(L.O, L.ldo * es, 64));
     const int rowx = !L.x_rowmajor ? 0 : L.kin == 4 * KS ? 1 : 2;
     if (rowx == 2)
         return line ? rowtile_launch_st<T, KS, NT16, RG, true, 2>(L, st)

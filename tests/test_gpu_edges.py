@@ -327,3 +327,35 @@ def test_colmajor_points_off_lines(dev, dtype, m, k, n, shift):
                                        host_matrix(seed, si.STREAM_B, k, n, dtype, dist="int", r=6))
     assert np.array_equal(lab.cpu().numpy(), rlab)
     assert np.array_equal(to_np(dist), rdist)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m", [136, 144, 257, 300, 1011])
+@pytest.mark.parametrize("k,n", [(70, 5), (33, 16), (129, 20), (40, 32)])
+def test_wide_output_off_lines(dev, dtype, m, k, n):
+    """dA on 64 bytes (136 and 144 rows), and by half-height tiles on any
+    alignment: non-temporal stores of whole and of ragged tiles."""
+    seed = 5000 + m + k + n
+    dC = dev_matrix(seed, si.STREAM_DC, m, n, dtype, dev)
+    B = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev)
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_DC, m, n, dtype),
+                        host_matrix(seed, si.STREAM_B, k, n, dtype).T)
+    for d in (dC, _odd_ld(dC)):
+        for b in (B, B.contiguous()):
+            assert err(to_np(tsm.grad_a(d, b)), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(136, 6, 32), (144, 16, 16), (1008, 30, 8), (5003, 3, 2), (5003, 1, 5),
+                                   (1000, 4, 4)])
+def test_tall_product_on_64_bytes(dev, dtype, m, k, n):
+    """A and C on 64 bytes, or few columns on any alignment: non-temporal."""
+    seed = 5100 + m + k + n
+    A = dev_matrix(seed, si.STREAM_A, m, k, dtype, dev)
+    B = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev)
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype),
+                        host_matrix(seed, si.STREAM_B, k, n, dtype))
+    assert err(to_np(tsm.tsm2l(A, B)), ref) <= TOL[dtype]
+    C = torch.ones((n, m), dtype=dtype, device=dev).t()
+    tsm.tsm2l(_odd_ld(A), B, out=C, beta=3.0)
+    assert err(to_np(C), ref + 3.0) <= TOL[dtype]
