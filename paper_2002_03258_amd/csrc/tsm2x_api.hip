@@ -302,7 +302,10 @@ void plan_tn_plain(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan*
         // the time of a split in bytes at the streaming rate: X (with one tile
         // Y is staged twice as often, 6 %), the second launch, 4 to 5 us with
         // what it costs the host, and the partials, written and read once
-        const double bytes = (double)R * gx * ct * 16 * es * (wide || ct == 2 ? 1.0 : 1.06);
+        // (one group reads the columns that there are, of two the last is
+        // moved up and reads 16)
+        const double bytes = (double)R * (gx == 1 ? ncols : gx * ct * 16) * es *
+                             (wide || ct == 2 ? 1.0 : 1.06);
         const int64_t most = R / (RB * 4 * 2);
         int64_t last = 0;
         // candidates: one to four slices, and those that fill j workgroups per CU
@@ -320,6 +323,11 @@ void plan_tn_plain(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan*
             if (best == 0 || t < best) {
                 best = t;
                 P->ct = ct;
+            // fewer columns than a workgroup takes: loads with bounds checks and
+            // nothing held in flight, for which one workgroup per CU is too few
+            // (1400000 x 6, n = 16: FP64 58 us with 249 workgroups, 47 with 498;
+            // FP32 4000000 x 6, n = 1: 54 and 41)
+            if (ncols < (wide ? 16 : 16 * ct) && gx * s <= cus) t *= 1.2;
                 P->groups = gx * ct;
                 P->rslice = rs;
                 P->S = (int)s;

@@ -60,7 +60,31 @@ __device__ __forceinline__ void load_run(const T* __restrict__ p, int64_t valid,
     }
 }
 
-// The store counterpart; NT = false for ordinary stores (a wavefront whose
+// A run that may end beyond its column, in two parts so that no branch stands
+// between the loads of several: load the run's own elements, or the column's
+// last RL where fewer than RL are left (`valid`, possibly none); then, with
+// all of them in flight, shift what belongs to the run into place, zeros
+// behind it.  The column has RL elements at least and ends with the valid ones.
+template <typename T, int RL>
+__device__ __forceinline__ void load_clamped(const T* __restrict__ p, int64_t valid, T (&out)[RL]) {
+    typedef typename VecOf<T, RL>::mem V;
+    const V v = *reinterpret_cast<const V*>(p + (valid >= RL ? 0 : valid - RL));
+#pragma unroll
+    for (int r = 0; r < RL; ++r) out[r] = v[r];
+}
+template <typename T, int RL>
+__device__ __forceinline__ void place_clamped(int64_t valid, T (&x)[RL]) {
+    const int sh = valid >= RL ? 0 : valid > 0 ? RL - (int)valid : RL;
+#pragma unroll
+    for (int r = 0; r < RL; ++r) {
+        T v = T(0);
+#pragma unroll
+        for (int s = 0; s + r < RL; ++s) v = sh == s ? x[r + s] : v;
+        x[r] = v;
+    }
+}
+
+// The store counterpart of load_run; NT = false for ordinary stores (a wavefront whose
 // 16-byte stores leave gaps that a second instruction fills: non-temporal
 // stores of such half-filled lines reach HBM as separate partial writes).
 template <typename T, int RL, bool NT = true>

@@ -302,6 +302,9 @@ __global__ __launch_bounds__(256) void tn_kernel(
             flush<NA>(reinterpret_cast<Flat&>(acc), reinterpret_cast<Flat&>(tot));
     };
 
+    // bounds checks, for groups of fewer than NX columns (clamped, the load
+    // instructions without a live column cost more than the waits: FP32
+    // 20000000 x 3, n = 1: 189 us, 160 so) and for fewer than RL rows.
     // staged column sc: sc < NX -> X column c0 + sc, else Y column sc - NX
     auto load = [&](int64_t rb, T (&v)[G][NC / 4][RL]) {
 #pragma unroll
@@ -405,10 +408,52 @@ __global__ __launch_bounds__(256) void tn_kernel(
         }
     };
 
+    // steps that end beyond the range: the same at clamped rows, which are
+    // shifted into place once all are loaded.  (With a branch around each load
+    // the waits behind them drained every load, one after the other where
+    // some lanes had whole runs: FP32, row-major 300000 x 33, n = 32 239 us, 165
+    // so; n = 8: 77 and 59; 300000 x 40: 74 and 59)
+    auto load_part = [&](int64_t rb, T (&v)[G][NC / 4][RL]) {
+#pragma unroll
+        for (int gs = 0; gs < G; ++gs) {
+            const int64_t r = rb + gs * SR + RL * rl;
+#pragma unroll
+            for (int cg = 0; cg < NC / 4; ++cg) {
+                const int sc = 4 * cg + kk;
+                if (cg < NX / 4) {
+                    load_clamped(X + r + (c0 + sc) * ldx, wb1 - r, v[gs][cg]);
+                } else {
+                    const int p = sc - NX < n ? sc - NX : n - 1;
+                    if (YR) {
+#pragma unroll
+                        for (int q = 0; q < RL; ++q)
+                            v[gs][cg][q] = Y[(r + q < wb1 ? r + q : wb1 - 1) * ldy + p];
+                    } else {
+                        load_clamped(Y + r + (int64_t)p * ldy, wb1 - r, v[gs][cg]);
+                    }
+                }
+            }
+        }
+    };
+    auto place_part = [&](int64_t rb, T (&v)[G][NC / 4][RL]) {
+#pragma unroll
+        for (int gs = 0; gs < G; ++gs) {
+            const int64_t valid = wb1 - (rb + gs * SR + RL * rl);
+#pragma unroll
+            for (int cg = 0; cg < NC / 4; ++cg) {
+                if (YR && cg >= NX / 4) {
+#pragma unroll
+                    for (int q = 0; q < RL; ++q) v[gs][cg][q] = q < valid ? v[gs][cg][q] : T(0);
+                } else {
+                    place_clamped(valid, v[gs][cg]);
+                }
+            }
+        }
+    };
+
     // pf, whole steps: the next step held in flight across the waits
-    // for this one (the scheduling barriers keep its loads ahead of them;
-    // the bounds branches of the general loop made those waits drain every
-    // load).  Not with four stages per step, whose two steps do not fit the
+    // for this one (the scheduling barriers keep its loads ahead of them).
+    // Not with four stages per step, whose two steps do not fit the
     // registers.
     // whole steps, each column group and slice starting at another one; for
     // n > 16 only slices do, where there is one group: the groups otherwise
@@ -444,10 +489,11 @@ __global__ __launch_bounds__(256) void tn_kernel(
         }
         flush_at(nit);
         if (at(nit) < wb1) {
-            load(at(nit), va);
-            stage_mul(va, false);
+            load_part(at(nit), va);
+            place_part(at(nit), va);
+            stage_mul(va, true);
         }
-    } else if (wb1 > wb0) {
+    } else if (wb1 > wb0 && (ncols < NX || R < RL)) {
         const int64_t all = nit + (at(nit) < wb1 ? 1 : 0);
         T v[G][NC / 4][RL];
         load(at(0), v);
@@ -455,6 +501,24 @@ __global__ __launch_bounds__(256) void tn_kernel(
             T vn[G][NC / 4][RL];
             if (it + 1 < all) load(at(it + 1), vn);
             stage_mul(v, false);
+            if (it < nit) flush_at(it + 1);
+#pragma unroll
+            for (int gs = 0; gs < G; ++gs)
+#pragma unroll
+                for (int cg = 0; cg < NC / 4; ++cg)
+#pragma unroll
+                    for (int q = 0; q < RL; ++q) v[gs][cg][q] = vn[gs][cg][q];
+        }
+    } else if (wb1 > wb0) {
+        const int64_t all = nit + (at(nit) < wb1 ? 1 : 0);
+        T v[G][NC / 4][RL];
+        load_part(at(0), v);
+        for (int64_t it = 0; it < all; ++it) {
+            T vn[G][NC / 4][RL];
+            if (it + 1 < all) load_part(at(it + 1), vn);
+            __builtin_amdgcn_sched_barrier(0);
+            if (it == nit) place_part(at(it), v);
+            stage_mul(v, true);
             if (it < nit) flush_at(it + 1);
 #pragma unroll
             for (int gs = 0; gs < G; ++gs)
@@ -473,7 +537,7 @@ __global__ __launch_bounds__(256) void tn_kernel(
     // one 16-column output tile at a time
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-        __syncthreads();                       // red lies over the tiles, and is reused
+        if (OVER || ct > 0) __syncthreads();   // red lies over the tiles, and is reused
         tn_finish<T, NT16, WK>(ncols, n, O, ldo, beta, c0 + 16 * ct, cg0, s, nsl, part, red,
                                acc[ct], [](int kq, int r) { return Mfma<T>::mrow(kq, r); });
     }

@@ -359,3 +359,41 @@ def test_tall_product_on_64_bytes(dev, dtype, m, k, n):
     C = torch.ones((n, m), dtype=dtype, device=dev).t()
     tsm.tsm2l(_odd_ld(A), B, out=C, beta=3.0)
     assert err(to_np(C), ref + 3.0) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(1000, 33, 24), (77, 40, 5), (65, 65, 32), (500, 200, 17), (40, 35, 1),
+                                   (31, 130, 16), (33, 67, 20), (17, 4099, 8)])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_rowmajor_ragged_contraction(dev, dtype, m, k, n, pad):
+    """A row-major A whose k is no whole number of the reduction kernel's
+    steps, rows `pad` elements apart (NaN between them): the clamped rows of
+    the last step, B in either order, an infinity in the last column."""
+    seed = 5200 + m + k + n
+    store = torch.full((m, k + pad), float("nan"), dtype=dtype, device=dev)
+    A = store[:, pad // 2:pad // 2 + k]
+    A.copy_(dev_matrix(seed, si.STREAM_A, m, k, dtype, dev))
+    B = _odd_ld(dev_matrix(seed, si.STREAM_B, k, n, dtype, dev))
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype),
+                        host_matrix(seed, si.STREAM_B, k, n, dtype))
+    for b in (B, B.contiguous()):
+        C = torch.ones((n, m), dtype=dtype, device=dev).t()
+        tsm.tsm2r(A, b, out=C, beta=-0.5)
+        assert err(to_np(C), ref - 0.5) <= TOL[dtype]
+    A[m // 2, k - 1] = float("inf")
+    C = tsm.tsm2r(A, torch.ones((n, k), dtype=dtype, device=dev).t())
+    assert torch.isinf(C[m // 2]).all()
+    assert torch.isfinite(C).sum().item() == (m - 1) * n
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(1, 40, 5), (2, 16, 16), (3, 33, 20), (3, 5, 32), (5, 64, 3),
+                                   (70001, 6, 24), (40003, 24, 16), (2047, 31, 20), (300, 12, 1)])
+def test_grad_b_few_rows_or_columns(dev, dtype, m, k, n):
+    """Fewer rows than a 16-byte run, or fewer columns than a workgroup takes."""
+    seed = 5300 + m + k + n
+    A = _odd_ld(dev_matrix(seed, si.STREAM_A, m, k, dtype, dev))
+    dC = _odd_ld(dev_matrix(seed, si.STREAM_DC, m, n, dtype, dev))
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype).T,
+                        host_matrix(seed, si.STREAM_DC, m, n, dtype))
+    assert err(to_np(tsm.grad_b(A, dC)), ref) <= TOL[dtype]
