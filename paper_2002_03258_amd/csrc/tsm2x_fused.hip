@@ -285,10 +285,16 @@ static int bwd_launch(const LaunchBwd& L, int64_t* blocks_out, hipStream_t st, b
     if (plan_only) return 0;
     // 16-byte runs of the 16-bit planes (T's runs need no alignment)
     const bool pv = AF < 0 || (((uintptr_t)L.A & 15u) == 0 && L.lda % 8 == 0);
-    // non-temporal where every column starts on a 128-byte line (as rowtile)
+    // non-temporal where every column starts on a 128-byte line (as rowtile),
+    // those of dA on 64 bytes at least (FP64 4000008 x 32, n = 32, dA on 64: 636 us
+    // and 666 cached).  Also where a wavefront has a tile or two and the last
+    // is not whole: its element-wise loads wait for each other in the cached
+    // instance and hold up the call (127741 x 32, n = 32: FP64 35 and 45 us,
+    // FP32 27 and 34; 50000 x 32: FP32 20 and 29)
     const int64_t es = sizeof(T);
-    const bool line = (AF >= 0 || line_aligned(L.A, L.lda * es)) && line_aligned(L.dC, L.lddc * es) &&
-                      line_aligned(L.dA, L.ldda * es);
+    const bool line = ((AF >= 0 || line_aligned(L.A, L.lda * es)) && line_aligned(L.dC, L.lddc * es) &&
+                       line_aligned(L.dA, L.ldda * es, 64)) ||
+                      (need <= (int64_t)L.cus * (occ > 1 ? occ : 2) && L.m % TR != 0);
     const uint16_t* alo = ASPLIT ? (const uint16_t*)L.A + L.lda * L.k : nullptr;
     dim3 g((unsigned)bx), b(256);
 #define TSM_B(LINE, PV)                                                                            \
