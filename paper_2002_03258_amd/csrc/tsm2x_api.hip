@@ -96,9 +96,13 @@ bool plain_dtype(int dt) { return dt == TSM_F64 || dt == TSM_F32; }
 int esize(int dt) { return dt == TSM_F64 ? 8 : 4; }
 
 // What picks a kernel's instance: plain types, every column on a 128-byte
-// line; 16-bit planes, every column on 16 bytes.
-bool aligned(const void* p, int64_t ld, int dtype) {
-    return plain_dtype(dtype) ? line_aligned(p, ld * esize(dtype)) : ((uintptr_t)p & 15u) == 0 && ld % 8 == 0;
+// line, or on 64 bytes for a tall matrix of few columns (2^18 rows, 256
+// columns, n <= 16; FP64 beyond 128 columns n <= 8: 541440 x 256, n = 16 233 us
+// without and 242 with); 16-bit planes, every column on 16 bytes.
+bool aligned(const void* p, int64_t ld, int dtype, int64_t m, int64_t k, int64_t n) {
+    if (!plain_dtype(dtype)) return ((uintptr_t)p & 15u) == 0 && ld % 8 == 0;
+    const bool few = m >= (int64_t)1 << 18 && k <= 256 && n <= (dtype == TSM_F64 && k > 128 ? 8 : 16);
+    return line_aligned(p, ld * esize(dtype), few ? 64 : 128);
 }
 
 int pow2_ge(int64_t n) {
@@ -319,15 +323,15 @@ void plan_tn_plain(int64_t R, int64_t ncols, int64_t n, int dt, int cus, TNPlan*
             const int64_t s = cdiv(R, rs);
             const double len = (double)rs / (RB * 4);
             double t = bytes * grid_time(gx * s, cus) * (len + 2) / len;
-            if (s > 1) t += 30e6 + (double)s * gx * ct * 16 * (wide ? 32 : 16) * 16;
-            if (best == 0 || t < best) {
-                best = t;
-                P->ct = ct;
             // fewer columns than a workgroup takes: loads with bounds checks and
             // nothing held in flight, for which one workgroup per CU is too few
             // (1400000 x 6, n = 16: FP64 58 us with 249 workgroups, 47 with 498;
             // FP32 4000000 x 6, n = 1: 54 and 41)
             if (ncols < (wide ? 16 : 16 * ct) && gx * s <= cus) t *= 1.2;
+            if (s > 1) t += 30e6 + (double)s * gx * ct * 16 * (wide ? 32 : 16) * 16;
+            if (best == 0 || t < best) {
+                best = t;
+                P->ct = ct;
                 P->groups = gx * ct;
                 P->rslice = rs;
                 P->S = (int)s;
@@ -555,7 +559,11 @@ size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool
 // bound by the matrix cores at 64 (20480^2, n = 64: FP64 1313 us in two
 // passes, 946 in one, FP32 659 and 551; n = 33: 1119 and 722, 544 and 397).  32 elsewhere, for a caller's workspace that holds
 // the partials of 32 columns only, and where a plan of a narrower panel is
-// pinned.
+// pinned.  Also for a tall A of few columns, where a wavefront has too few
+// steps to gain back what its fewer neighbours cost: FP64 beyond 48 columns
+// (1000000 x 64, n = 64: 523 us in one pass, 396 in two; 50000 x 90: 48 and 40;
+// but 300000 x 72: 149 and 169), FP32 where the wavefronts' 16-column chunks are not
+// whole (1000000 x 40, n = 48: 347 and 271; 50000 x 40 one pass is the faster).
 int64_t panel_width(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
                     const void* A, int64_t lda, int dtype, const void* ws, size_t ws_bytes) {
     if (n <= 32 || transA || !plain_dtype(dtype) || (lform && k <= 32) || m <= 32) return 32;
@@ -564,8 +572,11 @@ int64_t panel_width(bool lform, int transA, int transB, int64_t m, int64_t k, in
         return p.S > 0 || p.tall >= 0;
     };
     if (pinned(32) || (n % 32 && pinned(n % 32))) return 32;
+    if (dtype == TSM_F64 ? n > 48 && (k <= 68 || k > 80) && k <= 96 && m >= 1 << 15
+                         : k <= 96 && k % 16 != 0 && m >= 1 << 18)
+        return 32;
     if (ws && !holds(ws, ws_bytes, tsm2r_ws(0, m, k, n < 64 ? n : 64, dtype, transB,
-                                            aligned(A, lda, dtype))))
+                                            aligned(A, lda, dtype, m, k, n))))
         return 32;
     return 64;
 }
@@ -575,11 +586,11 @@ int64_t panel_width(bool lform, int transA, int transB, int64_t m, int64_t k, in
 size_t caller_ws(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
                  const void* A, int64_t lda, int dtype, const void* ws, size_t ws_bytes) {
     if (lform && !transA && k <= 32) return 0;
-    const bool al = (transA && k <= 32) || aligned(A, lda, dtype);
     const int64_t panel = panel_width(lform, transA, transB, m, k, n, A, lda, dtype, ws, ws_bytes);
     size_t most = 0;
     for (const int64_t w : {n < panel ? n : panel, n > panel ? n % panel : (int64_t)0}) {
         if (w == 0) continue;
+        const bool al = (transA && k <= 32) || aligned(A, lda, dtype, m, k, w);
         const size_t fine = tsm2r_ws(transA, m, k, w, dtype, transB, al);
         const size_t coarse = tsm2r_ws(transA, m, k, w, dtype, transB, al, false);
         const size_t b = fine < coarse ? fine : coarse;
@@ -671,7 +682,7 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     }
     // TSM2R kernels; workspace = [split partials][B copied column-major, or
     // B's packed 16-bit terms for the precision form]
-    const bool avec = aligned(A, lda, dtype);
+    const bool avec = aligned(A, lda, dtype, m, k, n);
     const bool direct = plain_dtype(dtype) && transB && (!transA || (n <= 16 && m * k <= (int64_t)1 << 20));
     NNPlan P{};
     TNPlan T{};

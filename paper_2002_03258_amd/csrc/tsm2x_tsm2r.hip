@@ -321,6 +321,9 @@ struct NNInstance {
 // the second finds it in a cache: neighbouring tiles run on one XCD then, and
 // A's loads are not non-temporal.  FP32, n = 5, A 10007 x 9973: 82 us, 73 so;
 // FP32 20011^2, n = 8: 302 and 283; FP64 7777 x 6001, n = 12: 75 and 68.
+// Columns on 64 bytes of a tall matrix with few of them take it as well
+// (aligned() in the dispatch): 1000000 x 64, n = 1: FP64 98 us without, 88
+// with; FP32 541440 x 256, n = 16: 140 and 132; but 5000^2: 27 and 29.
 // Line-aligned columns keep the workgroups' round-robin order (FP32 16384^2
 // ran 2.5 % slower with neighbours on one XCD, others within 1.5 % either way).
 template <typename T, int NT16, int RG, int ST, bool LINE>
@@ -435,6 +438,10 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
             const int64_t W = tiles * s;
             const double len = (double)lc;
             double t = (double)m * k * es * ((double)(cdiv64(W, cus) * cus) / (double)W) * (len + 2) / len;
+            // fewer rows than a tile: no prefetch, one workgroup per CU is too few
+            // (33 x 1000000, n = 33: FP64 243 us with up to 256, 165 with 512; FP32
+            // 137 and 104)
+            if (m < I.tile_rows && W <= cus) t *= 1.25;
             if (s > 1) t += 30e6 + (double)s * m * n * 16;
             if (S == 1 || t < best) {
                 best = t;
@@ -519,7 +526,9 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
             };
             auto slice = [&](int64_t S) { return cdiv64(cdiv64(k, S), gran) * gran; };
             int64_t ks = slice(split(false)), W = tiles * cdiv64(k, ks);
-            bool take = W <= cus && 8 * W >= 7 * (int64_t)cus;
+            // (a matrix of fewer rows than a tile runs without the prefetch: FP32
+            // 100 x 1000000, n = 4: 173 us with 256 workgroups, 154 with 480)
+            bool take = m >= I.tile_rows && W <= cus && 8 * W >= 7 * (int64_t)cus;
             const int64_t have = P->tiles * P->S;
             if (fine && !take && 8 * have < 7 * (int64_t)cus) {
                 // the plan so far leaves CUs idle

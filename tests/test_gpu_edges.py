@@ -397,3 +397,21 @@ def test_grad_b_few_rows_or_columns(dev, dtype, m, k, n):
     ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype).T,
                         host_matrix(seed, si.STREAM_DC, m, n, dtype))
     assert err(to_np(tsm.grad_b(A, dC)), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(262152, 40, 5), (262160, 33, 16), (262147, 40, 40), (32771, 40, 50),
+                                   (40, 3000, 40), (100, 9000, 5)])
+def test_tall_products_of_few_columns(dev, dtype, m, k, n):
+    """Columns on 64 bytes (262152 and 262160 rows), more than 32 columns in
+    two passes, and fewer rows than a tile."""
+    seed = 5400 + m + k + n
+    A = dev_matrix(seed, si.STREAM_A, m, k, dtype, dev)
+    B = dev_matrix(seed, si.STREAM_B, k, n, dtype, dev)
+    ref = oracle.matmul(host_matrix(seed, si.STREAM_A, m, k, dtype),
+                        host_matrix(seed, si.STREAM_B, k, n, dtype))
+    got = tsm.tsm2r(A, B)
+    assert err(to_np(got), ref) <= TOL[dtype]
+    code = tsm.F64 if dtype == torch.float64 else tsm.F32
+    ws = torch.empty(tsm.workspace_size(tsm.OP_TSM2R, m, k, n, code) + 256, dtype=torch.uint8, device=dev)
+    assert torch.equal(tsm.tsm2r(A, B.contiguous(), workspace=ws), tsm.tsm2r(A, B.contiguous()))
