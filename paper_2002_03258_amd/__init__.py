@@ -306,9 +306,11 @@ def grad_a(dC: torch.Tensor, B: torch.Tensor, out: torch.Tensor | None = None) -
         _check_out(out, m, k, dC.dtype, dC.device)
     dC = colmajor(dC)
     # a large dA re-reads B for every row tile: faster from a column-major copy
-    # (float32 16384^2, n = 8: 520 us a step without the copy, 496 with); a small
-    # one takes less than the copy and its launch
-    if k > 32 and m * k > 1 << 22:
+    # (16384^2, n = 8: float32 173 us with it, 193 without, float64 321 and 390;
+    # 8192 x 4096: float64 49.1 and 49.5; n = 32, 4096 x 2048: 16.0 and 16.8, 25.4
+    # and 27.0); a small one takes less than the copy and its launch (4096^2, n =
+    # 8: 18.3 and 14.0, 31.1 and 29.6; n = 32, 2048^2: 12.6 and 11.2, 16.4 and 16.8)
+    if k > 32 and m * k > (1 << 24 if n <= 8 else 1 << 22):
         B = colmajor(B)
     B, tb, ldb = _operand(B)
     dA = out if out is not None else empty_colmajor(m, k, dC.dtype, dC.device)

@@ -683,7 +683,15 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     // TSM2R kernels; workspace = [split partials][B copied column-major, or
     // B's packed 16-bit terms for the precision form]
     const bool avec = aligned(A, lda, dtype, m, k, n);
-    const bool direct = plain_dtype(dtype) && transB && (!transA || (n <= 16 && m * k <= (int64_t)1 << 20));
+    // The reduction kernel reads B in runs down its columns.  A row-major B of
+    // up to 16 columns it loads value by value, which takes less than the copy
+    // and its launch, where a wavefront has up to 256 rows of it (1024^2, n = 4:
+    // FP32 10.2 us and 11.4 with the copy, FP64 9.0 and 11.4; FP64 2048^2, n = 16,
+    // 128 rows: 12.2 and 14.6; but FP32 1448^2, n = 4, 384 rows: 14.6 and 11.4;
+    // 2048^2, 512: 18.1 and 11.6) and the grid is not so large that its
+    // workgroups' loads add up (FP32 8192 x 256, n = 16, 256 workgroups: 7.7 and
+    // 11.5; 65536 x 128, 2048: 16.7 and 15.5).
+    bool direct = plain_dtype(dtype) && transB && !transA;
     NNPlan P{};
     TNPlan T{};
     size_t part = 0, need = 0;               // the partials' bytes, and with what follows them
@@ -692,6 +700,8 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
             plan_tsm2r_lp(m, k, n, dtype, cus, avec, &P, fine);
         } else if (transA) {
             T = plan_tn(k, m, n, dtype, cus, fine);
+            direct = transB && n <= 16 && (k <= 256 || T.rslice <= 4 * 256) &&
+                     T.groups / T.ct * T.S <= 4 * (int64_t)cus;
         } else if (plan_nn(m, k, n, dtype, cus, avec, &P, fine)) {
             return false;
         }
@@ -721,11 +731,6 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     }
     const void* Bk = B;
     int64_t ldbk = ldb;
-    // The tn kernel reads B in runs down its columns.  For a row-major B it
-    // loads them value by value where A is small, which takes less than the
-    // copy and its launch (1024^2, n = 4: FP64 13.1 us with the copy, 9.9
-    // without, FP32 13.4 and 11.0), and copies B beyond (FP32 2048^2, n = 16: 12.8 and
-    // 18.6; 1024^2, n = 30: 13.4 and 20.4).
     const bool copy = transB && !direct;
     if (copy) {
         void* bc = (char*)w + part;

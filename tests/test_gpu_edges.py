@@ -415,3 +415,30 @@ def test_tall_products_of_few_columns(dev, dtype, m, k, n):
     code = tsm.F64 if dtype == torch.float64 else tsm.F32
     ws = torch.empty(tsm.workspace_size(tsm.OP_TSM2R, m, k, n, code) + 256, dtype=torch.uint8, device=dev)
     assert torch.equal(tsm.tsm2r(A, B.contiguous(), workspace=ws), tsm.tsm2r(A, B.contiguous()))
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(1025, 1024, 4), (2048, 2048, 8), (200, 5000, 16), (1448, 1448, 4),
+                                   (64, 16384, 3), (20000, 100, 5), (257, 300, 16), (33, 256, 17)])
+def test_rowmajor_b_of_the_reduction_kernel(dev, dtype, m, k, n):
+    """Read in place or copied first, a row-major B gives the bits of its
+    column-major copy, with rows padded too."""
+    A = dev_matrix(5500, si.STREAM_A, m, k, dtype, dev).contiguous()
+    B = dev_matrix(5500, si.STREAM_B, k, n, dtype, dev)
+    rows = torch.full((k, n + 3), float("nan"), dtype=dtype, device=dev)
+    Bp = rows[:, 2:2 + n]
+    Bp.copy_(B)
+    want = tsm.tsm2r(A, B)
+    for b in (B.contiguous(), Bp):
+        assert torch.equal(tsm.tsm2r(A, b), want)
+    ref = oracle.matmul(host_matrix(5500, si.STREAM_A, m, k, dtype),
+                        host_matrix(5500, si.STREAM_B, k, n, dtype))
+    assert err(to_np(want), ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("m,k,n", [(4096, 4100, 8), (2049, 2048, 9), (2048, 2048, 32)])
+def test_large_da_rowmajor_b(dev, dtype, m, k, n):
+    dC = dev_matrix(5600, si.STREAM_DC, m, n, dtype, dev)
+    B = dev_matrix(5600, si.STREAM_B, k, n, dtype, dev)
+    assert torch.equal(tsm.grad_a(dC, B.contiguous()), tsm.grad_a(dC, B))
