@@ -581,8 +581,6 @@ static int occupancy(K kernel, int threads) {
     return nb;
 }
 
-static inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
-
 template <typename T, int KS, int NT16, int RG, bool LINE, int ROWX>
 static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
     // persistent grid: as many workgroups as fit at once (queried occupancy),
@@ -713,6 +711,19 @@ int launch_split_reduce(int dtype, int64_t groups, int S, int NP, int W, int64_t
     // eight or so, all in flight at once (FP32 2048^2, n = 16, 16 slices: 20.0
     // us with a wavefront per output, 14.4 with eight threads; 1500 x 28032,
     // n = 24, 21 slices: 49 us with a thread per output, 41 with eight).
+    // In pieces of at most 2^31 threads: a launch takes fewer than 2^32.
+    const int per = S > 64 ? 64 : S > 8 ? 8 : 1;
+    const int64_t most = ((int64_t)1 << 31) / per / ((int64_t)n * W);
+    if (most > 0 && groups > most) {
+        const int64_t es = dtype == DT_F64 ? 8 : 4;
+        for (int64_t g = 0; g < groups; g += most) {
+            const int64_t gn = groups - g < most ? groups - g : most;
+            const int rc = launch_split_reduce(dtype, gn, S, NP, W, rows - g * W, n, part + g * S * NP * W,
+                                               (char*)O + g * W * es, ldo, beta, st);
+            if (rc) return rc;
+        }
+        return 0;
+    }
     const int64_t total = groups * n * W;
 #define TSM_R(T, EL, NTH)                                                                         \
     TSM_LAUNCH((split_reduce_kernel<T, EL, NTH>), dim3((unsigned)((total + EL - 1) / EL)),        \

@@ -262,3 +262,25 @@ def test_buffers_of_many_streams_are_bounded(dev):
     _lib.lib().tsm2x_finalize()
     for h in handles:
         assert hip.hipStreamDestroy(h) == 0
+
+
+def test_ordered_sum_of_more_threads_than_one_launch_has(dev):
+    """A pinned split of a very tall product: the ordered sum of its slices
+    takes eight threads for each of 2^29 outputs, 2^32 threads in all, more than
+    one launch may have.  Small integers, every row exact."""
+    m, k, n = (1 << 24) + 256, 288, 32
+    col = (torch.arange(m, device=dev) % 7 - 3).to(torch.float32)
+    A = col.expand(k, m).contiguous().t()
+    B = torch.ones((n, k), dtype=torch.float32, device=dev).t()
+    tsm.pin_tsm2r(m, k, n, tsm.F32, 9, 1)
+    try:
+        assert tsm.tsm2r_plan(m, k, n, tsm.F32)["slices"] == 9
+        C = tsm.tsm2r(A, B)
+        torch.cuda.synchronize()
+    finally:
+        tsm.unpin_tsm2r(m, k, n, tsm.F32)
+    want = col * k
+    assert all(torch.equal(C[:, p], want) for p in range(n))
+    del A, B, C
+    _lib.lib().tsm2x_finalize()
+    torch.cuda.empty_cache()
