@@ -105,7 +105,7 @@ enum {
  * is split across wavefronts and workgroups and the partial sums are added in
  * double precision in a fixed order.  n > 64 runs in panels of 64 columns of
  * B and C (A read once per panel, as the paper's t2 < n), n > 32 in panels of
- * 32 for the 16-bit forms and transposed A.
+ * 32 for the 16-bit forms, transposed A, m <= 32 and a tall A of few columns.
  * dtype: any tsm_dtype.  Errors: -1..-11 for arguments 1..11. */
 int tsm2r(int64_t m, int64_t k, int64_t n, const void* A, int64_t lda,
           const void* B, int64_t ldb, void* C, int64_t ldc, int dtype,
@@ -360,7 +360,7 @@ int tsm2x_tsm2r_pin(int64_t m, int64_t k, int64_t n, int dtype, int slices, int 
  *                         enqueued by another thread;
  *   tsm2x_timing_row      row i: the kernel's demangled name without its
  *                         namespace and parameter list, e.g.
- *                         "rowtile_kernel<double, 4, 1, 1, true, false>"
+ *                         "rowtile_kernel<double, 4, 1, 1, true, 0>"
  *                         (static storage, valid until the next start), its
  *                         tag, launch count and summed launch time in
  *                         milliseconds.  Returns -1 for i out of range.

@@ -286,8 +286,10 @@ def tsmttsm(A: torch.Tensor, B: torch.Tensor, out: torch.Tensor | None = None,
             beta: float = 0.0, workspace: torch.Tensor | None = None) -> torch.Tensor:
     """C := beta*C + A^T*B for two tall matrices that share their long
     dimension (A m x k and B m x n, F64/F32, m large): the TSMTTSM form the
-    paper names in its related work.  C is k x n; it runs on the reduction
-    kernel of dB = A^T*dC (n in panels of 32 columns)."""
+    paper names in its related work.  C is k x n.  A row-major A of at most 32
+    columns runs on a kernel that reads both matrices by rows, another A on
+    the reduction kernel of dB = A^T*dC (column-major) or as a TSM2R product
+    (row-major)."""
     if A.dim() != 2 or B.dim() != 2 or A.shape[0] != B.shape[0]:
         raise ValueError("tsmttsm: A (m x k) and B (m x n) must share m")
     return gemm(A.t(), B, out=out, beta=beta, workspace=workspace)

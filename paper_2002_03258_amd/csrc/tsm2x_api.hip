@@ -536,8 +536,8 @@ size_t tsm2r_ws(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool tra
 // A column-major A of at most 32 rows, wider than the TSM2L kernels take:
 // both operands are long in k and short otherwise (tsmttsm of row-major
 // matrices), which the tt kernel reads as they stand; the TSM2R kernel tiles
-// rows, of which there are few here, and copies a row-major B (FP32 16 x
-// 1048576, n = 16, B row-major: 172 us, tt 29; B column-major: 122 and 33).
+// rows, of which there are few here (16 x 1048576, n = 16, B row-major: FP32
+// 105 us, tt 28, FP64 86 and 48; B column-major: 101 and 30, 86 and 54).
 // A plan pinned for the shape keeps the TSM2R kernel.
 bool tt_shape(int transA, int64_t m, int64_t k, int64_t n, int dtype) {
     if (transA || m > 32 || k <= 32 || !plain_dtype(dtype)) return false;
@@ -556,8 +556,8 @@ size_t tsm2r_ws_max(int transA, int64_t m, int64_t k, int64_t n, int dtype, bool
 
 // Columns of B and C per pass over A.  A column-major A on the TSM2R kernel
 // takes 64: with two passes of 32 the second reads A again, and the kernel is
-// bound by the matrix cores at 64 (20480^2, n = 64: FP64 1313 us in two
-// passes, 946 in one, FP32 659 and 551; n = 33: 1119 and 722, 544 and 397).  32 elsewhere, for a caller's workspace that holds
+// bound by the matrix cores at 64 (20480^2, n = 64: FP64 1270 us in two
+// passes, 918 in one, FP32 590 and 501; n = 33: 1109 and 685, 544 and 377).  32 elsewhere, for a caller's workspace that holds
 // the partials of 32 columns only, and where a plan of a narrower panel is
 // pinned.  Also for a tall A of few columns, where a wavefront has too few
 // steps to gain back what its fewer neighbours cost: FP64 beyond 48 columns

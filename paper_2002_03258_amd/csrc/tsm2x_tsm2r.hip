@@ -1,5 +1,6 @@
 // TSM2R on gfx950 (MI355X): C = A*B with column-major A (m x k, k large) and
-// B (k x n), n <= 32.  The kernel, its instances and the grid planner.
+// B (k x n), up to 64 columns in one pass.  The kernel, its instances and the
+// grid planner.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -87,7 +88,10 @@ __attribute__((amdgpu_waves_per_eu(nn_waves<T, NT16>(), 8))) void tsm2r_nn_kerne
 #pragma unroll
             for (int t = 0; t < NT16; ++t) acc[g][q][t] = Acc{0, 0, 0, 0};
     // the second set of sums, where registers allow it (n = 17..32 has none
-    // to spare; 49..64 spills 11 of them, 3 %)
+    // to spare; with 49..64 columns 11 registers spill for a column-major B, 3 %,
+    // and 52 or 84 for a row-major one, whose scratch accesses lie in the loop
+    // and which runs no slower for it: 20480^2, n = 64, 500 us and 504
+    // column-major.  FP64 spills 101 and 108 there, outside its loop, flush or not)
     constexpr bool FL = sizeof(T) == 4 && RG <= 2 && (NT16 == 1 || RG == 1);
     constexpr int NA = RG * RL * NT16;
     typedef Acc Flat[NA];
@@ -392,7 +396,7 @@ static inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // never formed).  Where neither rule fills 7/8 of the CUs, for the 64 columns
 // per wavefront or the 4 % for the partials, the split goes on to two chunks
 // per wavefront: idle CUs cost more than partials do (FP32 3001^2, n = 20, 24
-// workgroups 60 us, 240 22; 512 x 28032, n = 8, 136 and 252: 33 and 17; FP64
+// workgroups 60 us, 240 18; 512 x 28032, n = 8, 136 and 252: 33 and 17; FP64
 // 256 x 28032, n = 24, 136 and 252: 24 and 22).  pf is also on for n > 16 and
 // FP32 with n <= 4, with any grid (tsm2r_nn_kernel), and for every grid of at
 // most one workgroup per CU (FP64 4096^2, n = 8, 192 workgroups: 42 us without,
@@ -544,8 +548,11 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
                 take = W <= cus && (W > have || P->tall) && cost < a / have;
             }
             // float sums of 17..32 columns are not flushed (tsm2r_nn_kernel):
-            // no longer chains than the plan without the prefetch gave an A
-            // off the 128-byte lines
+            // off the 128-byte lines no longer chains than the plan without
+            // the prefetch has.  With them n = 32 would run 7 to 15 % faster
+            // (30004 x 30000 665 and 618 us, 16004^2 208 and 182) at an error
+            // half as large again (16004^2: 5.7e-7 and 8.0e-7); on the lines
+            // the plan has them
             if (dtype == DT_F32 && np == 32 && !line && cdiv64(k, ks) < P->S) take = false;
             if (take) {
                 P->fn = I.fn;

@@ -8,8 +8,8 @@
 // Y[r, 16 b + rl], one row r per kk.  Sixteen lanes read sixteen consecutive
 // values of a row, so an instruction reads whole rows of a row-major X and Y
 // in the operand order as they stand: no transposed copy of Y, nothing
-// through LDS.  (The TSM2R kernel, which tiles the rows of C, kept 4 to 8 of
-// 64 lanes on such a matrix, after a pass that copied Y column-major.)
+// through LDS.  (The TSM2R kernel, which tiles the rows of C, keeps 4 to 8 of
+// 64 lanes on such a matrix.)
 //
 // A column-major Y (YROW false) gives each lane RL consecutive rows of one
 // column in one 16-byte load; the steps then take the rows in that order.
