@@ -688,9 +688,10 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
     // and its launch, where a wavefront has up to 256 rows of it (1024^2, n = 4:
     // FP32 10.2 us and 11.4 with the copy, FP64 9.0 and 11.4; FP64 2048^2, n = 16,
     // 128 rows: 12.2 and 14.6; but FP32 1448^2, n = 4, 384 rows: 14.6 and 11.4;
-    // 2048^2, 512: 18.1 and 11.6) and the grid is not so large that its
-    // workgroups' loads add up (FP32 8192 x 256, n = 16, 256 workgroups: 7.7 and
-    // 11.5; 65536 x 128, 2048: 16.7 and 15.5).
+    // 2048^2, 512: 18.1 and 11.6; FP64 1448^2, 384 rows: n = 4 10.5 and 11.5, n =
+    // 8 14.3 and 11.5) and the workgroups' rows come to no more than 256 on a CU
+    // (FP32 8192 x 256, n = 16, 64 rows in 256 workgroups: 7.7 and 11.5; 15808 x
+    // 784, n = 16, 256 in 988: 43 and 39; 65536 x 128, 64 in 2048: 16.7 and 15.5).
     bool direct = plain_dtype(dtype) && transB && !transA;
     NNPlan P{};
     TNPlan T{};
@@ -700,8 +701,9 @@ int product(bool lform, int transA, int transB, int64_t m, int64_t k, int64_t n,
             plan_tsm2r_lp(m, k, n, dtype, cus, avec, &P, fine);
         } else if (transA) {
             T = plan_tn(k, m, n, dtype, cus, fine);
-            direct = transB && n <= 16 && (k <= 256 || T.rslice <= 4 * 256) &&
-                     T.groups / T.ct * T.S <= 4 * (int64_t)cus;
+            const int64_t rows = T.rslice / 4 < k ? T.rslice / 4 : k;
+            direct = transB && n <= 16 && rows <= (dtype == TSM_F64 && n <= 4 ? 384 : 256) &&
+                     T.groups / T.ct * T.S * rows <= 256 * (int64_t)cus;
         } else if (plan_nn(m, k, n, dtype, cus, avec, &P, fine)) {
             return false;
         }

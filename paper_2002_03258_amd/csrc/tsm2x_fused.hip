@@ -290,11 +290,13 @@ static int bwd_launch(const LaunchBwd& L, int64_t* blocks_out, hipStream_t st, b
     // and 666 cached).  Also where a wavefront has a tile or two and the last
     // is not whole: its element-wise loads wait for each other in the cached
     // instance and hold up the call (127741 x 32, n = 32: FP64 35 and 45 us,
-    // FP32 27 and 34; 50000 x 32: FP32 20 and 29)
+    // FP32 27 and 34; 50000 x 32: FP32 20 and 29; but FP64 54986 x 27, n = 16,
+    // fewer workgroups than CUs: 17.8 and 16.8)
     const int64_t es = sizeof(T);
     const bool line = ((AF >= 0 || line_aligned(L.A, L.lda * es)) && line_aligned(L.dC, L.lddc * es) &&
                        line_aligned(L.dA, L.ldda * es, 64)) ||
-                      (need <= (int64_t)L.cus * (occ > 1 ? occ : 2) && L.m % TR != 0);
+                      (need <= (int64_t)L.cus * (occ > 1 ? occ : 2) && L.m % TR != 0 &&
+                       (es == 4 || need > L.cus));
     const uint16_t* alo = ASPLIT ? (const uint16_t*)L.A + L.lda * L.k : nullptr;
     dim3 g((unsigned)bx), b(256);
 #define TSM_B(LINE, PV)                                                                            \

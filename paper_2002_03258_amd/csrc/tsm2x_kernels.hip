@@ -614,15 +614,19 @@ static int rowtile_launch_st(const LaunchRT& L, hipStream_t st) {
 // column of one row tile: on 64 bytes (FP64 1000 x 100000, kin = 16: 150 and
 // 240; 10008 x 10000: 250 and 342 at kin = 32), and for kin > 16 on any
 // alignment, whose tiles are half as high (FP32 10001 x 3000: 44 and 61; kin =
-// 8: 57 and 41), but for a few tiles.  A next-tile register prefetch was measured and
+// 8: 57 and 41), but for a few tiles and below 8 MB, which the caches take
+// (FP32 1017 x 1022, kin = 32: 9.9 and 8.5); from 2^16 rows on X too on 64
+// bytes (FP64 296864 x 160, kin = 8, X off it: 104 and 98; but 128 x 400000, kin
+// = 16: 131 and 161).  A next-tile register prefetch was measured and
 // dropped: the extra waves it costs hid the latency better.
 template <typename T, int KS, int NT16, int RG>
 static int rowtile_launch(const LaunchRT& L, hipStream_t st) {
     const int64_t es = sizeof(T);
     bool line = (L.x_rowmajor || line_aligned(L.X, L.ldx * es)) && line_aligned(L.O, L.ldo * es);
-    if (L.nout > 32)
-        line = line_aligned(L.O, L.ldo * es, 64) || (KS == 8 && L.m >= 256);
-    else if (!L.x_rowmajor && (KS < 8 || L.m <= (int64_t)1 << 20))
+    if (L.nout > 32 && L.m * L.nout * es >= (int64_t)1 << 23)
+        line = (line_aligned(L.O, L.ldo * es, 64) && (L.m < 1 << 16 || line_aligned(L.X, L.ldx * es, 64))) ||
+               (KS == 8 && L.m >= 256);
+    else if (L.nout <= 32 && !L.x_rowmajor && (KS < 8 || L.m <= (int64_t)1 << 20))
         line = L.kin + L.nout <= 6 ||
                (line_aligned(L.X, L.ldx * es, 64) && line_aligned(L.O, L.ldo * es, 64));
     const int rowx = !L.x_rowmajor ? 0 : L.kin == 4 * KS ? 1 : 2;

@@ -530,9 +530,7 @@ int plan_tsm2r(int64_t m, int64_t k, int64_t n, int dtype, int cus, bool line, N
             };
             auto slice = [&](int64_t S) { return cdiv64(cdiv64(k, S), gran) * gran; };
             int64_t ks = slice(split(false)), W = tiles * cdiv64(k, ks);
-            // (a matrix of fewer rows than a tile runs without the prefetch: FP32
-            // 100 x 1000000, n = 4: 173 us with 256 workgroups, 154 with 480)
-            bool take = m >= I.tile_rows && W <= cus && 8 * W >= 7 * (int64_t)cus;
+            bool take = W <= cus && 8 * W >= 7 * (int64_t)cus;
             const int64_t have = P->tiles * P->S;
             if (fine && !take && 8 * have < 7 * (int64_t)cus) {
                 // the plan so far leaves CUs idle
