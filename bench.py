@@ -360,14 +360,14 @@ def rows_kmeans(dev):
 
 
 def rows_general(dev):
-    """Shapes beyond one kernel launch: n > 32 in 32-column panels (A read once
-    per panel, the paper's t2 < n), a TSM2L-class product with k > 32 (on the
+    """Shapes beyond one kernel launch: n > 32 in panels of up to 64 columns (A
+    read once per panel, the paper's t2 < n), a TSM2L-class product with k > 32 (on the
     TSM2R kernels), and the dispatching gemm with a row-major B and beta = 1.
     GB/s counts the bytes each product moves."""
     import oracle
     out = []
     seed = si.config_seed(6)
-    cases = [("TSM2R n = 64 in two panels", "tsm2r", torch.float64, 20480, 20480, 64, False, 0.0),
+    cases = [("TSM2R n = 64 in one panel", "tsm2r", torch.float64, 20480, 20480, 64, False, 0.0),
              ("TSM2L class with k = 64", "tsm2l", torch.float64, 1 << 22, 64, 16, False, 0.0),
              ("gemm, row-major B, beta = 1", "gemm", torch.float32, 30720, 30720, 16, True, 1.0)]
     for name, fn, dtype, m, k, n, rowB, beta in cases:
@@ -387,7 +387,7 @@ def rows_general(dev):
             ref = ref + beta * C0[rows].double().cpu().numpy()
         e = oracle.normwise_error(C[rows].double().cpu().numpy(), ref)
         t = timed(lambda: f(A, B, out=C, beta=beta))
-        panels = (n + 31) // 32 if fn == "tsm2r" else 1
+        panels = (n + 63) // 64     # a square A, column-major float or double
         nb = (panels * m * k + k * n + (2 if beta != 0 else 1) * m * n) * es(dtype)
         out.append({"row": "general shapes: %s (m=%d k=%d n=%d)" % (name, m, k, n),
                     "dtype": str(dtype).replace("torch.", ""), "GBps": nb / t / 1e9,
