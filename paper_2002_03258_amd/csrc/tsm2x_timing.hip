@@ -55,7 +55,7 @@ hipEvent_t take_event() {
     return e;
 }
 
-// "tsm2l_bwd_kernel<double, 1, 1, 2, true, -1, false>": the demangled name
+// "tsm2l_bwd_kernel<double, 1, 1, 2, true, true, -1, false>": the demangled name
 // without return type, namespace and parameter list
 std::string kernel_name(const void* fn, hipStream_t st) {
     auto it = g_names.find(fn);
